@@ -61,6 +61,7 @@ Grid make_grid(const sph_box &b, double h_max, int64_t cell_cap, int max_axis)
 {
     Grid g{};
     const double want = 2.0 * h_max * (1.0 + 1e-9);
+    g.reach = 2.0 * h_max;
     for (int a = 0; a < 3; ++a) {
         g.periodic[a] = b.periodic[a];
         g.lo[a] = b.lo[a];
@@ -296,7 +297,7 @@ void free_ctx(sph_ctx ctx)
     if (ctx->step_graph) (void)hipGraphDestroy(ctx->step_graph);
     void *ptrs[] = {ctx->keys[0], ctx->keys[1], ctx->vals[0], ctx->vals[1], ctx->hist,
                     ctx->scan_part, ctx->cell_start, ctx->cell_end, ctx->perm_tmp,
-                    ctx->perm_tmp_id, ctx->red_part, ctx->status_dev, ctx->nb_mask, ctx->hflag_dev,
+                    ctx->perm_tmp_id, ctx->red_part, ctx->status_dev, ctx->hflag_dev,
                     ctx->fb_tiles, ctx->fb_count, ctx->it_words, ctx->it_hmax, ctx->cell_s2max,
                     ctx->iad_c, ctx->dtc, ctx->blk_words,
                     ctx->srec, ctx->drec, ctx->prec};
@@ -377,7 +378,6 @@ sph_status sph_ctx_create(sph_ctx *out, int64_t n_max, int32_t max_nb, sph_strea
     ALLOC(ctx->cell_end, ctx->cell_cap);
     ALLOC(ctx->cell_s2max, ctx->cell_cap);
     ALLOC(ctx->iad_c, 6 * n_max);
-    ALLOC(ctx->nb_mask, (int64_t)kSearchMaskWords * ((n_max + 63) / 64) * 64);
     ALLOC(ctx->fb_tiles, (n_max + 63) / 64);
     ALLOC(ctx->fb_count, 1);
     ALLOC(ctx->it_words, kItWords);

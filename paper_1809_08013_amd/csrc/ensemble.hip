@@ -222,7 +222,6 @@ int64_t arena_bytes_per_particle(int max_nb)
     const int64_t scratch = 2 * 4 + 2 * 4     // keys, vals (double-buffered)
                             + 1               // sort histograms (256 / 2048 * 4)
                             + 1               // cell table (cap / 8 cells * 8 B)
-                            + kSearchMaskWords * 4  // search bit masks
                             + 32 + 32 + 128   // search, density, pair records
                             + kPermFields * 8 + 4;  // reorder scratch
     return arena + scratch;

@@ -1,42 +1,51 @@
 // Algorithm 1, step 2 on the GPU: the neighbour search.
 //
-// One wavefront per tile of 64 consecutive particles (cell order), four
-// independent wavefronts per block. The wave first builds, in its own LDS
-// region, the union of the 27-cell stencils of the cells its particles live
-// in: the non-empty cells, sorted by their first particle and without
-// duplicates, so walking them visits candidates in ascending index order. It
-// then streams that union wave-uniformly: each candidate's record is one
-// scalar load into SGPRs, every lane tests it against its own particle with
-// the exact FP64 relation, and the outcome goes into a per-lane bit mask (one
-// bit per union position, kept in a global scratch region so that the LDS
-// footprint stays small and occupancy high; each 32-bit word of 64 lanes is
-// one 256-byte store). A second phase expands the masks row by row, so that
-// all lanes write row k of the ELL list together (one contiguous 256-byte
-// store per row) instead of scattering 4-byte writes; a per-wave table maps
-// each union position to its cell, so a set bit becomes an index with two
-// LDS reads.
+// The particles are taken in tiles of 64 consecutive ones (cell order). A
+// tile's wave or waves build the union of the 27-cell stencils of the cells its
+// particles live in: the non-empty cells, each cut to the part within reach
+// of the tile, sorted by first particle, so that walking them visits
+// candidates in ascending index order. The union is walked in blocks of 64
+// candidates.
 //
-// Periodic axes: when no stencil of the tile reaches across a periodic
-// boundary the image test is skipped. Otherwise, when every periodic axis has
-// at least 5 cells, the image is chosen once per (union cell, lane) from the
-// cell indices: a true neighbour lies in an adjacent cell, and for adjacent
-// cells the wrapped ones are exactly those whose raw difference exceeds half
-// the box, so adding -L, 0 or +L to the raw difference reproduces the
-// minimum-image arithmetic (d -= L or d += L) for every true neighbour; for
-// any other candidate a wrong image only makes the distance larger than half
-// the box, i.e. larger than 2 h_max, and it is rejected either way. With
-// fewer cells the image is chosen per candidate.
+// The relation of a block, 64 candidates x 64 particles, is a contraction:
+//   d_ji = |x_j|^2 - 2 x_j . x_i + (|x_i|^2 - s_i^2),  s = 2h,
+// in coordinates relative to the tile's centre and scaled by the largest
+// reach, so sixteen FP32 matrix products of 16 x 16 x 4 give it, and the sign
+// bits are shifted out of the accumulators, one vector instruction per 64
+// pairs. The relation itself is FP64 (r^2 < s^2, strictly, with r^2 =
+// fma(dz, dz, fma(dy, dy, dx dx))): the FP32 value only has to tell on which
+// side of zero d lies, and a pair with |d| under a bound eps on its error is
+// settled by the FP64 relation on its own. With u = 2^-24, coordinates rounded
+// to FP32 and t = |x_i| + |x_j| (for a pair at the reach at most 2 max|x_i| +
+// 1): four roundings of partial sums below t^2 + 1, three in |x_j|^2, one in
+// the start value, and 2 r u t from the coordinates: u (5 t^2 + 2 t + 8)
+// (measured: at most half of it); eps is 1.2 times that. (For a pair farther
+// away the error grows as t^2 but d as the square of its distance.) On a
+// 1%-jittered lattice, where 30 pairs of every particle lie within 1% of the
+// reach, one block in ten holds such a pair; lattice points exactly on the
+// shell are such pairs. So the lists are exactly those of the FP64 relation.
 //
-// A wave whose union has more candidates than the masks hold (dense cells)
-// streams the same union but lets each lane append its accepted candidates
-// directly; when no image is in play it walks, in each cell, only the z
-// slices (the lowest key bits order a cell's particles by z) within reach of
-// the tile's z extent. A wave with more distinct cells than its union build
-// holds (9), or with a union of many dense cells, takes
-// the per-lane path instead: each lane walks its own stencil (sorted by
-// Morton key) and writes its entries directly. Both paths produce the same set in the
-// same (ascending) order, so the sums over a list do not depend on the path
-// or on where the tile boundaries fall.
+// The bits (two 32-bit words a lane and block) stay in LDS, and each lane then
+// walks its own words and writes its list, row k of all lanes together. A
+// union of more candidates than LDS has bits for is taken in several chunks.
+// One wave does a tile; small runs put four on each, every wave taking a
+// quarter of the candidates.
+//
+// Periodic axes: every position is taken as its image nearest to the tile's
+// centre. Where the tile's extent from its centre plus the reach stays below
+// half the box, the difference of two such images is the minimum image for
+// every true neighbour (both lie within that distance of the centre) and
+// larger than the reach for every other pair. On a shorter axis a neighbour may
+// be the candidate's other image: a block with candidates so far out is tested
+// with both (no particle is within reach of two images, the axis being longer
+// than twice the reach). Blocks with a coordinate that FP32 cannot hold take
+// the FP64 relation with the minimum image for every pair.
+//
+// A tile with more distinct cells than its union build holds (9 or 18) takes the
+// per-lane path in a second kernel: each lane walks its own stencil (sorted by
+// Morton key) and writes its entries directly. Both paths produce the same set
+// in the same (ascending) order, so the sums over a list do not depend on the
+// path or on where the tile boundaries fall.
 #include <algorithm>
 #include <climits>
 
@@ -46,22 +55,29 @@ namespace sph {
 namespace {
 
 constexpr int kWave = 64;
-constexpr int kWavesPerBlock = 4;
-constexpr int kBlock = kWave * kWavesPerBlock;
-constexpr int kMaxCandidates = kSearchMaskWords * 32;
-// Stencil entries (27 per distinct cell, before dedup) a tile's union build
-// holds: 9 distinct cells (tiles of small runs, and tiles of a rotated
-// lattice after some steps, span more than four). Tiles with at most 4 sort
-// only the first 128 entries.
-constexpr int kEntries = 256;
-// Cells of a union handed to the second kernel (held two per lane there).
-constexpr int kDenseCells = 2 * 64;
-constexpr int kMaxWords = kSearchMaskWords;
-// Grid of the second kernel: one-wave blocks draining the worklist, up to 32
-// per CU (its occupancy limit is 5 waves per SIMD); the blocks past the
-// worklist's length exit at once. 2048 blocks left the dense centre of a 1M
-// Evrard sphere on 2 waves per SIMD (search 3.9 ms, 3.0 ms with this grid).
-constexpr int64_t kFallbackBlocks = 8192;
+// Shape of the search for W waves per tile. kMaxDist: distinct cells of a
+// tile that the union build takes (27 stencil entries each), kCells: cells of
+// the union after the cells out of reach are dropped; kBlocks: blocks of 64
+// candidates whose relation bits LDS holds at a time (a larger union is
+// taken in several chunks).
+//   W = 1: one wave does a tile. 22 blocks = 1,408 candidates (the mean union
+//          of the 1M patch is 1,150) leave 11 tiles on a CU.
+//   W = 4: four waves share one, for runs too small to fill the chip.
+template <int W>
+struct SearchShape;
+template <>
+struct SearchShape<1> {
+    static constexpr int kMaxDist = 9, kEntries = 256, kCells = 92, kBlocks = 16;
+    typedef uint8_t Cell;
+};
+template <>
+struct SearchShape<4> {
+    static constexpr int kMaxDist = 18, kEntries = 512, kCells = 486, kBlocks = 28;
+    typedef uint16_t Cell;
+};
+// Grid of the second kernel: one-wave blocks draining the worklist; the blocks
+// past the worklist's length exit at once.
+constexpr int64_t kFallbackBlocks = 2048;
 
 enum WrapMode { WRAP_NONE = 0, WRAP_CELL = 1, WRAP_PAIR = 2 };
 
@@ -112,25 +128,6 @@ __device__ __forceinline__ int wrap_or_clip(int c, int nc, int periodic, bool &o
     return c;
 }
 
-// Squared separation of the relation test, with the image conventions of
-// the mode. sh: the per-cell image shift (WRAP_CELL).
-template <int Mode>
-__device__ __forceinline__ double sep2(const SearchRec &me, const SearchRec &o, const Grid &g,
-                                       const double (&sh)[3])
-{
-    double dx = me.x - o.x, dy = me.y - o.y, dz = me.z - o.z;
-    if (Mode == WRAP_CELL) {
-        dx += sh[0];
-        dy += sh[1];
-        dz += sh[2];
-    } else if (Mode == WRAP_PAIR) {
-        if (g.periodic[0]) dx = min_image_sel(dx, g.len[0], g.half[0]);
-        if (g.periodic[1]) dy = min_image_sel(dy, g.len[1], g.half[1]);
-        if (g.periodic[2]) dz = min_image_sel(dz, g.len[2], g.half[2]);
-    }
-    return __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
-}
-
 // A double that is the same in every lane, as a wave-uniform value.
 __device__ __forceinline__ double uniform_f64(double v)
 {
@@ -138,36 +135,6 @@ __device__ __forceinline__ double uniform_f64(double v)
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u);
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-
-// acc * 2 + [r2 < s2], s2 wave-uniform: the comparison's lane mask is the
-// carry-in of one add (acc + acc + carry), which shifts the bit in.
-__device__ __forceinline__ uint32_t shift_in(uint32_t acc, double r2, double s2)
-{
-    uint32_t out;
-    asm("v_cmp_gt_f64 vcc, %2, %1\n\t"
-        "v_addc_co_u32 %0, vcc, %3, %3, vcc"
-        : "=v"(out)
-        : "v"(r2), "s"(s2), "v"(acc)
-        : "vcc");
-    return out;
-}
-
-// acc * 2 + [r2 < s2a or r2 < s2b], s2b wave-uniform: the two lane masks are
-// joined on the scalar unit (comparing against the larger of the two would
-// cost two more vector instructions).
-__device__ __forceinline__ uint32_t shift_in2(uint32_t acc, double r2, double s2a, double s2b)
-{
-    uint32_t out;
-    uint64_t t;
-    asm("v_cmp_lt_f64 %1, %2, %3\n\t"
-        "v_cmp_gt_f64 vcc, %4, %2\n\t"
-        "s_or_b64 vcc, vcc, %1\n\t"
-        "v_addc_co_u32 %0, vcc, %5, %5, vcc"
-        : "=v"(out), "=&s"(t)
-        : "v"(r2), "v"(s2a), "s"(s2b), "v"(acc)
-        : "vcc", "scc");
-    return out;
 }
 
 // Relation test: r2 < (2h_i)^2 or r2 < (2h_j)^2, i.e. r2 < (2 max(h_i,h_j))^2.
@@ -192,204 +159,18 @@ __device__ __forceinline__ bool related(const SearchRec &me, const SearchRec &o,
     return (r2 < me.s2) | (r2 < o.s2);
 }
 
-// Per-wave LDS, overlaid by lifetime: the union cells are formed from the
-// sorted entries (all entries are read before the first cell is written);
-// the position -> cell table is filled after the stream and the self-bit
-// removal, when the cells are no longer read; the first union positions are
-// written once the distinct keys have been read. At 256 entries this is 5 KiB
-// per wave, 20 KiB per block: 8 blocks per CU.
-template <int E>
-struct SearchLds {
-    static_assert(E % (2 * kWave) == 0 && E <= 256, "entries: whole pairs per lane, uint8 cells");
-    union {
-        struct {
-            union {
-                int2 ent[E];      // stencil entries {first particle, entry index}
-                int2 cells[E];    // union cells {first, end}, ascending (formed from ent)
-            };
-            uint32_t cxyz[E];     // packed cell coordinates x | y << 10 | z << 20
-        };
-        uint8_t cellof[kMaxCandidates];   // union position -> union cell
-    };
-    union {
-        uint32_t dkeys[kWave];    // keys of the tile's distinct cells
-        int u0[E];                // first union position of each cell
-    };
-    int base[E];                  // first particle minus first union position
-};
-
-// Stream the union (cells[0..nu)) and record, for each candidate u, whether
-// it is related to the lane's particle. Masks are 32-bit words bm[word][lane]
-// (word = u / 32) filled from the top: candidate u sits at bit 31 - u % 32.
-// Within a cell the next four records are loaded while the current four are
-// tested, so the scalar-load latency is overlapped with work.
-template <int Mode, bool UniformH, int E>
-__device__ __forceinline__ void stream_union(const SearchRec &me, const int (&myc)[3],
-                                             const SearchRec *__restrict__ srec,
-                                             const SearchLds<E> &L, int nu, const Grid &g,
-                                             uint32_t *__restrict__ bm, int lane, int &cnt,
-                                             uint64_t &occ0, uint32_t &occ1)
-{
-    uint32_t acc = 0;
-    int u = 0;
-    double sh[3] = {0.0, 0.0, 0.0};
-    auto flush = [&](int w, uint32_t word) {
-        bm[w * kWave + lane] = word;
-        cnt += __popc(word);
-        if (w < 64) occ0 |= word ? (1ull << w) : 0ull;
-        else occ1 |= word ? (1u << (w - 64)) : 0u;
-    };
-    auto step = [&](const SearchRec &o) {
-        const double r2 = sep2<Mode>(me, o, g, sh);
-        // uniform h: every (2h)^2 is the same number, the candidate's is
-        // taken (a scalar operand, and the whole record is then loaded in
-        // wide scalar loads)
-        acc = UniformH ? shift_in(acc, r2, o.s2) : shift_in2(acc, r2, me.s2, o.s2);
-        ++u;
-        if ((u & 31) == 0) {
-            flush((u >> 5) - 1, acc);
-            acc = 0;
-        }
-    };
-    for (int c = 0; c < nu; ++c) {
-        const int s = __builtin_amdgcn_readfirstlane(L.cells[c].x);
-        const int e = __builtin_amdgcn_readfirstlane(L.cells[c].y);
-        if (Mode == WRAP_CELL) {
-            const uint32_t p = __builtin_amdgcn_readfirstlane(L.cxyz[c]);
-            const int cc[3] = {(int)(p & 1023u), (int)((p >> 10) & 1023u), (int)(p >> 20)};
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                const int d = cc[a] - myc[a];
-                sh[a] = !g.periodic[a] ? 0.0 : (d >= 2 ? g.len[a] : (d <= -2 ? -g.len[a] : 0.0));
-            }
-        }
-        int j = s;
-        if (e - j >= 4) {
-            SearchRec a0 = srec[j], a1 = srec[j + 1], a2 = srec[j + 2], a3 = srec[j + 3];
-            j += 4;
-            while (e - j >= 4) {
-                const SearchRec b0 = srec[j], b1 = srec[j + 1], b2 = srec[j + 2],
-                                b3 = srec[j + 3];
-                // issue the loads of b0..b3 before the work on a0..a3
-                __builtin_amdgcn_sched_barrier(0);
-                step(a0);
-                step(a1);
-                step(a2);
-                step(a3);
-                // keep the wait for b0..b3 (scalar loads complete out of order,
-                // so it is a full wait) after the work on a0..a3
-                __builtin_amdgcn_sched_barrier(0);
-                a0 = b0;
-                a1 = b1;
-                a2 = b2;
-                a3 = b3;
-                j += 4;
-            }
-            step(a0);
-            step(a1);
-            step(a2);
-            step(a3);
-        }
-        for (; j < e; ++j) step(srec[j]);
-    }
-    if (u & 31) flush(u >> 5, acc << (32 - (u & 31)));
-}
-
-// Stream a union too large for the masks (dense cells): the same
-// wave-uniform walk, each lane appending its accepted candidates to its own
-// list as it goes (few candidates pass, so the scattered stores are rare).
-// The union is held across the lanes: lane l has cell l in r0/p0 (range,
-// packed coordinates) and cell l + 64 in r1/p1.
-template <int Mode, bool UniformH>
-__device__ __forceinline__ int stream_direct(const SearchRec &me, const int (&myc)[3],
-                                             const SearchRec *__restrict__ srec, int2 r0,
-                                             int2 r1, uint32_t p0, uint32_t p1, int nu,
-                                             const Grid &g, bool active, int64_t i, int64_t ld,
-                                             int max_nb, int32_t *__restrict__ idx)
-{
-    int cnt = 0;
-    double sh[3] = {0.0, 0.0, 0.0};
-    const int32_t ii = active ? (int32_t)i : -1;
-    auto step = [&](const SearchRec &o, int32_t j) {
-        if (related<Mode, UniformH>(me, o, g, sh) && j != ii && active) {
-            if (cnt < max_nb) idx[(int64_t)cnt * ld + i] = j;
-            ++cnt;
-        }
-    };
-    for (int c = 0; c < nu; ++c) {
-        const bool hi_half = c >= kWave;
-        const int cl = c & (kWave - 1);
-        const int s = __builtin_amdgcn_readlane(hi_half ? r1.x : r0.x, cl);
-        const int e = __builtin_amdgcn_readlane(hi_half ? r1.y : r0.y, cl);
-        if (Mode == WRAP_CELL) {
-            const uint32_t p = (uint32_t)__builtin_amdgcn_readlane((int)(hi_half ? p1 : p0), cl);
-            const int cc[3] = {(int)(p & 1023u), (int)((p >> 10) & 1023u), (int)(p >> 20)};
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                const int d = cc[a] - myc[a];
-                sh[a] = !g.periodic[a] ? 0.0 : (d >= 2 ? g.len[a] : (d <= -2 ? -g.len[a] : 0.0));
-            }
-        }
-        int j = s;
-        if (e - j >= 4) {
-            SearchRec a0 = srec[j], a1 = srec[j + 1], a2 = srec[j + 2], a3 = srec[j + 3];
-            j += 4;
-            while (e - j >= 4) {
-                const SearchRec b0 = srec[j], b1 = srec[j + 1], b2 = srec[j + 2],
-                                b3 = srec[j + 3];
-                step(a0, j - 4);
-                step(a1, j - 3);
-                step(a2, j - 2);
-                step(a3, j - 1);
-                __builtin_amdgcn_sched_barrier(0);
-                a0 = b0;
-                a1 = b1;
-                a2 = b2;
-                a3 = b3;
-                j += 4;
-            }
-            step(a0, j - 4);
-            step(a1, j - 3);
-            step(a2, j - 2);
-            step(a3, j - 1);
-        }
-        for (; j < e; ++j) step(srec[j], j);
-    }
-    return cnt;
-}
-
-// Window of a union cell for a dense tile (no periodic image in play): the
-// sub-range of the cell's particles that can hold a candidate related to a
-// particle of the tile, R^2 being the larger of the tile's and the cell's
-// largest (2h)^2.
-// - The whole cell is skipped when its x or y range lies more than R + a
-//   millionth of a cell beyond the tile's extent [lo, hi] on that axis: every
-//   candidate is then farther than both smoothing diameters from every
-//   particle of the tile (a particle's cell index comes from the same
+// Window of a cell for an extent [lo, hi] and a reach r (no periodic image in
+// play): the sub-range of the cell's particles that can hold a point within r.
+// - The whole cell is skipped when its x or y range lies more than r + a
+//   millionth of a cell beyond the extent on that axis: every candidate is
+//   then farther than r (a particle's cell index comes from the same
 //   arithmetic, whose rounding is some 1e-13 of a cell).
-// - Otherwise only the z slices within R + (one slice) of the tile's z
-//   extent are kept, by the same argument; a cell's keys are ordered by
-//   slice, so the window is found by binary search.
+// - Otherwise only the z slices within r + (one slice) of the z extent are
+//   kept, by the same argument; a cell's keys are ordered by slice, so the
+//   window is found by binary search.
 // The first and last cell of an axis also hold the particles clamped into
 // them from outside the box, so their range is taken as unbounded on the
 // outer side, and their outer slice is always kept.
-// z_window_r: the same for a given reach r (s2max not read).
-__device__ __forceinline__ int2 z_window_r(int2 cr, uint32_t p, const Grid &g,
-                                           const double (&tlo)[3], const double (&thi)[3],
-                                           double r, const uint32_t *__restrict__ keys);
-
-__device__ __forceinline__ int2 z_window(int2 cr, uint32_t p, const Grid &g, const double (&tlo)[3],
-                                         const double (&thi)[3], double s2t,
-                                         const unsigned long long *__restrict__ s2max,
-                                         const uint32_t *__restrict__ keys)
-{
-    if (cr.x >= cr.y) return cr;
-    const int x = (int)(p & 1023u), y = (int)((p >> 10) & 1023u), z = (int)(p >> 20);
-    const int64_t cell = ((int64_t)z * g.nc[1] + y) * g.nc[0] + x;
-    const double s2c = __longlong_as_double((long long)s2max[cell]);
-    return z_window_r(cr, p, g, tlo, thi, sqrt(fmax(s2t, s2c)), keys);
-}
-
 __device__ __forceinline__ int2 z_window_r(int2 cr, uint32_t p, const Grid &g,
                                            const double (&tlo)[3], const double (&thi)[3],
                                            double r, const uint32_t *__restrict__ keys)
@@ -431,39 +212,245 @@ __device__ __forceinline__ int2 z_window_r(int2 cr, uint32_t p, const Grid &g,
     return make_int2(first, a);
 }
 
-// One tile of 64 particles. Multi: the particles belong to one run of an
-// ensemble (slot in the high key bits) and the tile uses that run's grid
-// and cell range; a tile found spanning two runs would take the per-lane
-// path with each lane's own run.
-template <bool Multi>
+// Window of a union cell (coordinates cc) for a tile of the given centre and
+// half extents and a reach r, on images nearest to the centre: an empty range
+// when the cell lies more than r + a millionth of a cell beyond the tile on
+// some axis, else the z slices within r + (one slice) of the tile's z extent.
+// The same bounds as z_window_r, and as there the outer side of an open axis'
+// border cells is unbounded. Only a cell of kWindowMin particles or more is
+// searched for its slices: a shorter one costs less tested whole.
+constexpr int kWindowMin = 48;
+__device__ __forceinline__ int2 tile_window(int2 cr, const int (&cc)[3], const Grid &g,
+                                            const double (&ctr)[3], const double (&ext)[3],
+                                            double r, const uint32_t *__restrict__ keys)
+{
+    double fl = 0.0, fh = 0.0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        // low face of the cell from the centre, in cells
+        double d = (double)cc[a] - (ctr[a] - g.lo[a]) * g.inv_s[a];
+        if (g.periodic[a]) {
+            const double half = 0.5 * g.nc[a];
+            if (d + 0.5 > half) d -= g.nc[a];
+            else if (d + 0.5 < -half) d += g.nc[a];
+        }
+        const double e = (ext[a] + r) * g.inv_s[a] + 1e-6;
+        const bool above = d > e && (g.periodic[a] || cc[a] > 0);
+        const bool below = d + 1.0 < -e && (g.periodic[a] || cc[a] < g.nc[a] - 1);
+        if (above || below) return make_int2(cr.x, cr.x);
+        fl = -e - d;
+        fh = e - d;
+    }
+    if (cr.y - cr.x < kWindowMin) return cr;
+    const double ns = (double)(1 << g.zbits);
+    double ql = fmax(floor(fl * ns) - 1.0, 0.0);
+    double qh = fmin(floor(fh * ns) + 1.0, ns - 1.0);
+    if (!g.periodic[2] && cc[2] == 0) qh = fmax(qh, 0.0);
+    if (!g.periodic[2] && cc[2] == g.nc[2] - 1) ql = fmin(ql, ns - 1.0);
+    if (ql > qh) return make_int2(cr.x, cr.x);
+    if (ql == 0.0 && qh == ns - 1.0) return cr;
+    const uint32_t base = keys[cr.x] & ~((1u << g.zbits) - 1u);
+    const uint32_t klo = base | (uint32_t)ql, khi = base | (uint32_t)qh;
+    // first key >= klo and first key > khi, side by side
+    int a = cr.x, e = cr.y, p = cr.x, q = cr.y;
+    while (a < e || p < q) {
+        const int m = (a + e) >> 1, r = (p + q) >> 1;
+        const uint32_t km = keys[min(m, cr.y - 1)], kr = keys[min(r, cr.y - 1)];
+        if (a < e) {
+            if (km < klo) a = m + 1; else e = m;
+        }
+        if (p < q) {
+            if (kr <= khi) p = r + 1; else q = r;
+        }
+    }
+    return make_int2(a, p);
+}
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+// 4 x 4 transpose of registers against groups of 16 lanes: out[q] holds, in
+// lane group k, what in[k] held in lane group q.
+__device__ __forceinline__ void transpose4(uint32_t (&v)[4])
+{
+    auto s32 = [](uint32_t &x, uint32_t &y) {
+        const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+        x = r[0];
+        y = r[1];
+    };
+    auto s16 = [](uint32_t &x, uint32_t &y) {
+        const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+        x = r[0];
+        y = r[1];
+    };
+    s32(v[0], v[2]);
+    s32(v[1], v[3]);
+    s16(v[0], v[1]);
+    s16(v[2], v[3]);
+}
+__device__ __forceinline__ void transpose4(float a, float b, float c, float d, float (&out)[4])
+{
+    uint32_t v[4] = {__float_as_uint(a), __float_as_uint(b), __float_as_uint(c),
+                     __float_as_uint(d)};
+    transpose4(v);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) out[q] = __uint_as_float(v[q]);
+}
+
+// LDS of a tile. The union build's arrays are dead when the first relation
+// bits are written.
+template <int W>
+struct SearchLds {
+    typedef SearchShape<W> S;
+    static constexpr int E = S::kCells + 4;  // (whole groups of four)
+    static constexpr int kChunk = S::kBlocks * kWave;
+    union {
+        struct {
+            int ukey[S::kEntries + 4];   // first particle of each distinct non-empty cell
+            int2 urange[S::kEntries];    // the part of it within reach
+        };
+        uint32_t mask[2 * S::kBlocks][kWave];  // relation bits, [word of 32 candidates][lane]
+    };
+    int u0[E];                  // union position of each cell's first candidate
+    int base[E];                // first candidate minus union position
+    typename S::Cell cellof[kChunk];  // cell at each position of the chunk
+    int cnt[W][W > 1 ? kWave : 1];  // entries of each wave's share of the chunk
+    double red[6];              // extents x, y, z of the tile (low, high)
+    uint32_t dkeys[S::kMaxDist];
+    int wsum[W];
+};
+
+// A position relative to the tile's centre, as its nearest image on periodic
+// axes.
+__device__ __forceinline__ double rel(double v, double c, const Grid &g, int a)
+{
+    const double d = v - c;
+    return g.periodic[a] ? min_image_sel(d, g.len[a], g.half[a]) : d;
+}
+
+// What the relation of a tile's blocks needs of the tile's particles, in four
+// groups of 16: the matrix operands (-2x, -2y, -2z, 1), for varying h also
+// (-1, s_i^2, 0, 0), and the accumulators' start |x_i|^2 - s_i^2.
+struct TileOps {
+    float b[4], b3[4], c[4];
+    float eps;  // |d| below this: the FP64 relation decides
+};
+
+// Relation bits of 64 candidates (one per lane: x, y, z, |x|^2, s^2) with the
+// lane's particle: w[0] candidates 0..31, w[1] 32..63, the first at bit 31,
+// given the lanes hold the candidates in the order of cand_of_lane. Close:
+// the pairs too close to call instead. Returns the smallest |d| the lane saw.
+template <bool UniformH, bool Close>
+__device__ __forceinline__ float block_bits(float x, float y, float z, float n, float s,
+                                            const TileOps &T, uint32_t (&w)[2])
+{
+    // operands of the four 16-candidate groups, one component per lane group
+    float a[4], a3[4];
+    transpose4(x, y, z, n, a);
+    if (!UniformH) transpose4(s, 1.0f, 0.0f, 0.0f, a3);
+    uint32_t bit[4];
+    float m = 3e38f;
+    auto products = [&](int h, floatx4 (&d)[4]) {
+        const floatx4 c = {T.c[h], T.c[h], T.c[h], T.c[h]};
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            d[r] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[r], T.b[h], c, 0, 0, 0);
+        if (!UniformH) {
+            // r^2 - s_j^2 beside r^2 - s_i^2: the smaller one decides
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const floatx4 e =
+                    __builtin_amdgcn_mfma_f32_16x16x4f32(a3[r], T.b3[h], d[r], 0, 0, 0);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) d[r][q] = fminf(d[r][q], e[q]);
+            }
+        }
+    };
+    auto collect = [&](int h, const floatx4 (&d)[4]) {
+        uint32_t b = 0u;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float t = Close ? fabsf(d[r][q]) - T.eps : d[r][q];
+                b = __builtin_amdgcn_alignbit(b, __float_as_uint(t), 31);
+            }
+            if (!Close) {
+                m = fminf(fminf(m, fabsf(d[r][0])), fabsf(d[r][1]));
+                m = fminf(fminf(m, fabsf(d[r][2])), fabsf(d[r][3]));
+            }
+        }
+        bit[h] = b;
+    };
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        floatx4 d[4];
+        products(h, d);
+        collect(h, d);
+    }
+    // Accumulator q of a lane is row 4 (lane / 16) + q of a product, column
+    // lane % 16; after the transpose each lane has all four lane groups' bits
+    // of its own particle.
+    transpose4(bit);
+    w[0] = (bit[0] << 16) | (bit[1] & 0xffffu);
+    w[1] = (bit[2] << 16) | (bit[3] & 0xffffu);
+    return m;
+}
+
+// Candidate (of a block's 64) that a lane holds as a matrix row, so that the
+// bits of block_bits come out in candidate order: row 4 g + q of group r is
+// candidate 16 g + 4 r + q.
+__device__ __forceinline__ int cand_of_lane(int lane)
+{
+    return ((lane & 12) << 2) | ((lane & 48) >> 2) | (lane & 3);
+}
+
+// The FP64 relation of particle `me` with one record, minimum image on
+// periodic axes.
+__device__ __forceinline__ bool related_exact(const SearchRec &me, const SearchRec &o,
+                                              const Grid &g)
+{
+    const double no_shift[3] = {0.0, 0.0, 0.0};
+    return related<WRAP_PAIR, false>(me, o, g, no_shift);
+}
+
+// Barrier of the tile's waves.
+template <int W>
+__device__ __forceinline__ void tile_sync()
+{
+    if constexpr (W == 1) wave_sync(); else __syncthreads();
+}
+
+// One tile of 64 particles by the whole block of W waves. Multi: the
+// particles belong to one run of an ensemble (slot in the high key bits), and
+// the tile uses that run's grid and cell range.
+template <bool Multi, int W>
 __device__ __forceinline__ void search_tile(
     int64_t tile, int64_t n, int64_t ld, const SearchRec *__restrict__ srec,
     const uint32_t *__restrict__ keys, const int32_t *__restrict__ cstart,
     const int32_t *__restrict__ cend, const Grid &g0, int max_nb, int32_t *__restrict__ count,
-    int32_t *__restrict__ idx, uint32_t *__restrict__ mask_scratch,
-    const uint32_t *__restrict__ hflag, uint32_t *status0, const BatchDev &b,
-    SearchLds<kEntries> &L,
-    int32_t *__restrict__ fb_tiles, uint32_t *fb_count,
+    int32_t *__restrict__ idx, const uint32_t *__restrict__ hflag, uint32_t *status0,
+    const BatchDev &b, SearchLds<W> &L, int32_t *__restrict__ fb_tiles, uint32_t *fb_count,
     const unsigned long long *__restrict__ s2max)
 {
-    const int lane = threadIdx.x & (kWave - 1);
+    typedef SearchShape<W> Shape;
+    constexpr int kThreadsT = W * kWave;
+    constexpr int kQ = Shape::kEntries / kThreadsT;  // stencil entries per thread, at most
+    constexpr int kChunk = SearchLds<W>::kChunk;
+    static_assert(Shape::kMaxDist * kStencil <= Shape::kEntries, "entries");
+    const int tid = threadIdx.x;
+    const int lane = tid & (kWave - 1);
+    const int w = W == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid / kWave);
     int64_t t0, tend;
     tile_span<Multi>(tile, n, b, t0, tend);
-    uint32_t *bm = mask_scratch + tile * (kMaxWords * kWave);
     const int64_t i = t0 + lane;
     const bool active = i < tend;
     const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
 
-    const uint32_t key = active ? keys[i] : 0xFFFFFFFFu;
-    const SearchRec me = active ? srec[i] : SearchRec{0.0, 0.0, 0.0, 0.0};
-    // run of the tile (lane 0 is always active) and whether all lanes share it
-    int my_slot = 0, slot0 = 0;
-    bool mixed = false;
-    if constexpr (Multi) {
-        my_slot = active ? (int)(key >> kEnsSlotShift) : 0;
-        slot0 = __builtin_amdgcn_readfirstlane(my_slot);
-        mixed = __ballot(active && my_slot != slot0) != 0ull;
-    }
+    // Every wave holds the tile's 64 particles, one per lane.
+    const uint32_t key = keys[active ? i : t0];
+    const SearchRec me = srec[active ? i : t0];  // (idle lanes: the first particle's)
+    int slot0 = 0;
+    if constexpr (Multi) slot0 = __builtin_amdgcn_readfirstlane((int)(key >> kEnsSlotShift));
     // the run's grid, read once into wave-uniform registers
     Grid gm;
     if constexpr (Multi) {
@@ -482,157 +469,171 @@ __device__ __forceinline__ void search_tile(
     const bool first = active && (lane == 0 || ckey != prev);
     const uint64_t fm = __ballot(first);
     const int ndist = __popcll(fm);
-    if (first) L.dkeys[__popcll(fm & lt)] = mkey;
+    if (ndist > Shape::kMaxDist) {
+        if (tid == 0) fb_tiles[atomicAdd(fb_count, 1u)] = (int32_t)tile;
+        return;  // (the whole block)
+    }
+    if (w == 0 && first) L.dkeys[__popcll(fm & lt)] = mkey;
 
-    // The image test can be skipped for the whole wave when, on every
-    // periodic axis, the union of the stencils spans less than half the box:
-    // then |d| < L/2 for every candidate. Per-cell images need >= 5 cells.
-    const int myc[3] = {(int)compact3(mkey), (int)compact3(mkey >> 1),
-                        (int)compact3(mkey >> 2)};
-    bool wrap = false, few_cells = false;
+    // Extents of the tile around its first particle (nearest images), the
+    // axes dealt to the waves; the centre is taken from them.
+    const double ref[3] = {uniform_f64(me.x), uniform_f64(me.y), uniform_f64(me.z)};
+    const double mc[3] = {me.x, me.y, me.z};
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        if (!g.periodic[a]) continue;
-        int mn = active ? myc[a] : INT_MAX, mx = active ? myc[a] : INT_MIN;
+        if (a % W != w) continue;
+        double lo = rel(mc[a], ref[a], g, a), hi = lo;
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) {
-            mn = min(mn, __shfl_xor(mn, o, kWave));
-            mx = max(mx, __shfl_xor(mx, o, kWave));
+            lo = fmin(lo, __shfl_xor(lo, o, kWave));
+            hi = fmax(hi, __shfl_xor(hi, o, kWave));
         }
-        // candidates lie in cells [mn - 1, mx + 1]: |d| < (mx - mn + 3) cells
-        if (mn < 1 || mx > g.nc[a] - 2 || 2 * (mx - mn + 3) >= g.nc[a]) wrap = true;
-        if (g.nc[a] < 5) few_cells = true;
+        if (lane == 0) {
+            L.red[2 * a] = lo;
+            L.red[2 * a + 1] = hi;
+        }
     }
+    double s2t = me.s2;
+    const bool uniform_h = Multi ? b.runs[slot0].uniform_h != 0 : hflag[0] == 0;
+    if (!uniform_h) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) s2t = fmax(s2t, __shfl_xor(s2t, o, kWave));
+    }
+    tile_sync<W>();
 
-    constexpr int E = kEntries;
-    constexpr int kC = E / kWave;  // entries per lane
-    const int nent = ndist * kStencil;
-    bool use_union = nent <= E && !mixed;
-    int nu = 0, total = 0;
-    wave_sync();
-    if (use_union) {
-        // stencil cells of every distinct cell; empty ones become sentinels
-        for (int e = lane; e < E; e += kWave) {
-            int2 v = make_int2(INT_MAX, e);
-            if (e < nent) {
-                const uint32_t k = L.dkeys[e / kStencil];
-                const int s = e % kStencil;
-                bool okx, oky, okz;
-                const int x = wrap_or_clip((int)compact3(k) + s % 3 - 1, g.nc[0], g.periodic[0], okx);
-                const int y = wrap_or_clip((int)compact3(k >> 1) + (s / 3) % 3 - 1, g.nc[1],
-                                           g.periodic[1], oky);
-                const int z = wrap_or_clip((int)compact3(k >> 2) + s / 9 - 1, g.nc[2],
-                                           g.periodic[2], okz);
-                if (okx && oky && okz) {
-                    const int64_t cell = cbase + ((int64_t)z * g.nc[1] + y) * g.nc[0] + x;
-                    const int a = cstart[cell], e2 = cend[cell];
-                    if (a < e2) v = make_int2(a, e);
-                }
+    // Centre and half extents; the periodic axes (bits of both) on which the
+    // image nearest to the centre does not do for every pair, a candidate's
+    // other image being within reach too; and whether whole cells can be placed
+    // by their nearest image (a cell to spare).
+    double ctr[3], ext[3];
+    int both = 0;
+    bool cull = g.zbits > 0, plain = true;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const double lo = uniform_f64(L.red[2 * a]), hi = uniform_f64(L.red[2 * a + 1]);
+        ctr[a] = ref[a] + 0.5 * (lo + hi);
+        ext[a] = 0.5 * (hi - lo) * (1.0 + 1e-9);
+        if (g.periodic[a]) {
+            const double far = ext[a] + g.reach * (1.0 + 1e-6);
+            if (!(far + 1.001 / g.inv_s[a] < g.half[a])) cull = false;
+            if (!(far < g.half[a])) {
+                both |= 1 << a;
+                ext[a] = g.half[a];
             }
-            L.ent[e] = v;
+            // no cell of the stencils across a boundary: raw differences
+            const double cw = 1.0 / g.inv_s[a];
+            plain = plain && ctr[a] - ext[a] > g.lo[a] + 1.001 * cw &&
+                    ctr[a] + ext[a] < g.hi[a] - 1.001 * cw &&
+                    ext[a] + 2.001 * cw < g.half[a];
         }
-        wave_sync();
-        // bitonic sort of the first sortN entries by first particle (the
-        // rest are sentinels, already in place): the sortN / 2
-        // compare-exchanges of a step are disjoint, up to kC / 2 per lane
-        const int sortN = nent <= 2 * kWave ? 2 * kWave : E;
-        for (int k = 2; k <= sortN; k <<= 1) {
-            for (int j = k >> 1; j > 0; j >>= 1) {
-#pragma unroll
-                for (int q = 0; q < kC / 2; ++q) {
-                    if (2 * kWave * q >= sortN) break;
-                    const int p = lane + q * kWave;
-                    const int lo_i = ((p & ~(j - 1)) << 1) | (p & (j - 1));
-                    const int hi_i = lo_i | j;
-                    const int2 ea = L.ent[lo_i], eb = L.ent[hi_i];
-                    const bool up = (lo_i & k) == 0;
-                    if ((ea.x > eb.x) == up) {
-                        L.ent[lo_i] = eb;
-                        L.ent[hi_i] = ea;
-                    }
-                }
-                wave_sync();
-            }
-        }
-        // drop sentinels and duplicates (a cell listed by several stencils);
-        // a kept entry's cell is recomputed from its entry index. Lane holds
-        // entries lane + q * 64.
-        int2 v[kC];
-        bool kp[kC];
-        uint64_t m[kC];
-        int off[kC + 1];
-        off[0] = 0;
-#pragma unroll
-        for (int q = 0; q < kC; ++q) {
-            const int e = lane + q * kWave;
-            v[q] = L.ent[e];
-            const int pv = e == 0 ? INT_MIN : L.ent[e - 1].x;
-            kp[q] = v[q].x != INT_MAX && v[q].x != pv;
-            m[q] = __ballot(kp[q]);
-            off[q + 1] = off[q] + __popcll(m[q]);
-        }
-        nu = off[kC];
-        auto keep = [&](const int2 ve, int pos) {
-            const uint32_t k = L.dkeys[ve.y / kStencil];
-            const int s = ve.y % kStencil;
-            bool ok;
-            const int x = wrap_or_clip((int)compact3(k) + s % 3 - 1, g.nc[0], g.periodic[0], ok);
-            const int y = wrap_or_clip((int)compact3(k >> 1) + (s / 3) % 3 - 1, g.nc[1],
-                                       g.periodic[1], ok);
-            const int z = wrap_or_clip((int)compact3(k >> 2) + s / 9 - 1, g.nc[2],
-                                       g.periodic[2], ok);
-            const int64_t cell = cbase + ((int64_t)z * g.nc[1] + y) * g.nc[0] + x;
-            L.cells[pos] = make_int2(ve.x, cend[cell]);
-            L.cxyz[pos] = (uint32_t)x | ((uint32_t)y << 10) | ((uint32_t)z << 20);
-        };
-#pragma unroll
-        for (int q = 0; q < kC; ++q)
-            if (kp[q]) keep(v[q], off[q] + __popcll(m[q] & lt));
-        wave_sync();
-        if constexpr (!Multi) {
-            if (!wrap && g.zbits > 0) {
-                // Each union cell only in its window for the tile (as for the
-                // dense unions of the second kernel): cells beyond reach in x
-                // or y are emptied, the others keep the z slices within reach
-                // of the tile's z extent. Windows stay inside their cells, so
-                // the cells stay ascending and hold the tile's own particles.
-                double tlo[3], thi[3];
-                double s2t = active ? me.s2 : 0.0;
-                const double mc[3] = {me.x, me.y, me.z};
-#pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    tlo[a] = active ? mc[a] : INFINITY;
-                    thi[a] = active ? mc[a] : -INFINITY;
-                }
-#pragma unroll
-                for (int o = 32; o > 0; o >>= 1) {
-#pragma unroll
-                    for (int a = 0; a < 3; ++a) {
-                        tlo[a] = fmin(tlo[a], __shfl_xor(tlo[a], o, kWave));
-                        thi[a] = fmax(thi[a], __shfl_xor(thi[a], o, kWave));
-                    }
-                    s2t = fmax(s2t, __shfl_xor(s2t, o, kWave));
-                }
-                // the reduced values are the same in every lane: keep them in
-                // scalar registers (vector registers bound the occupancy)
-#pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    tlo[a] = uniform_f64(tlo[a]);
-                    thi[a] = uniform_f64(thi[a]);
-                }
-                s2t = uniform_f64(s2t);
+    }
+    both = __builtin_amdgcn_readfirstlane(both);
+    plain = __builtin_amdgcn_readfirstlane((int)plain) != 0;
+
+    // The union: stencil entries of the distinct cells, without those that an
+    // earlier distinct cell's stencil holds too (and without the second copy of
+    // a cell on a periodic axis of two cells), cut to what is within reach.
+    int nu = 0;
 #pragma unroll 1
-                for (int c = lane; c < nu; c += kWave)
-                    L.cells[c] = z_window(L.cells[c], L.cxyz[c], g, tlo, thi, s2t, s2max, keys);
-                wave_sync();
+    for (int q = 0; q < kQ; ++q) {
+        if (q * kThreadsT >= ndist * kStencil) break;
+        const int e = tid + q * kThreadsT;
+        const int c = e / kStencil, st = e - c * kStencil;
+        int ekey = INT_MAX;
+        int2 er = make_int2(0, 0);
+        if (c < ndist) {
+            const uint32_t k = L.dkeys[c];
+            const int oz = st / 9, oy = (st - oz * 9) / 3, ox = st - oz * 9 - oy * 3;
+            const int off[3] = {ox - 1, oy - 1, oz - 1};
+            const int own[3] = {(int)compact3(k), (int)compact3(k >> 1), (int)compact3(k >> 2)};
+            int cc[3];
+            bool ok = true;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                bool oka;
+                cc[a] = wrap_or_clip(own[a] + off[a], g.nc[a], g.periodic[a], oka);
+                ok = ok && oka;
+                if (g.periodic[a] &&
+                    ((g.nc[a] == 2 && off[a] > 0) || (g.nc[a] == 1 && off[a] != 0)))
+                    ok = false;
+            }
+            for (int p = 0; p < c; ++p) {
+                const uint32_t kp = L.dkeys[p];
+                const int po[3] = {(int)compact3(kp), (int)compact3(kp >> 1),
+                                   (int)compact3(kp >> 2)};
+                bool near = true;
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    const int d = abs(cc[a] - po[a]);
+                    near = near && (d <= 1 || (g.periodic[a] && d >= g.nc[a] - 1));
+                }
+                ok = ok && !near;
+            }
+            if (ok) {
+                const int64_t cell =
+                    cbase + ((int64_t)cc[2] * g.nc[1] + cc[1]) * g.nc[0] + cc[0];
+                er = make_int2(cstart[cell], cend[cell]);
+                if (er.x < er.y) {
+                    ekey = er.x;
+                    if (cull) {
+                        const double s2c =
+                            Multi ? g.reach * g.reach
+                                  : (uniform_h ? s2t
+                                               : __longlong_as_double((long long)s2max[cell]));
+                        er = tile_window(er, cc, g, ctr, ext, sqrt(fmax(s2t, s2c)), keys);
+                        if (er.x >= er.y) ekey = INT_MAX;
+                    }
+                }
             }
         }
-        // u0[c]: exclusive prefix of the cell lengths; lane holds cells
-        // c = lane + q * 64
+        // append the kept entries
+        const uint64_t m = __ballot(ekey != INT_MAX);
+        int at = nu;
+        if constexpr (W == 1) {
+            nu += __popcll(m);
+        } else {
+            if (lane == 0) L.wsum[w] = __popcll(m);
+            tile_sync<W>();
 #pragma unroll
-        for (int q = 0; q < kC; ++q) {
-            const int c = lane + q * kWave;
-            const int l = c < nu ? L.cells[c].y - L.cells[c].x : 0;
+            for (int v = 0; v < W; ++v) {
+                const int cv = L.wsum[v];
+                if (v < w) at += cv;
+                nu += cv;
+            }
+            tile_sync<W>();
+        }
+        if (ekey != INT_MAX) {
+            at += __popcll(m & lt);
+            L.ukey[at] = ekey;
+            L.urange[at] = er;
+        }
+    }
+    nu = __builtin_amdgcn_readfirstlane(nu);
+    if (nu > Shape::kCells) {
+        if (tid == 0) fb_tiles[atomicAdd(fb_count, 1u)] = (int32_t)tile;
+        return;  // (the whole block)
+    }
+    if (tid < 4) L.ukey[nu + tid] = INT_MAX;  // (read in groups of four)
+    tile_sync<W>();
+    // place in the order of first particles: the number of smaller keys
+    for (int e = tid; e < nu; e += kThreadsT) {
+        const int k = L.ukey[e];
+        const int2 r = L.urange[e];
+        int rank = 0;
+        for (int q = 0; q < nu; q += 4) {
+            const int4 o = *reinterpret_cast<const int4 *>(&L.ukey[q]);
+            rank += (o.x < k) + (o.y < k) + (o.z < k) + (o.w < k);
+        }
+        L.base[rank] = r.x;          // (first candidate; the position is taken off below)
+        L.u0[rank] = r.y - r.x;      // (length)
+    }
+    tile_sync<W>();
+    // union positions: exclusive prefix of the lengths
+    int total = 0;
+    if (w == 0) {
+        for (int c0 = 0; c0 < nu; c0 += kWave) {
+            const int c = c0 + lane;
+            const int l = c < nu ? L.u0[c] : 0;
             int sc = l;
 #pragma unroll
             for (int o = 1; o < kWave; o <<= 1) {
@@ -641,146 +642,286 @@ __device__ __forceinline__ void search_tile(
             }
             if (c < nu) {
                 L.u0[c] = total + sc - l;
-                L.base[c] = L.cells[c].x - (total + sc - l);
+                L.base[c] -= total + sc - l;
             }
             total += __shfl(sc, kWave - 1, kWave);
         }
-        wave_sync();
-        if (total > kMaxCandidates) {
-            if (nu <= kDenseCells) {
-                // Too large for the masks: the second kernel walks the same
-                // union, read from this tile's scratch region (cells, then
-                // coordinates, then the count), with each lane appending
-                // directly.
-                int2 *gc = reinterpret_cast<int2 *>(bm);
-                uint32_t *gx = bm + 2 * kDenseCells;
-                for (int c = lane; c < nu; c += kWave) {
-                    gc[c] = L.cells[c];
-                    gx[c] = L.cxyz[c];
-                }
-                if (lane == 0) {
-                    bm[3 * kDenseCells] = (uint32_t)nu;
-                    fb_tiles[atomicAdd(fb_count, 1u)] = (int32_t)(0x80000000u | (uint32_t)tile);
-                }
-                return;
-            }
-            use_union = false;  // many dense cells: the per-lane path
+        if (W > 1 && lane == 0) L.wsum[0] = total;
+    }
+    tile_sync<W>();
+    if (W > 1) total = L.wsum[0];
+    total = __builtin_amdgcn_readfirstlane(total);
+    // union position of the lane's own particle (its cell's part holds it)
+    int u_self = -1;
+    {
+        int lo = 0, hi = nu - 1;
+        while (lo < hi) {  // last cell with first candidate <= i
+            const int mid = (lo + hi + 1) >> 1;
+            if (L.base[mid] + L.u0[mid] <= (int)i) lo = mid; else hi = mid - 1;
         }
+        if (active) u_self = (int)i - L.base[lo];
     }
 
-    if (use_union) {
-        const bool uniform_h = Multi ? b.runs[slot0].uniform_h != 0 : hflag[0] == 0;
-        const int mode = !wrap ? WRAP_NONE : (few_cells ? WRAP_PAIR : WRAP_CELL);
+    // The tile's matrix operands.
+    const double scale = 1.0 / g.reach;
+    // coordinates from the centre; axes of `far`: on the other side of the box
+    auto scaled = [&](const SearchRec &o, int far, float (&v)[3]) {
+        const double p[3] = {o.x, o.y, o.z};
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            double d = p[a] - ctr[a];
+            if (!plain) {
+                d = rel(p[a], ctr[a], g, a);
+                if ((far >> a) & 1) d -= __builtin_copysign(g.len[a], d);
+            }
+            v[a] = (float)(d * scale);
+        }
+    };
+    // coordinates whose squares FP32 does not hold, or an s above the reach
+    // the grid was built for: FP64 for every pair
+    auto odd = [](float nn, float s) { return !(nn < 1.2e24f && s <= 1.0001f); };
+    TileOps T;
+    bool exact = false;
+    {
+        float v[3];
+        scaled(me, 0, v);
+        const double s2 = me.s2 * (scale * scale);
+        const double nd = ((double)v[0] * v[0] + (double)v[1] * v[1]) + (double)v[2] * v[2];
+        const float cc = (float)(nd - s2), ss = (float)s2, nn = (float)nd;
+        transpose4(-2.0f * v[0], -2.0f * v[1], -2.0f * v[2], 1.0f, T.b);
+        transpose4(-1.0f, ss, 0.0f, 0.0f, T.b3);
+        transpose4(cc, cc, cc, cc, T.c);
+        float most = nn;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) most = fmaxf(most, __shfl_xor(most, o, kWave));
+        const float t1 = 2.0f * sqrtf(most) * 1.00001f + 1.0f;
+        T.eps = 5.9604645e-8f * ((6.0f * t1 + 2.4f) * t1 + 9.6f);
+        if (__ballot(odd(nn, ss)) != 0ull || !(T.eps < 1e30f)) exact = true;
+    }
+    exact = __ballot(exact) != 0ull;
+    const bool full = tend - t0 == kWave;
+
+    int carry = 0;  // the lane's entries in earlier chunks
+    const int cand = cand_of_lane(lane);
+    for (int c0 = 0; c0 < total; c0 += kChunk) {
+        const int len = min(total - c0, kChunk);
+        // ---- cell of each position of the chunk: a lane per cell; long cells
+        // by the whole wave
+        for (int cb = w * kWave; cb < nu; cb += W * kWave) {
+            const int c = cb + lane;
+            int a = 0, e = 0;
+            if (c < nu) {
+                a = max(L.u0[c] - c0, 0);
+                e = min((c + 1 < nu ? L.u0[c + 1] : total) - c0, len);
+            }
+            const uint64_t big = __ballot(e - a > kWave);
+            if (e - a <= kWave)
+                for (int u = a; u < e; ++u) L.cellof[u] = (typename Shape::Cell)c;
+            for (uint64_t m = big; m != 0ull; m &= m - 1) {
+                const int q = __builtin_ctzll(m);
+                const int qa = __builtin_amdgcn_readlane(a, q), qe = __builtin_amdgcn_readlane(e, q);
+                for (int u = qa + lane; u < qe; u += kWave)
+                    L.cellof[u] = (typename Shape::Cell)(cb + q);
+            }
+        }
+        tile_sync<W>();
+        auto candidate_at = [&](int u) -> int { return L.base[L.cellof[u]] + c0 + u; };
+        // ---- relation bits of the wave's blocks [b0, b1)
+        const int nblk = (len + kWave - 1) / kWave;
+        const int per = W == 1 ? nblk : (nblk + W - 1) / W;
+        const int b0 = min(w * per, nblk), b1 = min(b0 + per, nblk);
         int cnt = 0;
-        uint64_t occ0 = 0;  // bit w: mask word w has at least one bit for this lane
-        uint32_t occ1 = 0;  // the same for words 64..
-#define SPH_STREAM(M, U) \
-    stream_union<M, U>(me, myc, srec, L, nu, g, bm, lane, cnt, occ0, occ1)
-        if (mode == WRAP_NONE) {
-            if (uniform_h) SPH_STREAM(WRAP_NONE, true); else SPH_STREAM(WRAP_NONE, false);
-        } else if (mode == WRAP_CELL) {
-            if (uniform_h) SPH_STREAM(WRAP_CELL, true); else SPH_STREAM(WRAP_CELL, false);
-        } else {
-            if (uniform_h) SPH_STREAM(WRAP_PAIR, true); else SPH_STREAM(WRAP_PAIR, false);
-        }
-#undef SPH_STREAM
-        // the lane's own particle is in the union: drop its bit
-        if (active) {
-            int lo = 0, hi = nu - 1;
-            while (lo < hi) {  // last cell with start <= i
-                const int mid = (lo + hi + 1) >> 1;
-                if (L.cells[mid].x <= i) lo = mid; else hi = mid - 1;
-            }
-            const int u_self = L.u0[lo] + (int)(i - L.cells[lo].x);
-            const int ws = u_self >> 5;
-            const uint32_t bit = 0x80000000u >> (u_self & 31);
-            const uint32_t word = bm[ws * kWave + lane];
-            if (word & bit) {
-                bm[ws * kWave + lane] = word & ~bit;
-                --cnt;
-                if ((word & ~bit) == 0) {
-                    if (ws < 64) occ0 &= ~(1ull << ws);
-                    else occ1 &= ~(1u << (ws - 64));
-                }
-            }
-        } else {
-            cnt = 0;
-        }
-        wave_sync();
-        // union position -> union cell, for the expansion (overlays the
-        // union-build arrays, which are not read after this point)
-        for (int c = 0; c < nu; ++c) {
-            const int a = L.u0[c], e = c + 1 < nu ? L.u0[c + 1] : total;
-            for (int uu = a + lane; uu < e; uu += kWave) L.cellof[uu] = (uint8_t)c;
-        }
-        wave_sync();
-        int maxc = cnt;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) maxc = max(maxc, __shfl_xor(maxc, o, kWave));
-        const int rows = min(maxc, max_nb);
-        // Expand row by row: row k of every lane is written by one store. Each
-        // lane walks its non-empty words (occ) with the next word already in
-        // flight. Rows go out in chunks: the chunk's entries are formed in
-        // registers first, then stored together, so that a wait for a mask
-        // word (stores share its counter) waits for the previous chunk's
-        // stores once per chunk, not once per row.
-        auto pop_word = [&]() -> int {
-            if (occ0 != 0) {
-                const int w = __builtin_ctzll(occ0);
-                occ0 &= occ0 - 1;
-                return w;
-            }
-            if (occ1 == 0) return -1;
-            const int w = 64 + __builtin_ctz(occ1);
-            occ1 &= occ1 - 1;
-            return w;
+        uint32_t occ = 0u;  // words 2 b0 + k that hold a neighbour
+        auto load = [&](int blk) -> SearchRec {
+            return srec[candidate_at(min(blk * kWave + cand, len - 1))];
         };
-        int w_cur = pop_word();
-        uint32_t cur = w_cur >= 0 ? bm[w_cur * kWave + lane] : 0u;
-        int w_nxt = pop_word();
-        uint32_t nxt = w_nxt >= 0 ? bm[w_nxt * kWave + lane] : 0u;
-        constexpr int kChunk = 16;
-        const int mine = min(cnt, max_nb);
-        for (int k0 = 0; k0 < rows; k0 += kChunk) {
-            int val[kChunk];
+        SearchRec nx = me;
+        if (b0 < b1) nx = load(b0);
+        for (int blk = b0; blk < b1; ++blk) {
+            const SearchRec o = nx;
+            if (blk + 1 < b1) nx = load(blk + 1);
+            const int ub = blk * kWave;
+            float v[3];
+            scaled(o, 0, v);
+            auto norm = [&]() {
+                return __builtin_fmaf(v[2], v[2], __builtin_fmaf(v[1], v[1], v[0] * v[0]));
+            };
+            const float sj = uniform_h ? 0.0f : (float)(o.s2 * (scale * scale));
+            uint32_t bits[2] = {0u, 0u};
+            // both images of the candidates, on the axes where some of them
+            // may be within reach on the other side
+            int other = 0;
+            if (both) {
+                const double p[3] = {o.x, o.y, o.z};
 #pragma unroll
-            for (int r = 0; r < kChunk; ++r) {
-                val[r] = 0;
-                if (k0 + r < mine) {
-                    if (cur == 0) {
-                        cur = nxt;
-                        w_cur = w_nxt;
-                        w_nxt = pop_word();
-                        nxt = w_nxt >= 0 ? bm[w_nxt * kWave + lane] : 0u;
-                    }
-                    const int t = __builtin_clz(cur);
-                    val[r] = w_cur * 32 + t;
-                    cur &= ~(0x80000000u >> t);
+                for (int a = 0; a < 3; ++a) {
+                    const double lim = g.half[a] - g.reach * (1.0 + 1e-6);
+                    if (((both >> a) & 1) &&
+                        __ballot(!(fabs(rel(p[a], ctr[a], g, a)) < lim)) != 0ull)
+                        other |= 1 << a;
                 }
             }
+            auto images = [&](auto &&each) {
+                for (int far = other;; far = (far - 1) & other) {
+                    if (other) scaled(o, far, v);
+                    each(norm());
+                    if (far == 0) break;
+                }
+            };
+            bool close = false;
+            if (!exact && __ballot(odd(norm(), sj)) == 0ull) {
+                float m = 3e38f;
+                images([&](float nn) {
+                    uint32_t t[2];
+                    m = fminf(m, uniform_h
+                                     ? block_bits<true, false>(v[0], v[1], v[2], nn, sj, T, t)
+                                     : block_bits<false, false>(v[0], v[1], v[2], nn, sj, T, t));
+                    bits[0] |= t[0];
+                    bits[1] |= t[1];
+                });
+                close = __ballot(m < T.eps) != 0ull;
+            } else {
+                const SearchRec mine = srec[active ? i : t0];
+                uint32_t acc = 0u;
+#pragma unroll 1
+                for (int c = 0; c < kWave; ++c) {
+                    const int j = __builtin_amdgcn_readfirstlane(candidate_at(min(ub + c, len - 1)));
+                    acc = (acc << 1) | (related_exact(mine, srec[j], g) ? 1u : 0u);
+                    if (c == 31) bits[0] = acc;
+                }
+                bits[1] = acc;
+            }
+            // positions past the end, idle lanes
+            const int nv = len - ub;
+            auto cut = [&](uint32_t (&q)[2]) {
+                if (nv < kWave) {
+                    q[0] &= nv >= 32 ? 0xffffffffu : ~(0xffffffffu >> nv);
+                    q[1] &= nv <= 32 ? 0u : ~(0xffffffffu >> (nv - 32));
+                }
+                if (!full) {
+                    q[0] = active ? q[0] : 0u;
+                    q[1] = active ? q[1] : 0u;
+                }
+            };
+            cut(bits);
+            if (close) {
+                // pairs too close to call: the FP64 relation, one pair of
+                // every lane at a time
+                uint32_t amb[2] = {0u, 0u};
+                images([&](float nn) {
+                    uint32_t t[2];
+                    if (uniform_h) block_bits<true, true>(v[0], v[1], v[2], nn, sj, T, t);
+                    else block_bits<false, true>(v[0], v[1], v[2], nn, sj, T, t);
+                    amb[0] |= t[0];
+                    amb[1] |= t[1];
+                });
+                cut(amb);
+                const SearchRec mine = srec[active ? i : t0];
 #pragma unroll
-            for (int r = 0; r < kChunk; ++r)
-                if (k0 + r < mine) val[r] += L.base[L.cellof[val[r]]];
-            // Rows of 64 consecutive entries, whole lines: stored
-            // non-temporally, the list (read back only by the next calls)
-            // does not evict the union's records from L2. The scattered
-            // appends of the per-lane walks stay ordinary stores (partial
-            // lines written non-temporally double their time).
+                for (int r = 0; r < 2; ++r) {
+                    uint32_t a = amb[r];
+                    while (__ballot(a != 0u) != 0ull) {
+                        if (a != 0u) {
+                            const int t = __builtin_clz(a);
+                            const uint32_t bt = 0x80000000u >> t;
+                            a &= ~bt;
+                            const SearchRec oj = srec[candidate_at(ub + 32 * r + t)];
+                            bits[r] = related_exact(mine, oj, g) ? bits[r] | bt : bits[r] & ~bt;
+                        }
+                    }
+                }
+            }
+            L.mask[2 * blk][lane] = bits[0];
+            L.mask[2 * blk + 1][lane] = bits[1];
+            cnt += __popc(bits[0]) + __popc(bits[1]);
+            occ |= ((bits[0] ? 1u : 0u) | (bits[1] ? 2u : 0u)) << (2 * (blk - b0));
+        }
+        // the lane's own particle
+        const int us = u_self - c0;
+        if (us >= b0 * kWave && us < min(b1 * kWave, len)) {
+            const uint32_t word = L.mask[us >> 5][lane], bt = 0x80000000u >> (us & 31);
+            if (word & bt) {
+                L.mask[us >> 5][lane] = word & ~bt;
+                --cnt;
+                if (word == bt) occ &= ~(1u << ((us >> 5) - 2 * b0));
+            }
+        }
+        // ---- rows of the wave's entries: after those of the waves before it
+        int row0 = carry, tot = cnt;
+        if constexpr (W > 1) {
+            L.cnt[w][lane] = cnt;
+            tile_sync<W>();
+            tot = 0;
 #pragma unroll
-            for (int r = 0; r < kChunk; ++r)
-                if (k0 + r < mine)
-                    __builtin_nontemporal_store(val[r], &idx[(int64_t)(k0 + r) * ld + i]);
+            for (int v = 0; v < W; ++v) {
+                const int cv = L.cnt[v][lane];
+                if (v < w) row0 += cv;
+                tot += cv;
+            }
+        } else {
+            wave_sync();
         }
-        if (active) {
-            count[i] = cnt;
-            if (cnt > max_nb) atomicOr(Multi ? &b.status[slot0] : status0, ST_CAPACITY);
+        const int mine = max(0, min(cnt, max_nb - row0));
+        int rows = mine;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) rows = max(rows, __shfl_xor(rows, o, kWave));
+        rows = __builtin_amdgcn_readfirstlane(rows);
+        // Each lane walks its non-empty words with the next one already in
+        // flight; the entries of 16 rows are formed, looked up and stored
+        // together. One wave and one chunk: row k of every lane at once, whole
+        // lines, stored non-temporally, so that the list (read back only by the
+        // next calls) does not evict the records from L2. Rows that start at
+        // different places are ordinary stores (partial lines written
+        // non-temporally double their time).
+        const bool whole = W == 1 && c0 == 0;
+        uint32_t cur = 0u, nxt = 0u;
+        int ucur = 0, unxt = 0;
+        auto pop = [&]() {
+            // (no word left: any in bounds, its entries are past the lane's)
+            const int k = min(2 * b0 + __builtin_ctz(occ | 0x80000000u), 2 * Shape::kBlocks - 1);
+            occ &= occ - 1u;
+            unxt = 32 * k;
+            nxt = L.mask[k][lane];
+        };
+        pop();
+        constexpr int kRows = 16;
+        for (int k0 = 0; k0 < rows; k0 += kRows) {
+            int val[kRows];
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) {
+                if (cur == 0u) {
+                    cur = nxt;
+                    ucur = unxt;
+                    pop();
+                }
+                const int t = __builtin_clz(cur | 1u);
+                val[r] = min(ucur + t, len - 1);
+                cur &= ~(0x80000000u >> t);
+            }
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) val[r] = candidate_at(val[r]);
+            if (whole) {
+                int32_t *at = idx + (int64_t)k0 * ld + t0;
+#pragma unroll
+                for (int r = 0; r < kRows; ++r)
+                    if (k0 + r < mine)
+                        __builtin_nontemporal_store(val[r], &at[(int64_t)r * ld + lane]);
+            } else {
+                int32_t *at = idx + (int64_t)(row0 + k0) * ld + i;
+#pragma unroll
+                for (int r = 0; r < kRows; ++r) {
+                    if (k0 + r < mine) *at = val[r];
+                    at += ld;
+                }
+            }
         }
-        return;
+        carry += tot;
+        if (c0 + kChunk < total) tile_sync<W>();  // the chunk's arrays are written again
     }
-
-    // The tile takes the per-lane path, in a kernel of its own (its
-    // registers would otherwise lower the occupancy of this one).
-    if (lane == 0) fb_tiles[atomicAdd(fb_count, 1u)] = (int32_t)tile;
+    if (w == 0 && active) {
+        count[i] = carry;
+        if (carry > max_nb) atomicOr(Multi ? &b.status[slot0] : status0, ST_CAPACITY);
+    }
 }
 
 // Per-lane path, one wave per listed tile: each lane visits its own
@@ -794,16 +935,13 @@ fallback_kernel(int64_t n, int64_t ld, const SearchRec *__restrict__ srec,
                 const uint32_t *__restrict__ keys, const int32_t *__restrict__ cstart,
                 const int32_t *__restrict__ cend, Grid g0, int max_nb,
                 int32_t *__restrict__ count, int32_t *__restrict__ idx, uint32_t *status0,
-                BatchDev b, const int32_t *__restrict__ fb_tiles, const uint32_t *fb_count,
-                const uint32_t *__restrict__ mask_scratch, const uint32_t *__restrict__ hflag,
-                const unsigned long long *__restrict__ s2max)
+                BatchDev b, const int32_t *__restrict__ fb_tiles, const uint32_t *fb_count)
 {
     const int lane = threadIdx.x;
     if (Multi) n = b.hdr->n_out;
     const uint32_t nfb = *fb_count;
     for (uint32_t q = blockIdx.x; q < nfb; q += gridDim.x) {
-    const uint32_t entry = (uint32_t)fb_tiles[q];
-    const int64_t tile = (int64_t)(entry & 0x7FFFFFFFu);
+    const int64_t tile = (int64_t)fb_tiles[q];
     int64_t t0, tend;
     tile_span<Multi>(tile, n, b, t0, tend);
     const int64_t i = t0 + lane;
@@ -814,75 +952,6 @@ fallback_kernel(int64_t n, int64_t ld, const SearchRec *__restrict__ srec,
     const uint32_t mkey = Multi ? ((key >> kSliceBits) & kEnsMortonMask) : (key >> g0.zbits);
     const int myc[3] = {(int)compact3(mkey), (int)compact3(mkey >> 1),
                         (int)compact3(mkey >> 2)};
-    if (entry & 0x80000000u) {
-        // a union too large for the masks (its particles are of one run)
-        const uint32_t *bm = mask_scratch + tile * (kMaxWords * kWave);
-        const int nu = (int)__builtin_amdgcn_readfirstlane(bm[3 * kDenseCells]);
-        const int slot0 = __builtin_amdgcn_readfirstlane(my_slot);
-        const Grid &g = Multi ? b.runs[slot0].grid : g0;
-        bool wrap = false, few_cells = false;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            if (!g.periodic[a]) continue;
-            int mn = active ? myc[a] : INT_MAX, mx = active ? myc[a] : INT_MIN;
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) {
-                mn = min(mn, __shfl_xor(mn, o, kWave));
-                mx = max(mx, __shfl_xor(mx, o, kWave));
-            }
-            if (mn < 1 || mx > g.nc[a] - 2 || 2 * (mx - mn + 3) >= g.nc[a]) wrap = true;
-            if (g.nc[a] < 5) few_cells = true;
-        }
-        const bool uniform_h = Multi ? b.runs[slot0].uniform_h != 0 : hflag[0] == 0;
-        const int mode = !wrap ? WRAP_NONE : (few_cells ? WRAP_PAIR : WRAP_CELL);
-        const int2 *gc = reinterpret_cast<const int2 *>(bm);
-        const uint32_t *gx = bm + 2 * kDenseCells;
-        int2 r0 = make_int2(0, 0), r1 = make_int2(0, 0);
-        uint32_t p0 = 0u, p1 = 0u;
-        if (lane < nu) {
-            r0 = gc[lane];
-            p0 = gx[lane];
-        }
-        if (lane + kWave < nu) {
-            r1 = gc[lane + kWave];
-            p1 = gx[lane + kWave];
-        }
-        if (!Multi && mode == WRAP_NONE && g.zbits > 0) {
-            // walk only each cell's window (single run: the cell table
-            // carries the cells' largest (2h)^2)
-            const double mc[3] = {me.x, me.y, me.z};
-            double tlo[3], thi[3];
-            double s2t = active ? me.s2 : 0.0;
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                tlo[a] = active ? mc[a] : INFINITY;
-                thi[a] = active ? mc[a] : -INFINITY;
-            }
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) {
-#pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    tlo[a] = fmin(tlo[a], __shfl_xor(tlo[a], o, kWave));
-                    thi[a] = fmax(thi[a], __shfl_xor(thi[a], o, kWave));
-                }
-                s2t = fmax(s2t, __shfl_xor(s2t, o, kWave));
-            }
-            if (lane < nu) r0 = z_window(r0, p0, g, tlo, thi, s2t, s2max, keys);
-            if (lane + kWave < nu) r1 = z_window(r1, p1, g, tlo, thi, s2t, s2max, keys);
-        }
-        int cnt;
-#define SPH_DIRECT(M, U) \
-    stream_direct<M, U>(me, myc, srec, r0, r1, p0, p1, nu, g, active, i, ld, max_nb, idx)
-        if (mode == WRAP_NONE) cnt = uniform_h ? SPH_DIRECT(WRAP_NONE, true) : SPH_DIRECT(WRAP_NONE, false);
-        else if (mode == WRAP_CELL) cnt = uniform_h ? SPH_DIRECT(WRAP_CELL, true) : SPH_DIRECT(WRAP_CELL, false);
-        else cnt = uniform_h ? SPH_DIRECT(WRAP_PAIR, true) : SPH_DIRECT(WRAP_PAIR, false);
-#undef SPH_DIRECT
-        if (active) {
-            count[i] = cnt;
-            if (cnt > max_nb) atomicOr(Multi ? &b.status[slot0] : status0, ST_CAPACITY);
-        }
-        continue;
-    }
     if (!active) continue;
     const Grid &gl = Multi ? b.runs[my_slot].grid : g0;
     const int64_t cbl = Multi ? (int64_t)b.runs[my_slot].cell_base : 0;
@@ -948,36 +1017,34 @@ fallback_kernel(int64_t n, int64_t ld, const SearchRec *__restrict__ srec,
 
 __global__ void clear_count_kernel(uint32_t *c) { *c = 0u; }
 
-
-// At most 96 SGPRs (a few spill to VGPR lanes): 8 waves per SIMD instead of
-// the 7 that the compiler's own choice allows; the stream is latency-bound.
-template <bool Multi>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_num_sgpr(96)))
+// What bounds it (1M patch, one wave per tile): vector issue, 11,400
+// instructions a tile (3,800 for the 21.8 blocks of candidates, 3,600 for the
+// 124 list rows), 60% of the chip's rate at four waves per SIMD; the matrix
+// pipe is busy 17% of the time. Before, each candidate was tested in FP64 by
+// every lane (8 instructions a pair row) and the bits went through HBM: the 1M
+// patch took 715 us, now 480; the 1M Evrard sphere 2,700 us, now 1,990; 104k
+// particles 229 us, now 103; 8,000 particles 188 us, now 41 (one wave did a
+// tile however few there were).
+template <bool Multi, int W>
+__global__ void __launch_bounds__(W * kWave, 4)
 find_neighbors_kernel(int64_t n, int64_t ld, const SearchRec *__restrict__ srec,
                       const uint32_t *__restrict__ keys, const int32_t *__restrict__ cstart,
                       const int32_t *__restrict__ cend, Grid g, int max_nb,
                       int32_t *__restrict__ count, int32_t *__restrict__ idx,
-                      uint32_t *__restrict__ mask_scratch, const uint32_t *__restrict__ hflag,
-                      uint32_t *status, BatchDev b, int32_t *__restrict__ fb_tiles,
-                      uint32_t *fb_count, StepMask mask,
+                      const uint32_t *__restrict__ hflag, uint32_t *status, BatchDev b,
+                      int32_t *__restrict__ fb_tiles, uint32_t *fb_count, StepMask mask,
                       const unsigned long long *__restrict__ s2max)
 {
-    __shared__ SearchLds<kEntries> lds[kWavesPerBlock];
-    const int w = threadIdx.x / kWave;
-    SearchLds<kEntries> &L = lds[w];
+    __shared__ __attribute__((aligned(16))) SearchLds<W> L;
     const int64_t nn = Multi ? b.hdr->n_out : n;
     int64_t tile;
     if constexpr (Multi) {
         // The grid covers the capacity's tiles, the step uses the first
         // ntile: their blocks are spread over the eight XCDs, the rest exit.
-        const int64_t ntile = b.hdr->ntile;
-        const int64_t bt = xcd_used_block((ntile + kWavesPerBlock - 1) / kWavesPerBlock);
-        if (bt < 0) return;
-        tile = bt * kWavesPerBlock + w;
-        if (tile >= ntile) return;
+        tile = xcd_used_block(b.hdr->ntile);
+        if (tile < 0) return;
     } else {
-        tile = xcd_block() * kWavesPerBlock + w;
-        if (tile >= (nn + kWave - 1) / kWave) return;
+        tile = xcd_block();
         if (mask.bin) {
             // individual time steps: only tiles holding a particle whose step
             // closes need lists (the others keep their stale ones, unread)
@@ -985,10 +1052,9 @@ find_neighbors_kernel(int64_t n, int64_t ld, const SearchRec *__restrict__ srec,
             if (__ballot(i < nn && step_closes(mask, i)) == 0ull) return;
         }
     }
-    search_tile<Multi>(tile, nn, ld, srec, keys, cstart, cend, g, max_nb, count, idx,
-                       mask_scratch, hflag, status, b, L, fb_tiles, fb_count, s2max);
+    search_tile<Multi, W>(tile, nn, ld, srec, keys, cstart, cend, g, max_nb, count, idx, hflag,
+                          status, b, L, fb_tiles, fb_count, s2max);
 }
-
 
 // ---------------------------------------------------------------------------
 // Smoothing-length iteration (Algorithm 1, step 2, "neighbours and smoothing
@@ -1332,26 +1398,32 @@ __global__ void set_word_kernel(uint32_t *a, uint32_t v) { *a = v; }
 
 }  // namespace
 
+// Waves per tile of the search: four while the tiles would leave most of the
+// chip's 1,024 SIMDs with less than two waves each.
+constexpr int64_t kSharedTiles = 2048;
+
 hipError_t launch_find_neighbors(sph_ctx ctx, const sph_particles &p, const sph_nbrs &nb,
                                  const StepMask &mask)
 {
     const int64_t tiles = (p.n + kWave - 1) / kWave;
-    const unsigned blocks = (unsigned)((tiles + kWavesPerBlock - 1) / kWavesPerBlock);
     clear_count_kernel<<<1, 1, 0, ctx->stream>>>(ctx->fb_count);
     int tk = ktime_begin(ctx, TK_FIND_NEIGHBORS);
-    find_neighbors_kernel<false><<<blocks, kBlock, 0, ctx->stream>>>(
-        p.n, p.n, ctx->srec, ctx->sorted_keys, ctx->cell_start, ctx->cell_end, ctx->grid,
-        nb.max_nb, nb.count, nb.idx, ctx->nb_mask, ctx->hflag_dev, ctx->status_dev, BatchDev{},
-        ctx->fb_tiles, ctx->fb_count, mask,
-        reinterpret_cast<const unsigned long long *>(ctx->cell_s2max));
+    const unsigned long long *s2max =
+        reinterpret_cast<const unsigned long long *>(ctx->cell_s2max);
+#define SPH_SEARCH(W)                                                                      \
+    find_neighbors_kernel<false, W><<<(unsigned)tiles, W * kWave, 0, ctx->stream>>>(       \
+        p.n, p.n, ctx->srec, ctx->sorted_keys, ctx->cell_start, ctx->cell_end, ctx->grid,  \
+        nb.max_nb, nb.count, nb.idx, ctx->hflag_dev, ctx->status_dev, BatchDev{},          \
+        ctx->fb_tiles, ctx->fb_count, mask, s2max)
+    if (tiles <= kSharedTiles) SPH_SEARCH(4);
+    else SPH_SEARCH(1);
+#undef SPH_SEARCH
     ktime_end(ctx, tk);
     const unsigned fblocks = (unsigned)std::min<int64_t>(tiles, kFallbackBlocks);
     tk = ktime_begin(ctx, TK_FALLBACK);
     fallback_kernel<false><<<fblocks, kWave, 0, ctx->stream>>>(
         p.n, p.n, ctx->srec, ctx->sorted_keys, ctx->cell_start, ctx->cell_end, ctx->grid,
-        nb.max_nb, nb.count, nb.idx, ctx->status_dev, BatchDev{}, ctx->fb_tiles, ctx->fb_count,
-        ctx->nb_mask, ctx->hflag_dev,
-        reinterpret_cast<const unsigned long long *>(ctx->cell_s2max));
+        nb.max_nb, nb.count, nb.idx, ctx->status_dev, BatchDev{}, ctx->fb_tiles, ctx->fb_count);
     ktime_end(ctx, tk);
     return hipGetLastError();
 }
@@ -1359,19 +1431,22 @@ hipError_t launch_find_neighbors(sph_ctx ctx, const sph_particles &p, const sph_
 hipError_t launch_find_neighbors_batch(sph_ctx ctx, const BatchDev &b, int max_nb,
                                        int32_t *count, int32_t *idx)
 {
-    // the mask scratch holds one region per tile: the capacity's, plus at
-    // most one partial tile per run (each run is cut into its own tiles)
+    // the capacity's tiles, plus at most one partial tile per run (each run
+    // is cut into its own tiles)
     const int64_t tiles = (b.cap + kWave - 1) / kWave + kEnsMaxSlots;
-    const unsigned blocks = (unsigned)((tiles + kWavesPerBlock - 1) / kWavesPerBlock);
     clear_count_kernel<<<1, 1, 0, ctx->stream>>>(ctx->fb_count);
-    find_neighbors_kernel<true><<<blocks, kBlock, 0, ctx->stream>>>(
-        0, b.cap, ctx->srec, ctx->sorted_keys, ctx->cell_start, ctx->cell_end, Grid{}, max_nb,
-        count, idx, ctx->nb_mask, nullptr, nullptr, b, ctx->fb_tiles, ctx->fb_count,
-        StepMask{}, nullptr);
+#define SPH_SEARCH(W)                                                                      \
+    find_neighbors_kernel<true, W><<<(unsigned)tiles, W * kWave, 0, ctx->stream>>>(        \
+        0, b.cap, ctx->srec, ctx->sorted_keys, ctx->cell_start, ctx->cell_end, Grid{},     \
+        max_nb, count, idx, nullptr, nullptr, b, ctx->fb_tiles, ctx->fb_count, StepMask{}, \
+        nullptr)
+    if (tiles <= kSharedTiles + kEnsMaxSlots) SPH_SEARCH(4);
+    else SPH_SEARCH(1);
+#undef SPH_SEARCH
     const unsigned fblocks = (unsigned)std::min<int64_t>(tiles, kFallbackBlocks);
     fallback_kernel<true><<<fblocks, kWave, 0, ctx->stream>>>(
         0, b.cap, ctx->srec, ctx->sorted_keys, ctx->cell_start, ctx->cell_end, Grid{}, max_nb,
-        count, idx, nullptr, b, ctx->fb_tiles, ctx->fb_count, ctx->nb_mask, nullptr, nullptr);
+        count, idx, nullptr, b, ctx->fb_tiles, ctx->fb_count);
     return hipGetLastError();
 }
 

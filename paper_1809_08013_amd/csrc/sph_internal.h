@@ -44,6 +44,7 @@ struct Grid {
     double len[3];      // hi - lo
     double half[3];     // 0.5 * len (minimum image threshold)
     double inv_s[3];    // cells per unit length
+    double reach;       // 2 h_max the cells were sized for (0: no cells)
 };
 
 struct PermFields {
@@ -130,7 +131,6 @@ struct BatchDev {
 };
 
 constexpr int kStencil = 27;
-constexpr int kSearchMaskWords = 88;  // per lane of a search wave: 2816 candidates
 
 // Neighbour-side records, one per particle in cell order, so that a
 // neighbour's data is one aligned block instead of one cache line per array.
@@ -303,7 +303,6 @@ struct sph_ctx_s {
     int32_t *cell_start = nullptr;
     int32_t *cell_end = nullptr;
     int64_t cell_cap = 0;
-    uint32_t *nb_mask = nullptr;     // search bit masks: kSearchMaskWords words per particle slot
     double *cell_s2max = nullptr;    // per cell: largest (2h)^2 of its particles
     double *iad_c = nullptr;         // IAD matrices, 6 per particle (xx xy xz yy yz zz)
     int32_t *fb_tiles = nullptr;     // search tiles left to the per-lane path
