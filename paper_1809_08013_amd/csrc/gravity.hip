@@ -37,8 +37,8 @@
 // Tree build and moments use plain FP64 operations in the order of their
 // definition (no fused multiply-add; correctly rounded division and square
 // root), so the tree and every acceptance decision are the definition's; the
-// terms use fused multiply-adds and take 1/sqrt from the hardware estimate
-// refined by two Newton steps (about one ulp).
+// terms use fused multiply-adds and take 1/sqrt from the hardware estimate and
+// its error's series to second order (about one ulp).
 #include <algorithm>
 #include <cmath>
 
@@ -49,14 +49,23 @@ namespace {
 
 constexpr int kThreads = 256;
 
-// 1/sqrt(x), x > 0: the hardware estimate and two Newton steps (about one
-// ulp in FP64).
+// 1/sqrt(x), x > 0, from the hardware estimate y (relative error below 2^-25):
+// with e = 1 - x y^2, y (1 - e)^(-1/2) = y (1 + e/2 + 3 e^2 / 8) to a term of
+// order e^3, far below an ulp. Five operations where two Newton steps take
+// seven.
 __device__ __forceinline__ double rsq_newton(double x)
 {
-    double y = __builtin_amdgcn_rsq(x);
-    const double h = 0.5 * x;
-    y = y * __builtin_fma(-h * y, y, 1.5);
-    return y * __builtin_fma(-h * y, y, 1.5);
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = __builtin_fma(-(x * y), y, 1.0);
+    return __builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
+}
+
+// m x^(-3/2), x > 0, the same way: y^3 (1 - e)^(-3/2) = y^3 (1 + 3 e/2 + 15 e^2 / 8).
+__device__ __forceinline__ double mass_rsq3(double m, double y, double x)
+{
+    const double e = __builtin_fma(-(x * y), y, 1.0);
+    const double c = __builtin_fma(e, __builtin_fma(e, 1.875, 1.5), 1.0);
+    return ((m * y) * (y * y)) * c;
 }
 
 __global__ void __launch_bounds__(256)
@@ -68,10 +77,20 @@ pack_grav_kernel(int64_t n, const double *__restrict__ x, const double *__restri
     if (i < n) out[i] = DensRec{x[i], y[i], z[i], m[i]};
 }
 
+// Shares of the sum: the j are cut into up to this many ranges, each summed by
+// its own blocks, so that few particles still fill the chip (the partial sums
+// take three of the reorder scratch's rows each).
+constexpr int kDirectShares = kPermFields / 3;
+
+// What bounds it: FP64 issue, 18 instructions a pair. 40,009 particles (157
+// blocks for 256 CUs when one block did the whole sum, 23 instructions a pair):
+// 3.30 ms; in six shares 1.21 ms, in eight 1.08 ms (1.5e12 pairs/s, 0.86 ms at
+// full issue rate).
+template <bool Soft>
 __global__ void __launch_bounds__(kThreads)
 gravity_direct_kernel(int64_t n, const DensRec *__restrict__ rec, double e2,
                       double *__restrict__ gx, double *__restrict__ gy,
-                      double *__restrict__ gz)
+                      double *__restrict__ gz, double *__restrict__ part)
 {
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     const bool active = i < n;
@@ -80,17 +99,19 @@ gravity_direct_kernel(int64_t n, const DensRec *__restrict__ rec, double e2,
     auto term = [&](const DensRec &o) {
         const double dx = me.x - o.x, dy = me.y - o.y, dz = me.z - o.z;
         const double d2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, __builtin_fma(dx, dx, e2)));
-        const double rs = d2 > 0.0 ? rsq_newton(d2) : 0.0;
-        const double t = o.m * (rs * rs * rs);
+        double y = __builtin_amdgcn_rsq(d2);
+        if (!Soft) y = d2 > 0.0 ? y : 0.0;
+        const double t = mass_rsq3(o.m, y, d2);
         sx = __builtin_fma(-t, dx, sx);
         sy = __builtin_fma(-t, dy, sy);
         sz = __builtin_fma(-t, dz, sz);
     };
-    int64_t j = 0;
-    if (n >= 4) {
-        DensRec a0 = rec[0], a1 = rec[1], a2 = rec[2], a3 = rec[3];
-        j = 4;
-        while (n - j >= 4) {
+    int64_t j = n * blockIdx.y / gridDim.y;
+    const int64_t end = n * (blockIdx.y + 1) / gridDim.y;
+    if (end - j >= 4) {
+        DensRec a0 = rec[j], a1 = rec[j + 1], a2 = rec[j + 2], a3 = rec[j + 3];
+        j += 4;
+        while (end - j >= 4) {
             const DensRec b0 = rec[j], b1 = rec[j + 1], b2 = rec[j + 2], b3 = rec[j + 3];
             term(a0);
             term(a1);
@@ -109,14 +130,35 @@ gravity_direct_kernel(int64_t n, const DensRec *__restrict__ rec, double e2,
         term(a2);
         term(a3);
     }
-    for (; j < n; ++j) term(rec[j]);
+    for (; j < end; ++j) term(rec[j]);
     if (active) {
-        gx[i] = sx;
-        gy[i] = sy;
-        gz[i] = sz;
+        if (gridDim.y > 1) {
+            double *o = part + 3 * (int64_t)blockIdx.y * n + i;
+            o[0] = sx;
+            o[n] = sy;
+            o[2 * n] = sz;
+        } else {
+            gx[i] = sx;
+            gy[i] = sy;
+            gz[i] = sz;
+        }
     }
 }
 
+// The shares' sums, in their order.
+__global__ void __launch_bounds__(kThreads)
+gravity_shares_kernel(int64_t n, int shares, const double *__restrict__ part,
+                      double *__restrict__ gx, double *__restrict__ gy, double *__restrict__ gz)
+{
+    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (i >= n) return;
+    double s[3] = {part[i], part[n + i], part[2 * n + i]};
+    for (int k = 1; k < shares; ++k)
+        for (int a = 0; a < 3; ++a) s[a] += part[(3 * (int64_t)k + a) * n + i];
+    gx[i] = s[0];
+    gy[i] = s[1];
+    gz[i] = s[2];
+}
 
 // ------------------------------------------------------------ octree gravity
 
@@ -590,8 +632,8 @@ gravity_tree_kernel(const DensRec *__restrict__ pos, const int32_t *__restrict__
                     const double dx = me.x - o.x, dy = me.y - o.y, dz = me.z - o.z;
                     const double d2 =
                         __builtin_fma(dz, dz, __builtin_fma(dy, dy, __builtin_fma(dx, dx, e2)));
-                    const double rs = rsq_newton(d2);
-                    const double t = lpos[j] == k ? 0.0 : o.m * (rs * rs * rs);
+                    const double w = mass_rsq3(o.m, __builtin_amdgcn_rsq(d2), d2);
+                    const double t = lpos[j] == k ? 0.0 : w;
                     ax = __builtin_fma(-t, dx, ax);
                     ay = __builtin_fma(-t, dy, ay);
                     az = __builtin_fma(-t, dz, az);
@@ -618,8 +660,20 @@ hipError_t launch_gravity_direct(sph_ctx ctx, const sph_particles &p, double eps
 {
     pack_grav_kernel<<<blocks_for(p.n, 256), 256, 0, ctx->stream>>>(p.n, p.x, p.y, p.z, p.m,
                                                                     ctx->drec);
-    gravity_direct_kernel<<<blocks_for(p.n, kThreads), kThreads, 0, ctx->stream>>>(
-        p.n, ctx->drec, eps * eps, gx, gy, gz);
+    // eight waves per SIMD (2,048 blocks) where the shares allow it
+    const unsigned blocks = blocks_for(p.n, kThreads);
+    const unsigned shares = std::max(1u, std::min<unsigned>(kDirectShares, 2048u / blocks));
+    const dim3 grid(blocks, shares);
+    double *part = ctx->perm_tmp;  // (no build is under way)
+    if (eps * eps > 0.0)
+        gravity_direct_kernel<true><<<grid, kThreads, 0, ctx->stream>>>(p.n, ctx->drec, eps * eps,
+                                                                        gx, gy, gz, part);
+    else
+        gravity_direct_kernel<false><<<grid, kThreads, 0, ctx->stream>>>(p.n, ctx->drec, eps * eps,
+                                                                         gx, gy, gz, part);
+    if (shares > 1)
+        gravity_shares_kernel<<<blocks, kThreads, 0, ctx->stream>>>(p.n, (int)shares, part, gx, gy,
+                                                                    gz);
     return hipGetLastError();
 }
 
