@@ -216,7 +216,8 @@ int64_t sph_ctx_scratch_bytes(sph_ctx ctx);
  * the sums) every later launch, by this context, of the kernels
  * find_neighbors_kernel, fallback_kernel, density_kernel, iad_kernel and
  * momentum_kernel is bracketed by two HIP events on the context's stream (not
- * inside sph_step_capture); enable = 0 stops. sph_ctx_kernel_time waits for
+ * inside sph_step_capture; fallback_kernel's work is part of
+ * find_neighbors_kernel, so it has no launches); enable = 0 stops. sph_ctx_kernel_time waits for
  * the recorded launches and returns the named kernel's mean duration in ms
  * and its launch count since timing was enabled (SPH_E_INVALID for another
  * name). The events are created on the host (hipEventCreate), never

@@ -298,7 +298,7 @@ void free_ctx(sph_ctx ctx)
     void *ptrs[] = {ctx->keys[0], ctx->keys[1], ctx->vals[0], ctx->vals[1], ctx->hist,
                     ctx->scan_part, ctx->cell_start, ctx->cell_end, ctx->perm_tmp,
                     ctx->perm_tmp_id, ctx->red_part, ctx->status_dev, ctx->hflag_dev,
-                    ctx->fb_tiles, ctx->fb_count, ctx->it_words, ctx->it_hmax, ctx->cell_s2max,
+                    ctx->it_words, ctx->it_hmax, ctx->cell_s2max,
                     ctx->iad_c, ctx->dtc, ctx->blk_words,
                     ctx->srec, ctx->drec, ctx->prec};
     for (void *q : ptrs)
@@ -378,8 +378,6 @@ sph_status sph_ctx_create(sph_ctx *out, int64_t n_max, int32_t max_nb, sph_strea
     ALLOC(ctx->cell_end, ctx->cell_cap);
     ALLOC(ctx->cell_s2max, ctx->cell_cap);
     ALLOC(ctx->iad_c, 6 * n_max);
-    ALLOC(ctx->fb_tiles, (n_max + 63) / 64);
-    ALLOC(ctx->fb_count, 1);
     ALLOC(ctx->it_words, kItWords);
     ALLOC(ctx->it_hmax, 1);
     ALLOC(ctx->srec, n_max);

@@ -42,8 +42,8 @@
 // the FP64 relation with the minimum image for every pair.
 //
 // A tile with more distinct cells than its union build holds (9 or 18) takes the
-// per-lane path in a second kernel: each lane walks its own stencil (sorted by
-// Morton key) and writes its entries directly. Both paths produce the same set
+// per-lane path: each lane walks its own stencil (sorted by Morton key) and
+// writes its entries directly. Both paths produce the same set
 // in the same (ascending) order, so the sums over a list do not depend on the
 // path or on where the tile boundaries fall.
 #include <algorithm>
@@ -75,10 +75,6 @@ struct SearchShape<4> {
     static constexpr int kMaxDist = 18, kEntries = 512, kCells = 486, kBlocks = 28;
     typedef uint16_t Cell;
 };
-// Grid of the second kernel: one-wave blocks draining the worklist; the blocks
-// past the worklist's length exit at once.
-constexpr int64_t kFallbackBlocks = 2048;
-
 enum WrapMode { WRAP_NONE = 0, WRAP_CELL = 1, WRAP_PAIR = 2 };
 
 __device__ __forceinline__ uint32_t spread3(uint32_t v)
@@ -423,14 +419,15 @@ __device__ __forceinline__ void tile_sync()
 // One tile of 64 particles by the whole block of W waves. Multi: the
 // particles belong to one run of an ensemble (slot in the high key bits), and
 // the tile uses that run's grid and cell range.
+// Returns false, with nothing written, for a tile with more distinct cells or
+// union cells than the shape holds (the same for every thread).
 template <bool Multi, int W>
-__device__ __forceinline__ void search_tile(
+__device__ __forceinline__ bool search_tile(
     int64_t tile, int64_t n, int64_t ld, const SearchRec *__restrict__ srec,
     const uint32_t *__restrict__ keys, const int32_t *__restrict__ cstart,
     const int32_t *__restrict__ cend, const Grid &g0, int max_nb, int32_t *__restrict__ count,
     int32_t *__restrict__ idx, const uint32_t *__restrict__ hflag, uint32_t *status0,
-    const BatchDev &b, SearchLds<W> &L, int32_t *__restrict__ fb_tiles, uint32_t *fb_count,
-    const unsigned long long *__restrict__ s2max)
+    const BatchDev &b, SearchLds<W> &L, const unsigned long long *__restrict__ s2max)
 {
     typedef SearchShape<W> Shape;
     constexpr int kThreadsT = W * kWave;
@@ -469,10 +466,7 @@ __device__ __forceinline__ void search_tile(
     const bool first = active && (lane == 0 || ckey != prev);
     const uint64_t fm = __ballot(first);
     const int ndist = __popcll(fm);
-    if (ndist > Shape::kMaxDist) {
-        if (tid == 0) fb_tiles[atomicAdd(fb_count, 1u)] = (int32_t)tile;
-        return;  // (the whole block)
-    }
+    if (ndist > Shape::kMaxDist) return false;
     if (w == 0 && first) L.dkeys[__popcll(fm & lt)] = mkey;
 
     // Extents of the tile around its first particle (nearest images), the
@@ -609,10 +603,7 @@ __device__ __forceinline__ void search_tile(
         }
     }
     nu = __builtin_amdgcn_readfirstlane(nu);
-    if (nu > Shape::kCells) {
-        if (tid == 0) fb_tiles[atomicAdd(fb_count, 1u)] = (int32_t)tile;
-        return;  // (the whole block)
-    }
+    if (nu > Shape::kCells) return false;
     if (tid < 4) L.ukey[nu + tid] = INT_MAX;  // (read in groups of four)
     tile_sync<W>();
     // place in the order of first particles: the number of smaller keys
@@ -922,37 +913,31 @@ __device__ __forceinline__ void search_tile(
         count[i] = carry;
         if (carry > max_nb) atomicOr(Multi ? &b.status[slot0] : status0, ST_CAPACITY);
     }
+    return true;
 }
 
-// Per-lane path, one wave per listed tile: each lane visits its own
-// stencil's cells in ascending Morton order (= ascending order of their
+// Per-lane path, one wave for a tile whose union is not taken: each lane visits
+// its own stencil's cells in ascending Morton order (= ascending order of their
 // particles): the 27 keys are sorted in registers, then each cell is walked
 // once with the next record already in flight, so the lane's list is
 // ascending too.
 template <bool Multi>
-__global__ void __launch_bounds__(kWave)
-fallback_kernel(int64_t n, int64_t ld, const SearchRec *__restrict__ srec,
-                const uint32_t *__restrict__ keys, const int32_t *__restrict__ cstart,
-                const int32_t *__restrict__ cend, Grid g0, int max_nb,
-                int32_t *__restrict__ count, int32_t *__restrict__ idx, uint32_t *status0,
-                BatchDev b, const int32_t *__restrict__ fb_tiles, const uint32_t *fb_count)
+__device__ __forceinline__ void lane_lists(
+    int64_t tile, int64_t n, int64_t ld, const SearchRec *__restrict__ srec,
+    const uint32_t *__restrict__ keys, const int32_t *__restrict__ cstart,
+    const int32_t *__restrict__ cend, const Grid &g0, int max_nb, int32_t *__restrict__ count,
+    int32_t *__restrict__ idx, uint32_t *status0, const BatchDev &b)
 {
-    const int lane = threadIdx.x;
-    if (Multi) n = b.hdr->n_out;
-    const uint32_t nfb = *fb_count;
-    for (uint32_t q = blockIdx.x; q < nfb; q += gridDim.x) {
-    const int64_t tile = (int64_t)fb_tiles[q];
     int64_t t0, tend;
     tile_span<Multi>(tile, n, b, t0, tend);
-    const int64_t i = t0 + lane;
-    const bool active = i < tend;
-    const uint32_t key = active ? keys[i] : 0xFFFFFFFFu;
-    const SearchRec me = active ? srec[i] : SearchRec{0.0, 0.0, 0.0, 0.0};
-    const int my_slot = Multi && active ? (int)(key >> kEnsSlotShift) : 0;
+    const int64_t i = t0 + (threadIdx.x & (kWave - 1));
+    if (i >= tend) return;
+    const uint32_t key = keys[i];
+    const SearchRec me = srec[i];
+    const int my_slot = Multi ? (int)(key >> kEnsSlotShift) : 0;
     const uint32_t mkey = Multi ? ((key >> kSliceBits) & kEnsMortonMask) : (key >> g0.zbits);
     const int myc[3] = {(int)compact3(mkey), (int)compact3(mkey >> 1),
                         (int)compact3(mkey >> 2)};
-    if (!active) continue;
     const Grid &gl = Multi ? b.runs[my_slot].grid : g0;
     const int64_t cbl = Multi ? (int64_t)b.runs[my_slot].cell_base : 0;
     const double no_shift[3] = {0.0, 0.0, 0.0};
@@ -1012,10 +997,7 @@ fallback_kernel(int64_t n, int64_t ld, const SearchRec *__restrict__ srec,
     }
     count[i] = cnt;
     if (cnt > max_nb) atomicOr(Multi ? &b.status[my_slot] : status0, ST_CAPACITY);
-    }
 }
-
-__global__ void clear_count_kernel(uint32_t *c) { *c = 0u; }
 
 // What bounds it (1M patch, one wave per tile): vector issue, 11,400
 // instructions a tile (3,800 for the 21.8 blocks of candidates, 3,600 for the
@@ -1032,8 +1014,7 @@ find_neighbors_kernel(int64_t n, int64_t ld, const SearchRec *__restrict__ srec,
                       const int32_t *__restrict__ cend, Grid g, int max_nb,
                       int32_t *__restrict__ count, int32_t *__restrict__ idx,
                       const uint32_t *__restrict__ hflag, uint32_t *status, BatchDev b,
-                      int32_t *__restrict__ fb_tiles, uint32_t *fb_count, StepMask mask,
-                      const unsigned long long *__restrict__ s2max)
+                      StepMask mask, const unsigned long long *__restrict__ s2max)
 {
     __shared__ __attribute__((aligned(16))) SearchLds<W> L;
     const int64_t nn = Multi ? b.hdr->n_out : n;
@@ -1052,8 +1033,10 @@ find_neighbors_kernel(int64_t n, int64_t ld, const SearchRec *__restrict__ srec,
             if (__ballot(i < nn && step_closes(mask, i)) == 0ull) return;
         }
     }
-    search_tile<Multi, W>(tile, nn, ld, srec, keys, cstart, cend, g, max_nb, count, idx, hflag,
-                          status, b, L, fb_tiles, fb_count, s2max);
+    if (!search_tile<Multi, W>(tile, nn, ld, srec, keys, cstart, cend, g, max_nb, count, idx, hflag,
+                               status, b, L, s2max) &&
+        threadIdx.x < kWave)
+        lane_lists<Multi>(tile, nn, ld, srec, keys, cstart, cend, g, max_nb, count, idx, status, b);
 }
 
 // ---------------------------------------------------------------------------
@@ -1406,24 +1389,17 @@ hipError_t launch_find_neighbors(sph_ctx ctx, const sph_particles &p, const sph_
                                  const StepMask &mask)
 {
     const int64_t tiles = (p.n + kWave - 1) / kWave;
-    clear_count_kernel<<<1, 1, 0, ctx->stream>>>(ctx->fb_count);
-    int tk = ktime_begin(ctx, TK_FIND_NEIGHBORS);
+    const int tk = ktime_begin(ctx, TK_FIND_NEIGHBORS);
     const unsigned long long *s2max =
         reinterpret_cast<const unsigned long long *>(ctx->cell_s2max);
 #define SPH_SEARCH(W)                                                                      \
     find_neighbors_kernel<false, W><<<(unsigned)tiles, W * kWave, 0, ctx->stream>>>(       \
         p.n, p.n, ctx->srec, ctx->sorted_keys, ctx->cell_start, ctx->cell_end, ctx->grid,  \
         nb.max_nb, nb.count, nb.idx, ctx->hflag_dev, ctx->status_dev, BatchDev{},          \
-        ctx->fb_tiles, ctx->fb_count, mask, s2max)
+        mask, s2max)
     if (tiles <= kSharedTiles) SPH_SEARCH(4);
     else SPH_SEARCH(1);
 #undef SPH_SEARCH
-    ktime_end(ctx, tk);
-    const unsigned fblocks = (unsigned)std::min<int64_t>(tiles, kFallbackBlocks);
-    tk = ktime_begin(ctx, TK_FALLBACK);
-    fallback_kernel<false><<<fblocks, kWave, 0, ctx->stream>>>(
-        p.n, p.n, ctx->srec, ctx->sorted_keys, ctx->cell_start, ctx->cell_end, ctx->grid,
-        nb.max_nb, nb.count, nb.idx, ctx->status_dev, BatchDev{}, ctx->fb_tiles, ctx->fb_count);
     ktime_end(ctx, tk);
     return hipGetLastError();
 }
@@ -1434,19 +1410,13 @@ hipError_t launch_find_neighbors_batch(sph_ctx ctx, const BatchDev &b, int max_n
     // the capacity's tiles, plus at most one partial tile per run (each run
     // is cut into its own tiles)
     const int64_t tiles = (b.cap + kWave - 1) / kWave + kEnsMaxSlots;
-    clear_count_kernel<<<1, 1, 0, ctx->stream>>>(ctx->fb_count);
 #define SPH_SEARCH(W)                                                                      \
     find_neighbors_kernel<true, W><<<(unsigned)tiles, W * kWave, 0, ctx->stream>>>(        \
         0, b.cap, ctx->srec, ctx->sorted_keys, ctx->cell_start, ctx->cell_end, Grid{},     \
-        max_nb, count, idx, nullptr, nullptr, b, ctx->fb_tiles, ctx->fb_count, StepMask{}, \
-        nullptr)
+        max_nb, count, idx, nullptr, nullptr, b, StepMask{}, nullptr)
     if (tiles <= kSharedTiles + kEnsMaxSlots) SPH_SEARCH(4);
     else SPH_SEARCH(1);
 #undef SPH_SEARCH
-    const unsigned fblocks = (unsigned)std::min<int64_t>(tiles, kFallbackBlocks);
-    fallback_kernel<true><<<fblocks, kWave, 0, ctx->stream>>>(
-        0, b.cap, ctx->srec, ctx->sorted_keys, ctx->cell_start, ctx->cell_end, Grid{}, max_nb,
-        count, idx, nullptr, b, ctx->fb_tiles, ctx->fb_count);
     return hipGetLastError();
 }
 

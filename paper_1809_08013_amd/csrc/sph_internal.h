@@ -260,7 +260,7 @@ namespace sph {
 // durations are summed when sph_ctx_kernel_time reads them.
 enum TimedKernel {
     TK_FIND_NEIGHBORS = 0,  // find_neighbors_kernel
-    TK_FALLBACK,            // fallback_kernel
+    TK_FALLBACK,            // fallback_kernel (its path is part of the search kernel: no launches)
     TK_DENSITY,             // density_kernel
     TK_IAD,                 // iad_kernel
     TK_MOMENTUM,            // momentum_kernel
@@ -305,8 +305,6 @@ struct sph_ctx_s {
     int64_t cell_cap = 0;
     double *cell_s2max = nullptr;    // per cell: largest (2h)^2 of its particles
     double *iad_c = nullptr;         // IAD matrices, 6 per particle (xx xy xz yy yz zz)
-    int32_t *fb_tiles = nullptr;     // search tiles left to the per-lane path
-    uint32_t *fb_count = nullptr;
     uint32_t *it_words = nullptr;    // h iteration: out-of-band count, largest count
     unsigned long long *it_hmax = nullptr;  // h iteration: largest h (bit pattern)
 
