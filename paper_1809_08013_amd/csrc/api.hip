@@ -296,7 +296,7 @@ void free_ctx(sph_ctx ctx)
     if (ctx->step_exec) (void)hipGraphExecDestroy(ctx->step_exec);
     if (ctx->step_graph) (void)hipGraphDestroy(ctx->step_graph);
     void *ptrs[] = {ctx->keys[0], ctx->keys[1], ctx->vals[0], ctx->vals[1], ctx->hist,
-                    ctx->scan_part, ctx->cell_start, ctx->cell_end, ctx->perm_tmp,
+                    ctx->scan_part, ctx->flag_part, ctx->cell_start, ctx->cell_end, ctx->perm_tmp,
                     ctx->perm_tmp_id, ctx->red_part, ctx->status_dev, ctx->hflag_dev,
                     ctx->it_words, ctx->it_hmax, ctx->cell_s2max,
                     ctx->iad_c, ctx->dtc, ctx->blk_words,
@@ -362,8 +362,7 @@ sph_status sph_ctx_create(sph_ctx *out, int64_t n_max, int32_t max_nb, sph_strea
     ctx->stream = (hipStream_t)stream;
     ctx->n_max = n_max;
     ctx->max_nb = max_nb;
-    ctx->tiles_max = (n_max + kSortTile - 1) / kSortTile;
-    ctx->scan_len_max = ctx->tiles_max * kRadixBins;
+    ctx->scan_len_max = sort_tiles_max(n_max) * kRadixBins;
     ctx->cell_cap = std::max<int64_t>(n_max / 8 + 64, 65536);
     sph_status s = SPH_OK;
 #define ALLOC(ptr, count)                                   \
@@ -374,6 +373,7 @@ sph_status sph_ctx_create(sph_ctx *out, int64_t n_max, int32_t max_nb, sph_strea
     ALLOC(ctx->vals[1], n_max);
     ALLOC(ctx->hist, ctx->scan_len_max);
     ALLOC(ctx->scan_part, (ctx->scan_len_max + kScanChunk - 1) / kScanChunk + 1);
+    ALLOC(ctx->flag_part, sort_tiles_max(n_max) + kSortSmall / 256);
     ALLOC(ctx->cell_start, ctx->cell_cap);
     ALLOC(ctx->cell_end, ctx->cell_cap);
     ALLOC(ctx->cell_s2max, ctx->cell_cap);
@@ -463,9 +463,10 @@ sph_status sph_ctx_check(sph_ctx ctx)
 
 namespace {
 
-// sph_build_cells, with up to 6 extra per-particle arrays reordered alongside
+// sph_build_cells, with up to 6 extra per-particle arrays reordered alongside and,
+// if kd.dt_dev is set, a kick-drift of the (not yet reordered) particles first.
 sph_status build_cells(sph_ctx ctx, const sph_particles *p, const sph_box *box, double h_max,
-                       double *const *extra, int n_extra)
+                       double *const *extra, int n_extra, const KickDrift &kd = KickDrift{})
 {
     if (!ctx) return fail(nullptr, SPH_E_INVALID, "ctx is NULL");
     sph_status s;
@@ -479,7 +480,23 @@ sph_status build_cells(sph_ctx ctx, const sph_particles *p, const sph_box *box, 
     ctx->grid = make_grid(*box, h_max, ctx->cell_cap, kMaxAxisCells);
     ctx->n_built = p->n;
     if (p->n == 0) return SPH_OK;
-    SPH_HIP(ctx, launch_build_cells(ctx, *p, ctx->grid, h_max, extra, n_extra));
+    SPH_HIP(ctx, launch_build_cells(ctx, *p, ctx->grid, h_max, extra, n_extra, kd));
+    return SPH_OK;
+}
+
+// The checks of sph_integrate.
+sph_status check_integrate(sph_ctx ctx, const sph_particles *p, const sph_box *box, int32_t stage,
+                           const double *dt_dev, const sph_accel *a)
+{
+    if (!ctx) return fail(nullptr, SPH_E_INVALID, "ctx is NULL");
+    sph_status s;
+    if ((s = check_particles(ctx, p, true)) != SPH_OK) return s;
+    if ((s = check_box(ctx, box)) != SPH_OK) return s;
+    if (stage != SPH_KICK_DRIFT && stage != SPH_KICK)
+        return fail(ctx, SPH_E_INVALID, "unknown stage %d", stage);
+    if (!dt_dev || !a) return fail(ctx, SPH_E_INVALID, "dt_dev and accel are required");
+    if (p->n > 0 && (!a->ax || !a->ay || !a->az || !a->dudt))
+        return fail(ctx, SPH_E_INVALID, "ax, ay, az, dudt are required");
     return SPH_OK;
 }
 
@@ -652,16 +669,8 @@ sph_status sph_momentum_energy(sph_ctx ctx, const sph_particles *p, const sph_bo
 sph_status sph_integrate(sph_ctx ctx, const sph_particles *p, const sph_box *box,
                          int32_t stage, const double *dt_dev, const sph_accel *a)
 {
-    if (!ctx) return fail(nullptr, SPH_E_INVALID, "ctx is NULL");
-    sph_status s;
-    if ((s = check_particles(ctx, p, true)) != SPH_OK) return s;
-    if ((s = check_box(ctx, box)) != SPH_OK) return s;
-    if (stage != SPH_KICK_DRIFT && stage != SPH_KICK)
-        return fail(ctx, SPH_E_INVALID, "unknown stage %d", stage);
-    if (!dt_dev || !a) return fail(ctx, SPH_E_INVALID, "dt_dev and accel are required");
-    if (p->n == 0) return SPH_OK;
-    if (!a->ax || !a->ay || !a->az || !a->dudt)
-        return fail(ctx, SPH_E_INVALID, "ax, ay, az, dudt are required");
+    const sph_status s = check_integrate(ctx, p, box, stage, dt_dev, a);
+    if (s != SPH_OK || p->n == 0) return s;
     SPH_HIP(ctx, launch_integrate(ctx, *p, box_grid(*box), stage, dt_dev, *a));
     return SPH_OK;
 }
@@ -718,8 +727,15 @@ sph_status sph_step(sph_ctx ctx, const sph_particles *p, const sph_box *box, dou
         if (!f) return fail(ctx, SPH_E_INVALID, "fields is NULL");
         if ((s = sph_volume_weights(ctx, p, f->rho, prm->volume_p)) != SPH_OK) return s;
     }
-    if ((s = sph_integrate(ctx, p, box, SPH_KICK_DRIFT, dt_dev, a)) != SPH_OK) return s;
-    if ((s = sph_build_cells(ctx, p, box, h_max)) != SPH_OK) return s;
+    if ((s = check_integrate(ctx, p, box, SPH_KICK_DRIFT, dt_dev, a)) != SPH_OK) return s;
+    // the kick-drift is taken by the build's first kernel; where the build
+    // refuses its arguments, by its own
+    if ((s = build_cells(ctx, p, box, h_max, nullptr, 0,
+                         KickDrift{dt_dev, a->ax, a->ay, a->az, a->dudt})) != SPH_OK) {
+        if (s != SPH_E_HIP && p->n > 0)
+            SPH_HIP(ctx, launch_integrate(ctx, *p, box_grid(*box), SPH_KICK_DRIFT, dt_dev, *a));
+        return s;
+    }
     if ((s = sph_find_neighbors(ctx, p, box, nb)) != SPH_OK) return s;
     if (!f) return fail(ctx, SPH_E_INVALID, "fields is NULL");
     if ((s = sph_density(ctx, p, box, nb, prm, f->rho)) != SPH_OK) return s;

@@ -50,57 +50,232 @@ __device__ __forceinline__ uint32_t slice_of(double v, double lo, double inv_s, 
     return (uint32_t)q;
 }
 
-__global__ void clear_word_kernel(uint32_t *w) { *w = 0u; }
+// Place of a tile's count of a digit: digit-major where a scan turns the counts
+// into offsets; tile-major where the scatter adds them up itself, so that a wave
+// reads a tile's 256 counts as one row.
+struct HistAt {
+    int64_t digit, tile;
+    __device__ int64_t operator()(int64_t d, int64_t t) const { return d * digit + t * tile; }
+};
 
-// Sort key of each particle: the Morton key of its cell, then its z slice in
-// the cell; vals = current index. Flags h > h_max, and sets *hflag when some
-// h differs from h[0] (one atomic per wave: with variable h, one per
-// particle on the same word serialised the kernel, 168 us at 1M).
-__global__ void __launch_bounds__(256)
-keys_kernel(int64_t n, const double *__restrict__ x, const double *__restrict__ y,
-            const double *__restrict__ z, const double *__restrict__ h, Grid g,
-            double h_max, uint32_t *__restrict__ keys, int32_t *__restrict__ vals,
-            uint32_t *hflag, uint32_t *status)
+// The arrays of one build: the fields present (x, y, z first, then vx .. p_bg,
+// gx .. xw and the extra ones), where h and v stand among them, and the scratch
+// copies.
+struct BuildArrays {
+    PermFields f;
+    int h, g;               // index of h, and of gx (-1: absent)
+    double *tmp;            // rows of `stride`
+    int64_t stride;
+    int32_t *tmp_id;
+};
+
+// First kernel of a build, one block per sort tile: copies every field to the
+// scratch rows (the last kernel gathers them back in cell order), forms each
+// particle's sort key (the Morton key of its cell, then its z slice in the
+// cell) and the tile's digit counts for the first sort pass, clears the cell
+// table, flags h > h_max and notes whether some h differs from h[0]. Drift: the
+// particles take their kick-drift on the way, which saves a pass over the
+// state.
+template <bool Drift, int Threads, int Items>
+__global__ void __launch_bounds__(Threads)
+build_head_kernel(int64_t n, BuildArrays A, Grid g, double h_max, KickDrift kd,
+                  uint32_t *__restrict__ keys, uint32_t *__restrict__ hist, HistAt at,
+                  uint32_t *__restrict__ flag_part, uint32_t *status, int64_t ncell,
+                  int32_t *__restrict__ cstart, int32_t *__restrict__ cend,
+                  unsigned long long *__restrict__ s2max)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool active = i < n;
-    const double hi = active ? h[i] : 0.0;
-    // One flag update per block at most, and none once the flag is set: an
-    // atomic from every wave to the one word serialises in its L2 channel
-    // (~10 ns each, 150 us over 10^6 particles of varying h).
-    const int differs = __syncthreads_or(active && hi != h[0]);
-    const int above = __syncthreads_or(active && !(hi <= h_max));
-    if (threadIdx.x == 0) {
-        if (differs && __hip_atomic_load(hflag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u)
-            atomicOr(hflag, 1u);
-        if (above) atomicOr(status, ST_DOMAIN);
+    constexpr int kFirst = 11;  // fields in flight together: x .. p_bg
+    __shared__ uint32_t cnt[kRadixBins];
+    const int tid = threadIdx.x;
+    if (tid < kRadixBins) cnt[tid] = 0;
+    for (int64_t c = (int64_t)blockIdx.x * Threads + tid; c < ncell;
+         c += (int64_t)gridDim.x * Threads) {
+        cstart[c] = 0;
+        cend[c] = 0;
+        s2max[c] = 0ull;
     }
-    if (!active) return;
-    uint32_t cx = (uint32_t)cell_of(x[i], g.lo[0], g.inv_s[0], g.nc[0]);
-    uint32_t cy = (uint32_t)cell_of(y[i], g.lo[1], g.inv_s[1], g.nc[1]);
-    uint32_t cz = (uint32_t)cell_of(z[i], g.lo[2], g.inv_s[2], g.nc[2]);
-    const uint32_t zq = slice_of(z[i], g.lo[2], g.inv_s[2], (int)cz, g.zbits);
-    keys[i] = ((spread3(cx) | (spread3(cy) << 1) | (spread3(cz) << 2)) << g.zbits) | zq;
-    vals[i] = (int32_t)i;
+    const double *hp = A.f.f[A.h];
+    const double h0 = hp[0];
+    double dt = 0.0;
+    if (Drift) dt = kd.dt_dev[0];
+    bool differs = false, above = false;
+    __syncthreads();
+#pragma unroll 1
+    for (int it = 0; it < Items; ++it) {
+        const int64_t i = (int64_t)blockIdx.x * (Threads * Items) + it * Threads + tid;
+        if (i >= n) break;
+        double w[kFirst];
+#pragma unroll
+        for (int k = 0; k < kFirst; ++k)
+            if (k < A.f.nf) w[k] = A.f.f[k][i];
+        const double hi = hp[i];
+        const int32_t id = A.f.id[i];
+        if (Drift) {
+            // (the state of a step has x .. m, so v and u are 3 .. 6)
+            double t[3] = {kd.ax[i], kd.ay[i], kd.az[i]};
+            if (A.g >= 0) {
+#pragma unroll
+                for (int a = 0; a < 3; ++a) t[a] += A.f.f[A.g + a][i];
+            }
+            double p[3] = {w[0], w[1], w[2]}, v[3] = {w[3], w[4], w[5]};
+            half_kick(0.5 * dt, t, kd.dudt[i], v, w[6]);
+            drift(dt, g, v, p);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                w[a] = p[a];
+                w[3 + a] = v[a];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < kFirst; ++k)
+            if (k < A.f.nf) A.tmp[k * A.stride + i] = w[k];
+        A.tmp_id[i] = id;
+        differs |= hi != h0;
+        above |= !(hi <= h_max);
+        const uint32_t cx = (uint32_t)cell_of(w[0], g.lo[0], g.inv_s[0], g.nc[0]);
+        const uint32_t cy = (uint32_t)cell_of(w[1], g.lo[1], g.inv_s[1], g.nc[1]);
+        const uint32_t cz = (uint32_t)cell_of(w[2], g.lo[2], g.inv_s[2], g.nc[2]);
+        const uint32_t zq = slice_of(w[2], g.lo[2], g.inv_s[2], (int)cz, g.zbits);
+        const uint32_t key =
+            ((spread3(cx) | (spread3(cy) << 1) | (spread3(cz) << 2)) << g.zbits) | zq;
+        keys[i] = key;
+        atomicAdd(&cnt[key & (kRadixBins - 1)], 1u);
+#pragma unroll 4
+        for (int k = kFirst; k < A.f.nf; ++k) A.tmp[k * A.stride + i] = A.f.f[k][i];
+    }
+    const int any_differs = __syncthreads_or(differs);
+    const int any_above = __syncthreads_or(above);
+    if (tid == 0) {
+        flag_part[blockIdx.x] = any_differs ? 1u : 0u;
+        if (any_above) atomicOr(status, ST_DOMAIN);
+    }
+    if (hist && tid < kRadixBins) hist[at(tid, blockIdx.x)] = cnt[tid];
 }
 
-// Per-tile digit histogram, digit-major layout hist[d * ntiles + tile].
-__global__ void __launch_bounds__(kSortThreads)
+// Sorts n <= 1024 Items keys in one block: stable LSD passes of 8 bits with the
+// keys and their indices in registers, exchanged through LDS. Each wave takes a
+// contiguous run of the keys and ranks it 64 at a time (one ballot per digit
+// bit matches the lanes of equal digits) against its own digit counts, so the
+// order within a digit is kept and a pass has four barriers. Also reduces the
+// first kernel's h flags.
+template <int Items>
+__global__ void __launch_bounds__(1024)
+sort_small_kernel(int n, int key_bits, const uint32_t *__restrict__ kin,
+                  uint32_t *__restrict__ kout, int32_t *__restrict__ vout, int nflag,
+                  const uint32_t *__restrict__ flag_part, uint32_t *__restrict__ hflag)
+{
+    constexpr int kWaves = 16;
+    __shared__ uint32_t kbuf[1024 * Items];
+    __shared__ uint16_t vbuf[1024 * Items];
+    __shared__ uint32_t wcnt[kWaves][kRadixBins];
+    __shared__ uint32_t wtot[4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int any = __syncthreads_or(tid < nflag && flag_part[tid] != 0u);
+    if (tid == 0) hflag[0] = any ? 1u : 0u;
+    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    const int base = wave * (64 * Items) + lane;
+    uint32_t key[Items];
+    uint32_t val[Items];
+#pragma unroll
+    for (int it = 0; it < Items; ++it) {
+        const int i = base + it * 64;
+        key[it] = i < n ? kin[i] : 0xffffffffu;
+        val[it] = (uint32_t)i;
+    }
+    for (int shift = 0; shift < key_bits; shift += kRadixBits) {
+        const int bits = min(kRadixBits, key_bits - shift);  // (no key has more)
+        for (int d = lane; d < kRadixBins; d += 64) wcnt[wave][d] = 0;
+        uint32_t at[Items];  // rank within the wave's keys of the same digit
+#pragma unroll
+        for (int it = 0; it < Items; ++it) {
+            const bool valid = base + it * 64 < n;  // (the invalid ones stay at the end)
+            const uint32_t d = (key[it] >> shift) & (kRadixBins - 1);
+            uint64_t same = __ballot(valid);
+            for (int b = 0; b < bits; ++b) {
+                const bool bit = (d >> b) & 1u;
+                const uint64_t ones = __ballot(bit);
+                same &= bit ? ones : ~ones;
+            }
+            const uint32_t rank = __popcll(same & lt);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            const uint32_t before = wcnt[wave][d];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (valid && rank == 0) wcnt[wave][d] = before + __popcll(same);
+            at[it] = before + rank;
+        }
+        __syncthreads();
+        // first position of each (digit, wave)
+        uint32_t run = 0, tot = 0;
+        if (tid < kRadixBins) {
+            for (int w = 0; w < kWaves; ++w) {
+                const uint32_t c = wcnt[w][tid];
+                wcnt[w][tid] = tot;
+                tot += c;
+            }
+            run = tot;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t t = __shfl_up(run, o, 64);
+                if (lane >= o) run += t;
+            }
+            if (lane == 63) wtot[wave] = run;
+        }
+        __syncthreads();
+        if (tid < kRadixBins) {
+            uint32_t first = run - tot;
+            for (int w = 0; w < wave; ++w) first += wtot[w];
+            for (int w = 0; w < kWaves; ++w) wcnt[w][tid] += first;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < Items; ++it) {
+            if (base + it * 64 < n) {
+                const uint32_t d = (key[it] >> shift) & (kRadixBins - 1);
+                const uint32_t pos = wcnt[wave][d] + at[it];
+                kbuf[pos] = key[it];
+                vbuf[pos] = (uint16_t)val[it];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < Items; ++it) {
+            const int i = base + it * 64;
+            if (i < n) {
+                key[it] = kbuf[i];
+                val[it] = vbuf[i];
+            }
+        }
+    }
+#pragma unroll
+    for (int it = 0; it < Items; ++it) {
+        const int i = base + it * 64;
+        if (i < n) {
+            kout[i] = key[it];
+            vout[i] = (int32_t)val[it];
+        }
+    }
+}
+
+// Per-tile digit histogram.
+template <int Threads, int Items>
+__global__ void __launch_bounds__(Threads)
 radix_hist_kernel(const uint32_t *__restrict__ keys, int64_t n, const int64_t *n_dev, int shift,
-                  uint32_t *__restrict__ hist, int64_t ntiles)
+                  uint32_t *__restrict__ hist, HistAt at)
 {
     __shared__ uint32_t cnt[kRadixBins];
     if (n_dev) n = *n_dev;
-    cnt[threadIdx.x] = 0;
+    const int tid = threadIdx.x;
+    const int64_t base = (int64_t)blockIdx.x * (Threads * Items);
+    if (base >= n && at.digit == 1) return;  // (the scatter skips these tiles)
+    if (tid < kRadixBins) cnt[tid] = 0;
     __syncthreads();
-    int64_t base = (int64_t)blockIdx.x * kSortTile;
 #pragma unroll
-    for (int it = 0; it < kSortItems; ++it) {
-        int64_t i = base + it * kSortThreads + threadIdx.x;
+    for (int it = 0; it < Items; ++it) {
+        const int64_t i = base + it * Threads + tid;
         if (i < n) atomicAdd(&cnt[(keys[i] >> shift) & (kRadixBins - 1)], 1u);
     }
     __syncthreads();
-    hist[(int64_t)threadIdx.x * ntiles + blockIdx.x] = cnt[threadIdx.x];
+    if (tid < kRadixBins) hist[at(tid, blockIdx.x)] = cnt[tid];
 }
 
 // Block-wide exclusive scan of one value per thread (256 threads, wave64).
@@ -183,61 +358,134 @@ scan_down_kernel(uint32_t *__restrict__ a, int64_t len,
     }
 }
 
-// Stable scatter of one radix pass. Elements of a tile are ranked in index
-// order: sub-tile by sub-tile, wave by wave, lane by lane. Lanes holding the
-// same digit are matched with one ballot per digit bit.
-__global__ void __launch_bounds__(kSortThreads)
+// Stable scatter of one radix pass. Each wave takes a contiguous run of the
+// tile's keys and ranks it 64 at a time (lanes holding the same digit are
+// matched with one ballot per digit bit) against its own digit counts, so the
+// index order within a digit is kept and the block meets only three times.
+// Self: hist holds the tiles' digit counts (tile-major), and the block adds them
+// up into the offsets it needs; else they have been scanned (digit-major). vin
+// null: the values are the indices. flag_part (not null): block 0 also reduces
+// the build's h flags into hflag.
+// A pass over 1M keys takes 18.5 us in 2 launches (33 in 5 with the scan), over
+// 104,000 12 us (28); a launch alone is 4.5.
+template <int Threads, int Items, bool Self>
+__global__ void __launch_bounds__(Threads)
 radix_scatter_kernel(const uint32_t *__restrict__ kin, const int32_t *__restrict__ vin,
-                     int64_t n, const int64_t *n_dev, int shift,
-                     const uint32_t *__restrict__ hist, int64_t ntiles,
-                     uint32_t *__restrict__ kout, int32_t *__restrict__ vout)
+                     int64_t n, const int64_t *n_dev, int shift, int bits,
+                     const uint32_t *__restrict__ hist, int64_t tiles,
+                     uint32_t *__restrict__ kout, int32_t *__restrict__ vout,
+                     const uint32_t *__restrict__ flag_part, uint32_t *__restrict__ hflag)
 {
     if (n_dev) n = *n_dev;
-    if ((int64_t)blockIdx.x * kSortTile >= n) return;
-    constexpr int kWaves = kSortThreads / 64;
-    __shared__ uint32_t base_of[kRadixBins];
-    __shared__ uint32_t run[kRadixBins];
+    const int64_t tile0 = (int64_t)blockIdx.x * (Threads * Items);
+    if (tile0 >= n) return;
+    constexpr int kWaves = Threads / 64;
     __shared__ uint32_t wcnt[kWaves][kRadixBins];
+    __shared__ uint32_t base[kRadixBins];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    base_of[tid] = hist[(int64_t)tid * ntiles + blockIdx.x];
-    run[tid] = 0;
+    if (flag_part && blockIdx.x == 0) {
+        bool f = false;
+        for (unsigned q = tid; q < gridDim.x; q += Threads) f |= flag_part[q] != 0u;
+        const int any = __syncthreads_or(f);
+        if (tid == 0) hflag[0] = any ? 1u : 0u;
+    }
+    // the keys and the offsets are under way together
+    const int64_t first = tile0 + (int64_t)wave * (64 * Items) + lane;
+    uint32_t key[Items];
+    int32_t val[Items];
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) wcnt[w][tid] = 0;
-    __syncthreads();
+    for (int it = 0; it < Items; ++it) {
+        const int64_t i = first + it * 64;
+        key[it] = i < n ? kin[i] : 0u;
+        val[it] = i < n ? (vin ? vin[i] : (int32_t)i) : 0;
+    }
+    if constexpr (Self) {
+        // every wave adds up its share of the tiles, four digits a lane
+        __shared__ uint32_t wbefore[kWaves][kRadixBins];
+        __shared__ uint32_t wsum[4];
+        const uint4 *row = reinterpret_cast<const uint4 *>(hist) + lane;
+        uint4 total = {0, 0, 0, 0}, before = {0, 0, 0, 0};
+        const int live = (int)((n + Threads * Items - 1) / (Threads * Items));
+#pragma unroll 8
+        for (int t = wave; t < live; t += kWaves) {
+            const uint4 c = row[t * (kRadixBins / 4)];
+            const uint32_t m = t < (int)blockIdx.x ? ~0u : 0u;
+            total.x += c.x;
+            total.y += c.y;
+            total.z += c.z;
+            total.w += c.w;
+            before.x += c.x & m;
+            before.y += c.y & m;
+            before.z += c.z & m;
+            before.w += c.w & m;
+        }
+        reinterpret_cast<uint4 *>(wcnt[wave])[lane] = total;
+        reinterpret_cast<uint4 *>(wbefore[wave])[lane] = before;
+        __syncthreads();
+        uint32_t sum = 0, off = 0, run = 0;
+        if (tid < kRadixBins) {
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                sum += wcnt[w][tid];
+                off += wbefore[w][tid];
+                wcnt[w][tid] = 0;
+            }
+            run = sum;  // inclusive sum over the digits
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t v = __shfl_up(run, o, 64);
+                if (lane >= o) run += v;
+            }
+            if (lane == 63) wsum[wave] = run;
+        }
+        __syncthreads();
+        if (tid < kRadixBins) {
+            off += run - sum;
+            for (int w = 0; w < wave; ++w) off += wsum[w];
+            base[tid] = off;
+        }
+    } else {
+        for (int d = lane; d < kRadixBins; d += 64) wcnt[wave][d] = 0;
+        if (tid < kRadixBins) base[tid] = hist[(int64_t)tid * tiles + blockIdx.x];
+    }
     const uint64_t lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-    const int64_t tile0 = (int64_t)blockIdx.x * kSortTile;
-    for (int it = 0; it < kSortItems; ++it) {
-        const int64_t i = tile0 + it * kSortThreads + tid;
-        const bool valid = i < n;
-        const uint32_t k = valid ? kin[i] : 0u;
-        const int32_t v = valid ? vin[i] : 0;
-        const uint32_t d = (k >> shift) & (kRadixBins - 1);
-        uint64_t same = __ballot(valid);
+    uint32_t at[Items];  // rank within the wave's keys of the same digit
 #pragma unroll
-        for (int b = 0; b < kRadixBits; ++b) {
+    for (int it = 0; it < Items; ++it) {
+        const bool valid = first + it * 64 < n;
+        const uint32_t d = (key[it] >> shift) & (kRadixBins - 1);
+        uint64_t same = __ballot(valid);
+        for (int b = 0; b < bits; ++b) {
             const bool bit = (d >> b) & 1u;
             const uint64_t ones = __ballot(bit);
             same &= bit ? ones : ~ones;
         }
         const uint32_t rank = __popcll(same & lt_mask);
-        if (valid && rank == 0) wcnt[wave][d] = __popcll(same);
-        __syncthreads();
-        if (valid) {
-            uint32_t off = run[d];
-            for (int w = 0; w < wave; ++w) off += wcnt[w][d];
-            const uint32_t pos = base_of[d] + off + rank;
-            kout[pos] = k;
-            vout[pos] = v;
-        }
-        __syncthreads();
-        uint32_t tot = 0;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const uint32_t before = wcnt[wave][d];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (valid && rank == 0) wcnt[wave][d] = before + __popcll(same);
+        at[it] = before + rank;
+    }
+    __syncthreads();
+    // first position of each (digit, wave)
+    if (tid < kRadixBins) {
+        uint32_t run = base[tid];
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) {
-            tot += wcnt[w][tid];
-            wcnt[w][tid] = 0;
+            const uint32_t c = wcnt[w][tid];
+            wcnt[w][tid] = run;
+            run += c;
         }
-        run[tid] += tot;
-        __syncthreads();
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < Items; ++it) {
+        if (first + it * 64 < n) {
+            const uint32_t pos = wcnt[wave][(key[it] >> shift) & (kRadixBins - 1)] + at[it];
+            kout[pos] = key[it];
+            vout[pos] = val[it];
+        }
     }
 }
 
@@ -279,61 +527,59 @@ permute_store_kernel(int64_t n, const int64_t *n_dev, int64_t stride, PermFields
     }
 }
 
-// Cell table by binary search of each cell's key range (all its slices) in
-// the sorted keys: every entry is rewritten on every build, empty cells get
-// start == end. Also clears the cell's largest (2h)^2.
+// Last kernel of a build: gathers every field from the scratch rows into the
+// caller's arrays in cell order, writes the search records (position and
+// (2h)^2) and the cell table (a particle whose predecessor lies in another cell
+// ends that one and starts its own; cells without particles stay empty). With
+// varying h also each cell's largest (2h)^2, as the ordered bit pattern of a
+// positive double: a segmented maximum over the wave's lanes (a cell's
+// particles are consecutive), then one atomic per cell and wave.
 __global__ void __launch_bounds__(256)
-cell_table_kernel(int64_t ncell, Grid g, const uint32_t *__restrict__ keys, int64_t n,
+build_tail_kernel(int64_t n, const int32_t *__restrict__ perm, const uint32_t *__restrict__ keys,
+                  BuildArrays A, Grid g, SearchRec *__restrict__ srec,
                   int32_t *__restrict__ cstart, int32_t *__restrict__ cend,
-                  unsigned long long *__restrict__ s2max)
-{
-    int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= ncell) return;
-    const uint32_t cx = (uint32_t)(c % g.nc[0]);
-    const uint32_t cy = (uint32_t)((c / g.nc[0]) % g.nc[1]);
-    const uint32_t cz = (uint32_t)(c / ((int64_t)g.nc[0] * g.nc[1]));
-    const uint32_t key = (spread3(cx) | (spread3(cy) << 1) | (spread3(cz) << 2)) << g.zbits;
-    const uint32_t last = key | ((1u << g.zbits) - 1u);
-    int64_t lo = 0, hi = n;
-    while (lo < hi) {   // first index with keys[i] >= key
-        int64_t mid = (lo + hi) >> 1;
-        if (keys[mid] < key) lo = mid + 1; else hi = mid;
-    }
-    const int64_t s = lo;
-    hi = n;
-    while (lo < hi) {   // first index with keys[i] > last
-        int64_t mid = (lo + hi) >> 1;
-        if (keys[mid] <= last) lo = mid + 1; else hi = mid;
-    }
-    cstart[c] = (int32_t)s;
-    cend[c] = (int32_t)lo;
-    s2max[c] = 0ull;
-}
-
-// Largest (2h)^2 of each cell, as the ordered bit pattern of a positive
-// double: a segmented maximum over the wave's lanes (a cell's particles are
-// consecutive), then one atomic per cell and wave.
-__global__ void __launch_bounds__(256)
-cell_s2max_kernel(int64_t n, Grid g, const uint32_t *__restrict__ keys,
-                  const SearchRec *__restrict__ srec, unsigned long long *__restrict__ s2max)
+                  const uint32_t *__restrict__ hflag, unsigned long long *__restrict__ s2max)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int lane = threadIdx.x & 63;
     const bool active = i < n;
-    const uint32_t ck = active ? keys[i] >> g.zbits : 0xFFFFFFFFu;
-    unsigned long long v = active ? (unsigned long long)__double_as_longlong(srec[i].s2) : 0ull;
+    const int64_t at = active ? i : n - 1;
+    const int64_t j = perm[at];
+    const uint32_t ck = keys[at] >> g.zbits;
+    double w[kPermFields];
+#pragma unroll
+    for (int k = 0; k < kPermFields; ++k)
+        if (k < A.f.nf) w[k] = A.tmp[k * A.stride + j];
+    const int32_t id = A.tmp_id[j];
+    const double s = 2.0 * A.tmp[A.h * A.stride + j];
+    const double s2 = s * s;
+    auto cell = [&](uint32_t c) -> int64_t {
+        return ((int64_t)compact3(c >> 2) * g.nc[1] + compact3(c >> 1)) * g.nc[0] + compact3(c);
+    };
+    if (active) {
+#pragma unroll
+        for (int k = 0; k < kPermFields; ++k)
+            if (k < A.f.nf) A.f.f[k][i] = w[k];
+        A.f.id[i] = id;
+        srec[i] = SearchRec{w[0], w[1], w[2], s2};
+        const uint32_t pk = i > 0 ? keys[i - 1] >> g.zbits : 0u;
+        if (i == 0 || pk != ck) {
+            cstart[cell(ck)] = (int32_t)i;
+            if (i > 0) cend[cell(pk)] = (int32_t)i;
+        }
+        if (i == n - 1) cend[cell(ck)] = (int32_t)n;
+    }
+    if (hflag[0] == 0u) return;  // uniform h: not read
+    const uint32_t gk = active ? ck : 0xFFFFFFFFu;
+    unsigned long long v = active ? (unsigned long long)__double_as_longlong(s2) : 0ull;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
         const unsigned long long t = __shfl_down(v, o, 64);
-        const uint32_t tk = __shfl_down(ck, o, 64);
-        if (lane + o < 64 && tk == ck) v = t > v ? t : v;
+        const uint32_t tk = __shfl_down(gk, o, 64);
+        if (lane + o < 64 && tk == gk) v = t > v ? t : v;
     }
-    const uint32_t pk = __shfl_up(ck, 1, 64);
-    if (active && (lane == 0 || pk != ck)) {
-        const int64_t cell = ((int64_t)compact3(ck >> 2) * g.nc[1] + compact3(ck >> 1)) * g.nc[0] +
-                             compact3(ck);
-        atomicMax(&s2max[cell], v);
-    }
+    const uint32_t pk = __shfl_up(gk, 1, 64);
+    if (active && (lane == 0 || pk != gk)) atomicMax(&s2max[cell(ck)], v);
 }
 
 // ---------------------------------------------------------------------------
@@ -360,7 +606,7 @@ admit_kernel(BatchDev b)
 __global__ void __launch_bounds__(256)
 keys_batch_kernel(BatchDev b, const double *__restrict__ x, const double *__restrict__ y,
                   const double *__restrict__ z, const double *__restrict__ h,
-                  uint32_t *__restrict__ keys, int32_t *__restrict__ vals)
+                  uint32_t *__restrict__ keys)
 {
     const int64_t n = b.hdr->n_in;
     const int64_t step = (int64_t)gridDim.x * blockDim.x;
@@ -380,7 +626,6 @@ keys_batch_kernel(BatchDev b, const double *__restrict__ x, const double *__rest
             if (!(h[i] <= r.h_max)) atomicOr(&b.status[s], ST_DOMAIN);
         }
         keys[i] = key;
-        vals[i] = (int32_t)i;
     }
 }
 
@@ -438,79 +683,162 @@ hipError_t exclusive_scan(sph_ctx ctx, uint32_t *a, int64_t len)
     return hipGetLastError();
 }
 
-}  // namespace
+// Tiles of a sort of up to n keys: the smallest of 256 x 2, 256 x 4, 512 x 4 and
+// 1024 x 4 keys (threads x keys of one) that give at most kSortSelfTiles of
+// them, as small tiles keep more of the chip busy; the largest beyond.
+struct SortPlan {
+    int tile;
+    int64_t tiles;
+    bool self;
+    HistAt at() const { return self ? HistAt{1, kRadixBins} : HistAt{tiles, 1}; }
+};
 
-hipError_t radix_sort_pairs(sph_ctx ctx, uint32_t *k[2], int32_t *v[2], int64_t n,
-                            int key_bits, int *cur)
+SortPlan sort_plan(int64_t n)
+{
+    SortPlan p{kSortTileMin, 0, true};
+    while ((p.tiles = (n + p.tile - 1) / p.tile) > kSortSelfTiles && p.tile < kSortTile)
+        p.tile *= 2;
+    p.self = p.tiles <= kSortSelfTiles;
+    return p;
+}
+
+// CALL(threads, items) for a plan's tile
+#define SPH_SORT_TILE(tile, CALL)                                                          \
+    do {                                                                                   \
+        switch (tile) {                                                                    \
+        case 512: CALL(256, 2); break;                                                     \
+        case 1024: CALL(256, 4); break;                                                    \
+        case 2048: CALL(512, 4); break;                                                    \
+        default: CALL(1024, 4); break;                                                     \
+        }                                                                                  \
+    } while (0)
+
+// The passes over key_bits bits, from k[*cur], v[*cur]. identity: the first
+// pass's values are the indices; counted: its digit counts are in the
+// histogram already; flags: it also reduces the build's h flags.
+hipError_t sort_passes(sph_ctx ctx, uint32_t *const k[2], int32_t *const v[2], int64_t n,
+                       const int64_t *n_dev, int key_bits, const SortPlan &sp, bool identity,
+                       bool counted, bool flags, int *cur)
 {
     hipStream_t s = ctx->stream;
-    const int64_t ntiles = (n + kSortTile - 1) / kSortTile;
+    const unsigned nb = (unsigned)sp.tiles;
     hipError_t e;
     for (int shift = 0; shift < key_bits; shift += kRadixBits) {
-        radix_hist_kernel<<<(unsigned)ntiles, kSortThreads, 0, s>>>(k[*cur], n, nullptr, shift,
-                                                                     ctx->hist, ntiles);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        if ((e = exclusive_scan(ctx, ctx->hist, ntiles * kRadixBins)) != hipSuccess) return e;
-        radix_scatter_kernel<<<(unsigned)ntiles, kSortThreads, 0, s>>>(
-            k[*cur], v[*cur], n, nullptr, shift, ctx->hist, ntiles, k[*cur ^ 1], v[*cur ^ 1]);
+        const bool head = shift == 0;
+        const int bits = std::min(kRadixBits, key_bits - shift);
+        if (!(head && counted)) {
+#define SPH_HIST(T, I)                                                                     \
+    radix_hist_kernel<T, I><<<nb, T, 0, s>>>(k[*cur], n, n_dev, shift, ctx->hist, sp.at())
+            SPH_SORT_TILE(sp.tile, SPH_HIST);
+#undef SPH_HIST
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+        }
+        const int32_t *vin = head && identity ? nullptr : v[*cur];
+        const uint32_t *fp = head && flags ? ctx->flag_part : nullptr;
+        if (sp.self) {
+#define SPH_SCATTER(T, I)                                                                  \
+    radix_scatter_kernel<T, I, true><<<nb, T, 0, s>>>(                                     \
+        k[*cur], vin, n, n_dev, shift, bits, ctx->hist, sp.tiles, k[*cur ^ 1],             \
+        v[*cur ^ 1], fp, ctx->hflag_dev)
+            SPH_SORT_TILE(sp.tile, SPH_SCATTER);
+#undef SPH_SCATTER
+        } else {
+            if ((e = exclusive_scan(ctx, ctx->hist, sp.tiles * kRadixBins)) != hipSuccess)
+                return e;
+            radix_scatter_kernel<1024, 4, false><<<nb, 1024, 0, s>>>(
+                k[*cur], vin, n, n_dev, shift, bits, ctx->hist, sp.tiles, k[*cur ^ 1],
+                v[*cur ^ 1], fp, ctx->hflag_dev);
+        }
         if ((e = hipGetLastError()) != hipSuccess) return e;
         *cur ^= 1;
     }
     return hipSuccess;
 }
 
+}  // namespace
+
+hipError_t radix_sort_pairs(sph_ctx ctx, uint32_t *k[2], int32_t *v[2], int64_t n,
+                            int key_bits, int *cur)
+{
+    return sort_passes(ctx, k, v, n, nullptr, key_bits, sort_plan(n), false, false, false, cur);
+}
+
+// A build is: the head kernel (scratch copies, keys, first digit counts), the
+// sort (one block for a small run, else count and scatter per 8 bits), and the
+// tail kernel (gather, search records, cell table). Bound by launches up to
+// 100,000 particles (no kernel is under 4.5 us here) and by the two passes over
+// the state, 92 B each way a particle, beyond. 21 launches before: 8,000
+// particles 101 -> 31 us in 3, 104,000 127 -> 49 us in 7, 1M 234 -> 143 us in 7
+// (the drift included).
 hipError_t launch_build_cells(sph_ctx ctx, const sph_particles &p, const Grid &g,
-                              double h_max, double *const *extra, int n_extra)
+                              double h_max, double *const *extra, int n_extra,
+                              const KickDrift &kd)
 {
     const int64_t n = p.n;
     hipStream_t s = ctx->stream;
     const int64_t ncell = (int64_t)g.nc[0] * g.nc[1] * g.nc[2];
-    clear_word_kernel<<<1, 1, 0, s>>>(ctx->hflag_dev);
-    keys_kernel<<<blocks_for(n, 256), 256, 0, s>>>(n, p.x, p.y, p.z, p.h, g, h_max,
-                                                   ctx->keys[0], ctx->vals[0], ctx->hflag_dev,
-                                                   ctx->status_dev);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int key_bits = 3 * g.bits + g.zbits;
-    const int64_t ntiles = (n + kSortTile - 1) / kSortTile;
-    int cur = 0;
-    for (int shift = 0; shift < key_bits; shift += kRadixBits) {
-        radix_hist_kernel<<<(unsigned)ntiles, kSortThreads, 0, s>>>(
-            ctx->keys[cur], n, nullptr, shift, ctx->hist, ntiles);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        if ((e = exclusive_scan(ctx, ctx->hist, ntiles * kRadixBins)) != hipSuccess) return e;
-        radix_scatter_kernel<<<(unsigned)ntiles, kSortThreads, 0, s>>>(
-            ctx->keys[cur], ctx->vals[cur], n, nullptr, shift, ctx->hist, ntiles,
-            ctx->keys[cur ^ 1], ctx->vals[cur ^ 1]);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        cur ^= 1;
-    }
-    ctx->sorted_keys = ctx->keys[cur];
-
-    PermFields f{};
+    BuildArrays A{};
     double *fields[kPermFields] = {p.x, p.y, p.z, p.vx, p.vy, p.vz, p.u, p.h, p.m,
                                    p.rho_ref, p.p_bg, p.gx, p.gy, p.gz, p.xw};
     for (int k = 0; k < n_extra && 15 + k < kPermFields; ++k) fields[15 + k] = extra[k];
-    int h_field = -1;
+    A.h = A.g = -1;
     for (int k = 0; k < kPermFields; ++k) {
         if (!fields[k]) continue;
-        if (k == 7) h_field = f.nf;
-        f.f[f.nf++] = fields[k];
+        if (k == 7) A.h = A.f.nf;
+        if (k == 11) A.g = A.f.nf;
+        A.f.f[A.f.nf++] = fields[k];
     }
-    f.id = p.id;
-    permute_gather_kernel<<<blocks_for(n, 256), 256, 0, s>>>(n, nullptr, ctx->n_max,
-                                                             ctx->vals[cur], f, ctx->perm_tmp,
-                                                             ctx->perm_tmp_id, nullptr);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    permute_store_kernel<<<blocks_for(n, 256), 256, 0, s>>>(n, nullptr, ctx->n_max, f,
-                                                            ctx->perm_tmp, ctx->perm_tmp_id,
-                                                            nullptr, h_field, ctx->srec);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    A.f.id = p.id;
+    A.tmp = ctx->perm_tmp;
+    A.stride = ctx->n_max;
+    A.tmp_id = ctx->perm_tmp_id;
     unsigned long long *s2max = reinterpret_cast<unsigned long long *>(ctx->cell_s2max);
-    cell_table_kernel<<<blocks_for(ncell, 256), 256, 0, s>>>(ncell, g, ctx->sorted_keys, n,
-                                                             ctx->cell_start, ctx->cell_end, s2max);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    cell_s2max_kernel<<<blocks_for(n, 256), 256, 0, s>>>(n, g, ctx->sorted_keys, ctx->srec, s2max);
+    const int key_bits = std::max(1, 3 * g.bits + g.zbits);
+    const bool small = n <= kSortSmall;
+    const SortPlan sp = sort_plan(n);
+    uint32_t *hist = small ? nullptr : ctx->hist;
+    unsigned nb = (unsigned)sp.tiles;
+#define SPH_HEAD_D(D, T, I)                                                                \
+    build_head_kernel<D, T, I><<<nb, T, 0, s>>>(n, A, g, h_max, kd, ctx->keys[0], hist,    \
+                                                sp.at(), ctx->flag_part,                   \
+                                                ctx->status_dev, ncell, ctx->cell_start,   \
+                                                ctx->cell_end, s2max)
+#define SPH_HEAD(T, I)                                                                     \
+    do {                                                                                   \
+        if (kd.dt_dev) SPH_HEAD_D(true, T, I);                                             \
+        else SPH_HEAD_D(false, T, I);                                                      \
+    } while (0)
+    if (small) {
+        nb = (unsigned)blocks_for(n, 256);
+        SPH_HEAD(256, 1);
+    } else {
+        SPH_SORT_TILE(sp.tile, SPH_HEAD);
+    }
+#undef SPH_HEAD_D
+#undef SPH_HEAD
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    int cur = 0;
+    if (small) {
+#define SPH_SMALL(I)                                                                       \
+    sort_small_kernel<I><<<1, 1024, 0, s>>>((int)n, key_bits, ctx->keys[0], ctx->keys[1],  \
+                                            ctx->vals[1], (int)nb, ctx->flag_part,   \
+                                            ctx->hflag_dev)
+        if (n <= 2 * 1024) SPH_SMALL(2);
+        else if (n <= 4 * 1024) SPH_SMALL(4);
+        else if (n <= 8 * 1024) SPH_SMALL(8);
+        else SPH_SMALL(12);
+#undef SPH_SMALL
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        cur = 1;
+    } else if ((e = sort_passes(ctx, ctx->keys, ctx->vals, n, nullptr, key_bits, sp, true, true,
+                                true, &cur)) != hipSuccess) {
+        return e;
+    }
+    ctx->sorted_keys = ctx->keys[cur];
+    build_tail_kernel<<<blocks_for(n, 256), 256, 0, s>>>(n, ctx->vals[cur], ctx->sorted_keys, A, g,
+                                                         ctx->srec, ctx->cell_start,
+                                                         ctx->cell_end, ctx->hflag_dev, s2max);
     return hipGetLastError();
 }
 
@@ -553,22 +881,13 @@ hipError_t launch_build_cells_batch(sph_ctx ctx, const BatchDev &b, double *F, i
     const unsigned grid = std::min<unsigned>(blocks_for(cap, 256), 4096u);
     const int64_t *n_in = &b.hdr->n_in;
     keys_batch_kernel<<<grid, 256, 0, s>>>(b, F + 0 * cap, F + 1 * cap, F + 2 * cap,
-                                           F + 7 * cap, ctx->keys[0], ctx->vals[0]);
+                                           F + 7 * cap, ctx->keys[0]);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int64_t ntiles = (cap + kSortTile - 1) / kSortTile;
     int cur = 0;
-    for (int shift = 0; shift < kEnsKeyBits; shift += kRadixBits) {
-        radix_hist_kernel<<<(unsigned)ntiles, kSortThreads, 0, s>>>(
-            ctx->keys[cur], cap, n_in, shift, ctx->hist, ntiles);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        if ((e = exclusive_scan(ctx, ctx->hist, ntiles * kRadixBins)) != hipSuccess) return e;
-        radix_scatter_kernel<<<(unsigned)ntiles, kSortThreads, 0, s>>>(
-            ctx->keys[cur], ctx->vals[cur], cap, n_in, shift, ctx->hist, ntiles,
-            ctx->keys[cur ^ 1], ctx->vals[cur ^ 1]);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        cur ^= 1;
-    }
+    if ((e = sort_passes(ctx, ctx->keys, ctx->vals, cap, n_in, kEnsKeyBits, sort_plan(cap), true,
+                         false, false, &cur)) != hipSuccess)
+        return e;
     ctx->sorted_keys = ctx->keys[cur];
     PermFields f{};
     for (int k = 0; k < kEnsFields; ++k) f.f[f.nf++] = F + k * cap;

@@ -220,7 +220,7 @@ int64_t arena_bytes_per_particle(int max_nb)
                           + 4 + 4 * max_nb    // count, idx
                           + 3 * 4;            // id, slot, slot_tmp
     const int64_t scratch = 2 * 4 + 2 * 4     // keys, vals (double-buffered)
-                            + 1               // sort histograms (256 / 2048 * 4)
+                            + 2               // sort histograms (256 / 512 * 4)
                             + 1               // cell table (cap / 8 cells * 8 B)
                             + 32 + 32 + 128   // search, density, pair records
                             + kPermFields * 8 + 4;  // reorder scratch

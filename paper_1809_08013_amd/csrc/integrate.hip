@@ -30,27 +30,21 @@ integrate_kernel(int64_t n, int stage, const double *__restrict__ dt_dev, Grid g
         ty += gy[i];
         tz += gz[i];
     }
-    const double nvx = vx[i] + half * tx;
-    const double nvy = vy[i] + half * ty;
-    const double nvz = vz[i] + half * tz;
-    const double nu = u[i] + half * dudt[i];
-    vx[i] = nvx;
-    vy[i] = nvy;
-    vz[i] = nvz;
+    const double t[3] = {tx, ty, tz};
+    double v[3] = {vx[i], vy[i], vz[i]}, nu = u[i];
+    half_kick(half, t, dudt[i], v, nu);
+    vx[i] = v[0];
+    vy[i] = v[1];
+    vz[i] = v[2];
     u[i] = nu;
     if (stage == SPH_KICK_DRIFT) {
-        double p[3] = {x[i] + dt * nvx, y[i] + dt * nvy, z[i] + dt * nvz};
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            if (!g.periodic[a]) continue;
-            if (p[a] >= g.hi[a]) p[a] -= g.len[a];
-            else if (p[a] < g.lo[a]) p[a] += g.len[a];
-        }
+        double p[3] = {x[i], y[i], z[i]};
+        drift(dt, g, v, p);
         x[i] = p[0];
         y[i] = p[1];
         z[i] = p[2];
     } else {
-        const double s = x[i] + y[i] + z[i] + nvx + nvy + nvz + nu;
+        const double s = x[i] + y[i] + z[i] + v[0] + v[1] + v[2] + nu;
         if (!isfinite(s)) atomicOr(status, ST_NONFINITE);
     }
 }

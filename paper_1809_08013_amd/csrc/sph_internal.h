@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -22,9 +23,20 @@ enum : uint32_t {
 constexpr int kMaxAxisCells = 1024;   // 10 Morton bits per axis
 constexpr int kRadixBits = 8;
 constexpr int kRadixBins = 1 << kRadixBits;
-constexpr int kSortThreads = 256;
-constexpr int kSortItems = 8;
-constexpr int kSortTile = kSortThreads * kSortItems;   // keys per tile
+constexpr int kSortTile = 4096;                        // keys per tile, at most
+// Up to this many tiles, every scatter block works its offsets out from the
+// tiles' digit counts itself; beyond, a scan over all of them does (3 launches).
+constexpr int kSortSelfTiles = 256;
+// Up to this many keys, one block sorts them all in LDS.
+constexpr int kSortSmall = 12 * 1024;
+constexpr int kSortTileMin = 512;                      // keys per tile of the smallest sorts
+// Most tiles of a sort of up to n keys (the fewest keys for which the tiles are
+// not yet doubled have the most); each has a count of every digit.
+inline int64_t sort_tiles_max(int64_t n)
+{
+    auto tiles = [&](int64_t tile) { return (n + tile - 1) / tile; };
+    return std::max(std::min<int64_t>(kSortSelfTiles, tiles(kSortTileMin)), tiles(kSortTile));
+}
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 16;
 constexpr int kScanChunk = kScanThreads * kScanItems;  // elements per block
@@ -188,6 +200,29 @@ __device__ __forceinline__ bool step_closes(const StepMask &m, int64_t i)
     return ((m.sub + 1) & ((1 << (m.B - b)) - 1)) == 0;
 }
 
+// One half of a kick-drift-kick step: v += dt/2 (a + g), u += dt/2 du/dt, and
+// (KICK_DRIFT) x += dt v with periodic coordinates wrapped into [lo, hi). The
+// position and v, u of one particle are updated in place.
+__device__ __forceinline__ void half_kick(double half, const double (&t)[3], double du,
+                                          double (&v)[3], double &u)
+{
+    v[0] = v[0] + half * t[0];
+    v[1] = v[1] + half * t[1];
+    v[2] = v[2] + half * t[2];
+    u = u + half * du;
+}
+__device__ __forceinline__ void drift(double dt, const Grid &g, const double (&v)[3],
+                                      double (&p)[3])
+{
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        p[a] = p[a] + dt * v[a];
+        if (!g.periodic[a]) continue;
+        if (p[a] >= g.hi[a]) p[a] -= g.len[a];
+        else if (p[a] < g.lo[a]) p[a] += g.len[a];
+    }
+}
+
 // Block index remapped so that each XCD runs one contiguous range of blocks.
 // Blocks are dispatched to the 8 XCDs round-robin (block b to XCD b % 8);
 // giving XCD x the x-th contiguous slice keeps a Morton-contiguous region of
@@ -295,8 +330,8 @@ struct sph_ctx_s {
     int32_t *vals[2] = {nullptr, nullptr};
     uint32_t *hist = nullptr;        // kRadixBins * tiles_max
     uint32_t *scan_part = nullptr;   // block partials of the scan
-    int64_t tiles_max = 0;
     int64_t scan_len_max = 0;
+    uint32_t *flag_part = nullptr;   // per block of the build's first kernel: some h differs
     const uint32_t *sorted_keys = nullptr;  // key of each particle after the build
 
     // cell table, indexed by linear cell id (cz * ny + cy) * nx + cx
@@ -360,8 +395,15 @@ namespace sph {
 // Launchers (defined in the .hip files); each returns hipSuccess or the
 // launch error.
 // extra: up to 10 more per-particle FP64 arrays reordered with the particles.
+// kd: the particles take a kick-drift with the dt in device memory first
+// (sph_integrate(SPH_KICK_DRIFT), in the build's first kernel).
+struct KickDrift {
+    const double *dt_dev = nullptr;
+    const double *ax = nullptr, *ay = nullptr, *az = nullptr, *dudt = nullptr;
+};
 hipError_t launch_build_cells(sph_ctx ctx, const sph_particles &p, const Grid &g,
-                              double h_max, double *const *extra = nullptr, int n_extra = 0);
+                              double h_max, double *const *extra = nullptr, int n_extra = 0,
+                              const KickDrift &kd = KickDrift{});
 hipError_t launch_find_neighbors(sph_ctx ctx, const sph_particles &p,
                                  const sph_nbrs &nb, const StepMask &mask = StepMask{});
 // The interpolation kernel of a pair call: family (SPH_KERNEL_*), sinc

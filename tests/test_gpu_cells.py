@@ -1,0 +1,99 @@
+"""The cell build at the edges of its sorts: one block, tiles of every size,
+and more tiles than a block adds up by itself."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_1809_08013_amd import inputs as I  # noqa: E402
+from paper_1809_08013_amd import sph as S  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+KEYS = ["x", "y", "z", "vx", "vy", "vz", "u", "h", "m", "rho_ref", "p_bg"]
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _device():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    S.load()
+    torch.cuda.set_device(0)
+
+
+def _sites(n, spread):
+    """n particles on about n / 4 lattice sites further apart than 2 h, in
+    random order: a particle's neighbours are the others of its site."""
+    rng = np.random.default_rng(n)
+    side = max(1, round((n / 4) ** (1 / 3)))
+    ic = I.random_cloud(n, seed=n, h_min=0.2 / side, h_max=0.2 / side)
+    site = rng.integers(0, side ** 3, n)
+    for a, k in enumerate("xyz"):
+        getattr(ic, k)[:] = ((site // side ** a) % side + 0.5) / side
+    ic.h[:] = (0.2 / side) * (1.0 - spread * rng.random(side ** 3)[site])
+    return ic, site
+
+
+# one block of 1024 keys times 2, 4, 8 and 12; tiles of 512, 1024, 2048 and
+# 4096 keys (256 of each); more tiles
+SIZES = [1, 2, 255, 256, 257, 2048, 2049, 4097, 8193, 12287, 12288, 12289,
+         131072, 131073, 262144, 262145, 524288, 524289, 1048576, 1048577, 1100000]
+
+
+@pytest.mark.parametrize("n", SIZES)
+@pytest.mark.parametrize("spread", [0.0, 0.5])
+def test_order_and_table(n, spread):
+    ic, site = _sites(n, spread)
+    before = {k: np.array(a) for k, a in ic.arrays().items() if k in KEYS}
+    before["rho_ref"] = np.arange(n, dtype=np.float64)
+    print(f"cells n={n} spread={spread}", flush=True)
+    ctx = S.Context(n, 32)
+    st = S.SphState(ic, 32, rho_ref=before["rho_ref"])
+    S.sph_build_cells(ctx, st)
+    S.sph_find_neighbors(ctx, st)
+    S.sph_ctx_check(ctx)
+    got = st.host(KEYS + ["id", "count"], original_order=False)
+    ids = got["id"]
+    assert np.array_equal(np.sort(ids), np.arange(n))
+    for k in KEYS:  # every field moved with its particle
+        assert np.array_equal(got[k], before[k][ids]), k
+    # stable: the particles of a site (equal keys) keep their order
+    by_site = np.argsort(site[ids], kind="stable")
+    same = np.diff(site[ids][by_site]) == 0
+    assert (np.diff(ids[by_site])[same] > 0).all()
+    # the table finds every particle of the site
+    assert np.array_equal(got["count"], np.bincount(site)[site[ids]] - 1)
+
+
+@pytest.mark.parametrize("n_side,nz,gravity", [(8, 16, False), (20, 20, True), (24, 24, False),
+                                                (52, 52, True)])
+def test_step_is_its_parts(n_side, nz, gravity):
+    """One call of a step equals the calls it is made of, bit for bit."""
+    ic = I.square_patch(n_side, nz=nz)
+    rng = np.random.default_rng(n_side)
+    g = [rng.standard_normal(ic.n) for _ in range(3)] if gravity else None
+    prm = S.make_params(ic.params)
+    out = []
+    print(f"step n={ic.n} gravity={gravity}", flush=True)
+    for parts in (False, True):
+        ctx = S.Context(ic.n, 256)
+        st = S.SphState(ic, 256, g=g)
+        S.sph_init_forces(ctx, st, prm)
+        for _ in range(3):
+            if parts:
+                S.sph_integrate(ctx, st, S.SPH_KICK_DRIFT)
+                S.sph_build_cells(ctx, st)
+                S.sph_find_neighbors(ctx, st)
+                S.sph_density(ctx, st, prm)
+                S.sph_eos(ctx, st, prm)
+                S.sph_momentum_energy(ctx, st, prm)
+                S.sph_integrate(ctx, st, S.SPH_KICK)
+                S.sph_timestep(ctx, st, prm)
+            else:
+                S.sph_step(ctx, st, prm)
+        S.sph_ctx_check(ctx)
+        o = st.host(original_order=False)
+        o["dt"], o["diag"] = st.dt, st.diag
+        out.append(o)
+    for k in out[0]:
+        assert np.array_equal(out[0][k], out[1][k], equal_nan=True), k
