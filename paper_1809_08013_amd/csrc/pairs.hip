@@ -22,6 +22,7 @@
 #include <algorithm>
 #include <mutex>
 #include <type_traits>
+#include <utility>
 
 #include "sph_internal.h"
 
@@ -219,9 +220,10 @@ __device__ __forceinline__ int run_slot(const BatchDev &b, int64_t ii)
 }
 
 // First particle of the calling lane and end of its wave's particles. One
-// run: blocks of kThreads consecutive particles (wave w of block `tile`
-// takes its 64). Ensemble: `tile` is the wave's 64-particle tile of one run.
-template <bool Multi>
+// run: blocks of kThreads / S consecutive particles (wave w of block `tile`
+// takes its 64 / S, lanes S p .. S p + S - 1 the p-th). Ensemble: `tile` is the
+// wave's 64-particle tile of one run.
+template <bool Multi, int S>
 __device__ __forceinline__ void lane_span(int64_t tile, int64_t n, const BatchDev &b,
                                           int64_t &i, int64_t &end)
 {
@@ -230,9 +232,53 @@ __device__ __forceinline__ void lane_span(int64_t tile, int64_t n, const BatchDe
         tile_span<true>(tile, n, b, t0, end);
         i = t0 + (threadIdx.x & 63);
     } else {
-        i = tile * kThreads + threadIdx.x;
+        i = tile * (kThreads / S) + threadIdx.x / S;
         end = n;
     }
+}
+
+// Small runs leave most of the chip idle at one lane per particle, and a wave's
+// time is then its steps one after the other (8,000 particles: 125 waves on
+// 1,024 SIMDs, 0.5 us a step). There S = 4 or 16 lanes share a particle: lane s
+// takes list entries s, s + S, ... , and after every step the terms of the S
+// lanes are broadcast and added in list order by all of them, so the sums are bit
+// for bit those of one lane (and of the ensemble's kernels, which stay at one
+// lane per particle).
+// Density + momentum kernel at 1, 4 and 16 lanes (116 neighbours): FP64 8,000
+// particles 100, 41, 30 us; 15,600: 101, 43, 46; 64,000: 112, 92, 148; 91,000:
+// 147, 123, 203; 125,000: 154, 164, 281. FP32-pair 64,000: 93, 77, 132; 91,000:
+// 139, 110, 175; 125,000: 146, 145, 246.
+constexpr int64_t kSplit16Max = 12288, kSplit4Max = 114688;
+
+// v of lane L of the calling lane's S lanes (a quad, or a row of 16).
+template <int S, int L>
+__device__ __forceinline__ int split_lane(int v)
+{
+    constexpr int kCtrl = S == 4 ? L * 0x55 : 0x150 + L;  // quad_perm, row_newbcast
+    return __builtin_amdgcn_update_dpp(0, v, kCtrl, 0xf, 0xf, true);
+}
+template <int S, int L>
+__device__ __forceinline__ float split_lane(float v)
+{
+    return __int_as_float(split_lane<S, L>(__float_as_int(v)));
+}
+template <int S, int L>
+__device__ __forceinline__ double split_lane(double v)
+{
+    if constexpr (S == 16) {
+        return __longlong_as_double(__builtin_amdgcn_update_dpp(
+            0l, (long)__double_as_longlong(v), 0x150 + L, 0xf, 0xf, true));
+    } else {
+        return __hiloint2double(split_lane<S, L>(__double2hiint(v)),
+                                split_lane<S, L>(__double2loint(v)));
+    }
+}
+
+// add(lane 0 .. S - 1), in order.
+template <typename F, int... L>
+__device__ __forceinline__ void split_in_order(F add, std::integer_sequence<int, L...>)
+{
+    (add(std::integral_constant<int, L>{}), ...);
 }
 
 template <bool Multi>
@@ -278,7 +324,7 @@ inline int per_mask(const Grid &g)
     return (m == 0 || m == 4 || m == 7) ? m : -1;
 }
 
-template <bool F32, bool Multi, bool Big, int Per, int KF>
+template <bool F32, bool Multi, bool Big, int Per, int KF, int S>
 __device__ __forceinline__ void density_tile(int64_t tile, int64_t n, int64_t ld,
                                              const DensRec *__restrict__ drec,
                                              const double *__restrict__ h,
@@ -291,7 +337,7 @@ __device__ __forceinline__ void density_tile(int64_t tile, int64_t n, int64_t ld
     using R = typename std::conditional<F32, float, double>::type;
     const int lane = threadIdx.x & 63;
     int64_t i, iend;
-    lane_span<Multi>(tile, n, b, i, iend);
+    lane_span<Multi, S>(tile, n, b, i, iend);
     const bool active = i < iend;
     const int64_t ii = active ? i : (Multi ? i - lane : 0);
     // individual time steps: only particles whose step closes are evaluated
@@ -301,7 +347,9 @@ __device__ __forceinline__ void density_tile(int64_t tile, int64_t n, int64_t ld
     const DensRec me = drec[ii];
     const R inv_h = R(1) / (R)h[ii];
     R sum = (R)me.m;  // w(0) = 1
-    const int cnt = active ? min(count[ii], max_nb) : 0;
+    // the lane's entries: sub, sub + S, ...
+    const int sub = S > 1 ? lane % S : 0;
+    const int cnt = active ? (min(count[ii], max_nb) - sub + S - 1) / S : 0;
     int maxc = cnt;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) maxc = max(maxc, __shfl_xor(maxc, o, 64));
@@ -323,7 +371,7 @@ __device__ __forceinline__ void density_tile(int64_t tile, int64_t n, int64_t ld
     // the requests issued before the one it needs). Indices are read two
     // steps before their records; steps past a lane's count fetch its own
     // record (in bounds, unused).
-    // Index of step k: the list row min(k, max_nb - 1) is read whatever the
+    // Index of step k: the list row min(k S + sub, max_nb - 1) is read whatever the
     // lane's count (rows at or past the count hold stale values); the value
     // is clamped to a valid record only when it is used, so that the read
     // itself carries no condition.
@@ -331,20 +379,30 @@ __device__ __forceinline__ void density_tile(int64_t tile, int64_t n, int64_t ld
     // The list is read once per call: non-temporal loads keep its 4 B per
     // pair from evicting the neighbour records from L2.
     auto jat = [&](int k) -> int {
-        return __builtin_nontemporal_load(&idx[(int64_t)min(k, krow) * ld + ii]);
+        return __builtin_nontemporal_load(&idx[(int64_t)min(k * S + sub, krow) * ld + ii]);
     };
     const uint32_t jmax = (uint32_t)(n - 1);
     auto jfix = [&](int j) -> int { return (int)min((uint32_t)j, jmax); };
     auto step = [&](int k) {
         const double2 lo = *reinterpret_cast<const double2 *>(dst_own);
         const double2 hi = *reinterpret_cast<const double2 *>(dst_own + 16);
+        R tm = R(0), tw = R(0);  // the step's term
         if (k < cnt) {
             const R dx = (R)img<Per>(me.x - lo.x, im, 0);
             const R dy = (R)img<Per>(me.y - lo.y, im, 1);
             const R dz = (R)img<Per>(me.z - hi.x, im, 2);
             const R r = fast_sqrt(fma_r(dz, dz, fma_r(dy, dy, dx * dx)));
-            sum = fma_r((R)hi.y, shape_w<KF>(r * inv_h, sinc_n), sum);
+            tm = (R)hi.y;
+            tw = shape_w<KF>(r * inv_h, sinc_n);
+            if constexpr (S == 1) sum = fma_r(tm, tw, sum);
         }
+        if constexpr (S > 1)
+            split_in_order([&](auto L) {
+                constexpr int l = decltype(L)::value;
+                sum = fma_r(split_lane<S, l>(tm), split_lane<S, l>(tw), sum);
+                // (a broadcast takes registers only when its turn has come)
+                asm volatile("" : "+v"(tm), "+v"(sum));
+            }, std::make_integer_sequence<int, S>{});
     };
     double2 a0, a1, b0, b1;
     // (issued in the loop's order: the first set is waited for first)
@@ -375,7 +433,7 @@ __device__ __forceinline__ void density_tile(int64_t tile, int64_t n, int64_t ld
         step(k + 1);
     }
     const R sg = KF == KF_M4 ? (R)kInvPi : (R)sigma;
-    if (active && closes) rho[i] = (double)(sum * (sg * inv_h * inv_h * inv_h));
+    if (active && closes && sub == 0) rho[i] = (double)(sum * (sg * inv_h * inv_h * inv_h));
 }
 
 // Ensemble: the calling wave's 64-particle tile (-1: none). The grid covers
@@ -390,7 +448,7 @@ __device__ __forceinline__ int64_t ens_wave_tile(const BatchDev &b)
     return t < ntile ? t : -1;
 }
 
-template <bool F32, bool Multi, bool Big, int Per, int KF>
+template <bool F32, bool Multi, bool Big, int Per, int KF, int S = 1>
 __global__ void __launch_bounds__(kThreads)
 density_kernel(int64_t n, int64_t ld, const DensRec *__restrict__ drec,
                const double *__restrict__ h, const int32_t *__restrict__ count,
@@ -404,12 +462,12 @@ density_kernel(int64_t n, int64_t ld, const DensRec *__restrict__ drec,
         // over tiles keeps the tile body's loop-invariant values live)
         const int64_t t = ens_wave_tile(b);
         if (t >= 0)
-            density_tile<F32, true, Big, -1, KF>(t, b.hdr->n_out, ld, drec, h, count, idx,
+            density_tile<F32, true, Big, -1, KF, 1>(t, b.hdr->n_out, ld, drec, h, count, idx,
                                                  max_nb, g, rho,
                                                  b, buf, sigma, sinc_n, mask);
     } else {
-        density_tile<F32, false, Big, Per, KF>(xcd_cu_block(), n, ld, drec, h, count, idx,
-                                               max_nb, g, rho, b, buf, sigma, sinc_n, mask);
+        density_tile<F32, false, Big, Per, KF, S>(xcd_cu_block(), n, ld, drec, h, count, idx,
+                                                  max_nb, g, rho, b, buf, sigma, sinc_n, mask);
     }
 }
 
@@ -660,7 +718,7 @@ pack_vol_kernel(int64_t n, const double *__restrict__ x, const double *__restric
 // in place of the mean kernel gradient; c_j of the next step is loaded with
 // the records.
 template <bool F32, bool Multi, bool Big, int Per, bool UH, int KF, bool IAD = false,
-          bool GVE = false>
+          bool GVE = false, int S = 1>
 __device__ __forceinline__ void momentum_tile(
     int64_t tile, int64_t n, int64_t ld, const PairRec *__restrict__ rec,
     const int32_t *__restrict__ count, const int32_t *__restrict__ idx, int max_nb,
@@ -671,7 +729,7 @@ __device__ __forceinline__ void momentum_tile(
     using R = typename std::conditional<F32, float, double>::type;
     const int lane = threadIdx.x & 63;
     int64_t i, iend;
-    lane_span<Multi>(tile, n, b, i, iend);
+    lane_span<Multi, S>(tile, n, b, i, iend);
     const bool active = i < iend;
     const int64_t ii = active ? i : (Multi ? i - lane : 0);
     const Img im = lane_img<Multi>(g, b, ii);
@@ -731,7 +789,9 @@ __device__ __forceinline__ void momentum_tile(
         cix = cp[0]; ciy = cp[1]; ciz = cp[2];
         ciyy = cp[3]; ciyz = cp[4]; cizz = cp[5];
     }
-    const int cnt = active ? min(count[ii], max_nb) : 0;
+    // the lane's entries: sub, sub + S, ...
+    const int sub = S > 1 ? lane % S : 0;
+    const int cnt = active ? (min(count[ii], max_nb) - sub + S - 1) / S : 0;
     int maxc = cnt;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) maxc = max(maxc, __shfl_xor(maxc, o, 64));
@@ -752,14 +812,14 @@ __device__ __forceinline__ void momentum_tile(
     // step k is computed, alternating between two register sets (the loop
     // runs two steps per pass, so no set is copied and every wait counts only
     // the requests issued before the one it needs). Indices are read two
-    // steps before their records: the list row min(k, max_nb - 1) whatever
+    // steps before their records: the list row min(k S + sub, max_nb - 1) whatever
     // the lane's count (rows at or past the count hold stale values), the
     // value clamped to a valid record only when it is used, so that no read
     // carries a condition. Records fetched for steps past a lane's count are
     // never used.
     const int krow = max_nb - 1;
     auto jat = [&](int k) -> int {
-        return __builtin_nontemporal_load(&idx[(int64_t)min(k, krow) * ld + ii]);
+        return __builtin_nontemporal_load(&idx[(int64_t)min(k * S + sub, krow) * ld + ii]);
     };
     const uint32_t jmax = (uint32_t)(n - 1);
     auto jfix = [&](int j) -> int { return (int)min((uint32_t)j, jmax); };
@@ -767,22 +827,22 @@ __device__ __forceinline__ void momentum_tile(
         double2 c[kChunks];
         double2 e[3] = {};  // IAD: c_j of the set's step (zero otherwise)
     };
-    auto fetch_set = [&](int jk, RecSet &S) {
+    auto fetch_set = [&](int jk, RecSet &Q) {
 #pragma unroll
         for (int t = 0; t < kChunks; ++t)
-            S.c[t] = rec_chunk<Big, kRecBytes>(src_base, __shfl(jk, rsrc[t], 64), chunk_of(t));
+            Q.c[t] = rec_chunk<Big, kRecBytes>(src_base, __shfl(jk, rsrc[t], 64), chunk_of(t));
         if constexpr (IAD) {
             const double2 *cp = reinterpret_cast<const double2 *>(prm.iad_c + 6 * (int64_t)jk);
-            S.e[0] = cp[0];
-            S.e[1] = cp[1];
-            S.e[2] = cp[2];
+            Q.e[0] = cp[0];
+            Q.e[1] = cp[1];
+            Q.e[2] = cp[2];
         }
     };
-    auto put_set = [&](const RecSet &S) {
+    auto put_set = [&](const RecSet &Q) {
         wave_lds_fence();
 #pragma unroll
         for (int t = 0; t < kChunks; ++t)
-            *reinterpret_cast<double2 *>(buf + rsrc[t] * kMomStride + chunk_of(t)) = S.c[t];
+            *reinterpret_cast<double2 *>(buf + rsrc[t] * kMomStride + chunk_of(t)) = Q.c[t];
         wave_lds_fence();
     };
     auto step = [&](int k, const double2 f0, const double2 f1, const double2 f2) {
@@ -810,6 +870,7 @@ __device__ __forceinline__ void momentum_tile(
                 Xj_ = (R)q6.x; Qj_ = (R)q6.y;
             }
         }
+        R tg = R(0), tx = R(0), ty = R(0), tz = R(0), tv = R(0);  // the step's term (S > 1)
         if (k < cnt) {
             const double dxd = img<Per>(mex - q0.x, im, 0);
             const double dyd = img<Per>(mey - q0.y, im, 1);
@@ -877,13 +938,32 @@ __device__ __forceinline__ void momentum_tile(
                 su = fma_r(mGs, fma_r(wz, gz, fma_r(wy, gy, wx * gx)), su);
             } else {
                 const R mG = wgt * F;
+                if constexpr (S > 1) {
+                    tg = mG;
+                    tx = dx;
+                    ty = dy;
+                    tz = dz;
+                    tv = vdotr;
+                } else {
                 sx = fma_r(-mG, dx, sx);
                 sy = fma_r(-mG, dy, sy);
                 sz = fma_r(-mG, dz, sz);
                 su = fma_r(mG, vdotr, su);
+                }
             }
             mum = fmax(mum, fabs(mu));
         }
+        if constexpr (S > 1)
+            split_in_order([&](auto L) {
+                constexpr int l = decltype(L)::value;
+                const R mG = split_lane<S, l>(tg);
+                sx = fma_r(-mG, split_lane<S, l>(tx), sx);
+                sy = fma_r(-mG, split_lane<S, l>(ty), sy);
+                sz = fma_r(-mG, split_lane<S, l>(tz), sz);
+                su = fma_r(mG, split_lane<S, l>(tv), su);
+                // (a broadcast takes registers only when its turn has come)
+                asm volatile("" : "+v"(tg), "+v"(sx), "+v"(sy), "+v"(sz), "+v"(su));
+            }, std::make_integer_sequence<int, S>{});
     };
     RecSet A, B;
     // (issued in the loop's order: the first set is waited for first)
@@ -908,7 +988,11 @@ __device__ __forceinline__ void momentum_tile(
         jb = jat(k + 5);
         step(k + 1, f0, f1, f2);
     }
-    if (active && closes) {
+    if constexpr (S > 1) {
+#pragma unroll
+        for (int o = 1; o < S; o <<= 1) mum = fmax(mum, __shfl_xor(mum, o, 64));
+    }
+    if (active && closes && sub == 0) {
         ax[i] = (double)sx;
         ay[i] = (double)sy;
         az[i] = (double)sz;
@@ -917,7 +1001,8 @@ __device__ __forceinline__ void momentum_tile(
     }
 }
 
-template <bool F32, bool Multi, bool Big, int Per, int KF, bool IAD = false, bool GVE = false>
+template <bool F32, bool Multi, bool Big, int Per, int KF, bool IAD = false, bool GVE = false,
+          int S = 1>
 __global__ void __launch_bounds__(kThreads)
 momentum_kernel(int64_t n, int64_t ld, const PairRec *__restrict__ rec,
                 const int32_t *__restrict__ count, const int32_t *__restrict__ idx, int max_nb,
@@ -939,13 +1024,11 @@ momentum_kernel(int64_t n, int64_t ld, const PairRec *__restrict__ rec,
                                                                  ay, az, dudt, mumax, b, buf);
     } else if (hflag[0] == 0u) {
         // uniform h (flag of the last cell build)
-        momentum_tile<F32, false, Big, Per, true, KF>(xcd_block(), n, ld, rec, count, idx,
-                                                      max_nb, g, prm, ax, ay, az, dudt, mumax,
-                                                      b, buf);
+        momentum_tile<F32, false, Big, Per, true, KF, false, false, S>(
+            xcd_block(), n, ld, rec, count, idx, max_nb, g, prm, ax, ay, az, dudt, mumax, b, buf);
     } else {
-        momentum_tile<F32, false, Big, Per, false, KF>(xcd_block(), n, ld, rec, count, idx,
-                                                       max_nb, g, prm, ax, ay, az, dudt, mumax,
-                                                       b, buf);
+        momentum_tile<F32, false, Big, Per, false, KF, false, false, S>(
+            xcd_block(), n, ld, rec, count, idx, max_nb, g, prm, ax, ay, az, dudt, mumax, b, buf);
     }
 }
 
@@ -1065,8 +1148,13 @@ eos_batch_kernel(BatchDev b, const double *__restrict__ rho, const double *__res
 // Record arrays of 4 GiB or more need 64-bit element offsets.
 inline bool big_records(int64_t n, size_t rec) { return (uint64_t)n * rec >= (1ull << 32); }
 
+// Lanes per particle of a single run's gathers. (Records of 4 GiB do not occur
+// at the sizes that are split.)
+inline int split_of(int64_t n) { return n <= kSplit16Max ? 16 : (n <= kSplit4Max ? 4 : 1); }
+inline unsigned pair_blocks(int64_t n, int split) { return blocks_for(n, kThreads / split); }
+
 template <bool Multi>
-void density_launch(hipStream_t st, unsigned blocks, int precision, bool big, int64_t n,
+void density_launch(hipStream_t st, unsigned blocks, int precision, bool big, int split, int64_t n,
                     int64_t ld, const DensRec *drec, const double *h, const int32_t *count,
                     const int32_t *idx, int max_nb, const Grid &g, double *rho, const BatchDev &b,
                     const KernelSel &ks, const StepMask &mask = StepMask{})
@@ -1074,6 +1162,15 @@ void density_launch(hipStream_t st, unsigned blocks, int precision, bool big, in
 #define SPH_DENS_P(F, B, P, K)                                                             \
     density_kernel<F, Multi, B, P, K><<<blocks, kThreads, 0, st>>>(                        \
         n, ld, drec, h, count, idx, max_nb, g, rho, b, ks.sigma, ks.sinc_n, mask)
+#define SPH_DENS_S(F, K, S)                                                                 \
+    density_kernel<F, false, false, -1, K, S><<<blocks, kThreads, 0, st>>>(                \
+        n, ld, drec, h, count, idx, max_nb, g, rho, b, ks.sigma, ks.sinc_n, mask)
+#define SPH_DENS_SPLIT(F, S)                                                                 \
+    do {                                                                                   \
+        if (ks.family == SPH_KERNEL_WENDLAND_C2) SPH_DENS_S(F, KF_WENDLAND, S);               \
+        else if (ks.family == SPH_KERNEL_SINC) SPH_DENS_S(F, KF_SINC, S);                     \
+        else SPH_DENS_S(F, KF_M4, S);                                                         \
+    } while (0)
 #define SPH_DENS(F, B)                                                                     \
     do {                                                                                   \
         const int pm = Multi ? -1 : per_mask(g);                                           \
@@ -1085,17 +1182,31 @@ void density_launch(hipStream_t st, unsigned blocks, int precision, bool big, in
         else if (pm == 7) SPH_DENS_P(F, B, 7, KF_M4);                                      \
         else SPH_DENS_P(F, B, -1, KF_M4);                                                  \
     } while (0)
+    if constexpr (!Multi) {
+        if (split == 16) {
+            if (precision == SPH_FP32_PAIR) SPH_DENS_SPLIT(true, 16);
+            else SPH_DENS_SPLIT(false, 16);
+            return;
+        }
+        if (split == 4) {
+            if (precision == SPH_FP32_PAIR) SPH_DENS_SPLIT(true, 4);
+            else SPH_DENS_SPLIT(false, 4);
+            return;
+        }
+    }
     if (precision == SPH_FP32_PAIR) {
         if (big) SPH_DENS(true, true); else SPH_DENS(true, false);
     } else {
         if (big) SPH_DENS(false, true); else SPH_DENS(false, false);
     }
 #undef SPH_DENS
+#undef SPH_DENS_SPLIT
+#undef SPH_DENS_S
 #undef SPH_DENS_P
 }
 
 template <bool Multi>
-void momentum_launch(hipStream_t st, unsigned blocks, int precision, bool big, int64_t n,
+void momentum_launch(hipStream_t st, unsigned blocks, int precision, bool big, int split, int64_t n,
                      int64_t ld, const PairRec *rec, const int32_t *count, const int32_t *idx,
                      int max_nb, const Grid &g, const MomParams &mp, double *ax, double *ay,
                      double *az, double *dudt, double *mumax, const BatchDev &b,
@@ -1104,6 +1215,15 @@ void momentum_launch(hipStream_t st, unsigned blocks, int precision, bool big, i
 #define SPH_MOM_P(F, B, P, K)                                                              \
     momentum_kernel<F, Multi, B, P, K><<<blocks, kThreads, 0, st>>>(                       \
         n, ld, rec, count, idx, max_nb, g, mp, ax, ay, az, dudt, mumax, b, hflag)
+#define SPH_MOM_S(F, K, S)                                                                 \
+    momentum_kernel<F, false, false, -1, K, false, false, S><<<blocks, kThreads, 0, st>>>(  \
+        n, ld, rec, count, idx, max_nb, g, mp, ax, ay, az, dudt, mumax, b, hflag)
+#define SPH_MOM_SPLIT(F, S)                                                                  \
+    do {                                                                                   \
+        if (family == SPH_KERNEL_WENDLAND_C2) SPH_MOM_S(F, KF_WENDLAND, S);                   \
+        else if (family == SPH_KERNEL_SINC) SPH_MOM_S(F, KF_SINC, S);                         \
+        else SPH_MOM_S(F, KF_M4, S);                                                          \
+    } while (0)
 #define SPH_MOM_IAD(F, B, K)                                                               \
     momentum_kernel<F, false, B, -1, K, true><<<blocks, kThreads, 0, st>>>(                \
         n, ld, rec, count, idx, max_nb, g, mp, ax, ay, az, dudt, mumax, b, hflag)
@@ -1132,6 +1252,18 @@ void momentum_launch(hipStream_t st, unsigned blocks, int precision, bool big, i
         else if (pm == 7) SPH_MOM_P(F, B, 7, KF_M4);                                       \
         else SPH_MOM_P(F, B, -1, KF_M4);                                                   \
     } while (0)
+    if constexpr (!Multi) {
+        if (split == 16) {
+            if (precision == SPH_FP32_PAIR) SPH_MOM_SPLIT(true, 16);
+            else SPH_MOM_SPLIT(false, 16);
+            return;
+        }
+        if (split == 4) {
+            if (precision == SPH_FP32_PAIR) SPH_MOM_SPLIT(true, 4);
+            else SPH_MOM_SPLIT(false, 4);
+            return;
+        }
+    }
     if (precision == SPH_FP32_PAIR) {
         if (big) SPH_MOM(true, true); else SPH_MOM(true, false);
     } else {
@@ -1141,6 +1273,8 @@ void momentum_launch(hipStream_t st, unsigned blocks, int precision, bool big, i
 #undef SPH_MOM_GVE_K
 #undef SPH_MOM_GVE
 #undef SPH_MOM_IAD
+#undef SPH_MOM_SPLIT
+#undef SPH_MOM_S
 #undef SPH_MOM_P
 }
 
@@ -1150,13 +1284,14 @@ hipError_t launch_density(sph_ctx ctx, const sph_particles &p, const sph_nbrs &n
                           int precision, const KernelSel &ks, bool gve, double *rho,
                           const StepMask &mask)
 {
-    const unsigned nblk = blocks_for(p.n, kThreads);
+    const int split = split_of(p.n);
+    const unsigned nblk = pair_blocks(p.n, split);
     // generalised volume elements: the records carry X in place of m, the
     // kernel leaves k_i in rho, which is then scaled by m_i / X_i
     pack_dens_kernel<<<blocks_for(p.n, 256), 256, 0, ctx->stream>>>(
         p.n, nullptr, p.x, p.y, p.z, gve ? p.xw : p.m, ctx->drec);
     const int tk = ktime_begin(ctx, TK_DENSITY);
-    density_launch<false>(ctx->stream, nblk, precision, big_records(p.n, sizeof(DensRec)), p.n,
+    density_launch<false>(ctx->stream, nblk, precision, big_records(p.n, sizeof(DensRec)), split, p.n,
                           p.n, ctx->drec, p.h, nb.count, nb.idx, nb.max_nb, ctx->grid, rho,
                           BatchDev{}, ks, mask);
     ktime_end(ctx, tk);
@@ -1207,7 +1342,8 @@ hipError_t launch_density_noalloc(hipStream_t stream, const sph_particles &p, co
     // the static array) in place of the context's records
     pack_dens_kernel<<<blocks_for(p.n, 256), 256, 0, stream>>>(p.n, nullptr, p.x, p.y, p.z,
                                                                 gve ? p.xw : p.m, recs);
-    density_launch<false>(stream, blocks_for(p.n, kThreads), precision, false, p.n, p.n, recs,
+    const int split = split_of(p.n);
+    density_launch<false>(stream, pair_blocks(p.n, split), precision, false, split, p.n, p.n, recs,
                           p.h, nb.count, nb.idx, nb.max_nb, g, rho, BatchDev{}, ks);
     if (gve)
         gve_density_kernel<<<blocks_for(p.n, 256), 256, 0, stream>>>(p.n, p.m, p.xw, rho,
@@ -1236,7 +1372,6 @@ hipError_t launch_momentum(sph_ctx ctx, const sph_particles &p, const sph_nbrs &
                            const sph_params &prm, const sph_fields &f, const sph_accel &a,
                            const double *bin, int sub, int B)
 {
-    const unsigned nblk = blocks_for(p.n, kThreads);
     const KernelSel ks = kernel_sel(prm);
     const bool iad = prm.gradient == SPH_GRAD_IAD;
     const MomParams mp{prm.alpha, prm.beta, prm.eta2, ks.sigma, ks.sinc_n, ctx->iad_c, bin, sub,
@@ -1256,6 +1391,7 @@ hipError_t launch_momentum(sph_ctx ctx, const sph_particles &p, const sph_nbrs &
 #undef SPH_IAD
     }
     const bool gve = prm.volume == SPH_VOLUME_GENERALISED;
+    const int split = iad || gve ? 1 : split_of(p.n);
     const bool r32 = prm.precision == SPH_FP32_PAIR && !iad;  // PairRec32 records
     if (r32)
         pack_pair_kernel<true><<<blocks_for(p.n, 256), 256, 0, ctx->stream>>>(
@@ -1266,8 +1402,8 @@ hipError_t launch_momentum(sph_ctx ctx, const sph_particles &p, const sph_nbrs &
             p.n, nullptr, p.x, p.y, p.z, p.vx, p.vy, p.vz, p.h, p.m, f.rho, f.c, f.pr2,
             gve ? p.xw : nullptr, ctx->prec);
     const int tk = ktime_begin(ctx, TK_MOMENTUM);
-    momentum_launch<false>(ctx->stream, nblk, prm.precision,
-                           big_records(p.n, r32 ? sizeof(PairRec32) : sizeof(PairRec)),
+    momentum_launch<false>(ctx->stream, pair_blocks(p.n, split), prm.precision,
+                           big_records(p.n, r32 ? sizeof(PairRec32) : sizeof(PairRec)), split,
                            p.n, p.n, ctx->prec, nb.count, nb.idx, nb.max_nb, ctx->grid, mp,
                            a.ax, a.ay, a.az, a.dudt, a.mumax, BatchDev{}, ctx->hflag_dev,
                            ks.family, iad, gve);
@@ -1289,7 +1425,7 @@ hipError_t launch_density_batch(sph_ctx ctx, const BatchDev &b, int precision, c
     const unsigned g2 = ens_pair_blocks(cap);
     pack_dens_kernel<<<g1, 256, 0, ctx->stream>>>(0, n_out, F + 0 * cap, F + 1 * cap,
                                                   F + 2 * cap, F + 8 * cap, ctx->drec);
-    density_launch<true>(ctx->stream, g2, precision, big_records(cap, sizeof(DensRec)), 0, cap,
+    density_launch<true>(ctx->stream, g2, precision, big_records(cap, sizeof(DensRec)), 1, 0, cap,
                          ctx->drec, F + 7 * cap, count, idx, max_nb, Grid{}, rho, b,
                          KernelSel{SPH_KERNEL_M4, 0, 0.0});
     return hipGetLastError();
@@ -1325,7 +1461,7 @@ hipError_t launch_momentum_batch(sph_ctx ctx, const BatchDev &b, int precision,
             0, n_out, F + 0 * cap, F + 1 * cap, F + 2 * cap, F + 3 * cap, F + 4 * cap,
             F + 5 * cap, F + 7 * cap, F + 8 * cap, rho, c, pr2, nullptr, ctx->prec);
     momentum_launch<true>(ctx->stream, g2, precision,
-                          big_records(cap, r32 ? sizeof(PairRec32) : sizeof(PairRec)), 0, cap,
+                          big_records(cap, r32 ? sizeof(PairRec32) : sizeof(PairRec)), 1, 0, cap,
                           ctx->prec, count, idx, max_nb, Grid{}, MomParams{}, ax, ay, az, dudt,
                           mumax, b, nullptr, SPH_KERNEL_M4, false, false);
     return hipGetLastError();
