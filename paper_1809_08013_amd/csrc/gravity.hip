@@ -272,7 +272,7 @@ gtree_init_kernel(int64_t n, GNode *__restrict__ nodes, int32_t *__restrict__ lv
                   uint32_t *__restrict__ flags)
 {
     const int t = threadIdx.x;
-    if (t < 25) lvl[t] = t == 12 ? 1 : 0;  // lvl[24]: group count
+    if (t < 26) lvl[t] = t == 12 ? 1 : 0;  // lvl[24]: group count, lvl[25]: groups taken
     if (t == 0) {
         GNode r{};
         r.start = 0;
@@ -297,48 +297,74 @@ __device__ __forceinline__ int32_t lower_key(const uint32_t *__restrict__ keys, 
 }
 
 // Split the nodes of level l: children get a contiguous block of the next
-// level (one atomic per parent; ids vary from run to run, the tree does not).
+// level (one atomic per block; ids vary from run to run, the tree does not).
+// kSplitLanes lanes per node: lane o finds where octant o starts and writes that
+// child. (Bound by the searches' chain of reads on the levels of few nodes:
+// one lane doing all nine took 40 us a level there for 1M particles, now 8; the
+// eleven levels 307 us, now 102.)
+constexpr int kSplitLanes = 16;
 __global__ void __launch_bounds__(256)
 gtree_split_kernel(int l, const uint32_t *__restrict__ keys, GNode *__restrict__ nodes,
                    int32_t *__restrict__ lvl, int64_t node_cap, int leaf_size,
                    uint32_t *__restrict__ flags)
 {
-    if (flags[0] & 1u) return;  // an earlier level ran out of nodes
+    // an earlier level ran out of nodes (other blocks may set the flag
+    // meanwhile: the block decides as one)
+    __shared__ uint32_t full;
+    if (threadIdx.x == 0) full = flags[0] & 1u;
+    __syncthreads();
+    if (full) return;
     const int32_t base = lvl[l], cnt = lvl[12 + l];
     const int32_t base_next = base + cnt;
     if (blockIdx.x == 0 && threadIdx.x == 0) lvl[l + 1] = base_next;
-    const int64_t step = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < cnt; t += step) {
-        GNode &N = nodes[base + t];
-        N.child0 = -1;
-        N.nchild = 0;
-        if (l >= kGLevels || N.end - N.start <= leaf_size) continue;
+    const int o = threadIdx.x % kSplitLanes, sub = (threadIdx.x & 63) / kSplitLanes;
+    const int wave = threadIdx.x >> 6;
+    constexpr int kPer = 256 / kSplitLanes;  // nodes per block and pass
+    __shared__ int32_t wch[4], first_child;
+    for (int64_t t0 = (int64_t)blockIdx.x * kPer; t0 < cnt; t0 += (int64_t)gridDim.x * kPer) {
+        const int64_t t = t0 + threadIdx.x / kSplitLanes;
+        const bool node = t < cnt;
+        GNode &N = nodes[base + (node ? t : t0)];
+        const int32_t start = N.start, end = N.end;
+        const uint32_t prefix = N.prefix;
+        const bool split = node && l < kGLevels && end - start > leaf_size;
         const int shift = 3 * (kGLevels - 1 - l);
-        int32_t b[9];
-        for (uint32_t o = 0; o <= 8; ++o)
-            b[o] = lower_key(keys, N.start, N.end, ((N.prefix << 3) + o) << shift);
-        int nch = 0;
-        for (int o = 0; o < 8; ++o) nch += b[o + 1] > b[o];
-        const int32_t at = atomicAdd(&lvl[12 + l + 1], nch);
-        if ((int64_t)base_next + at + nch > node_cap) {
-            atomicOr(flags, 1u);
-            continue;
+        const int32_t first = split && o <= 8 ? lower_key(keys, start, end,
+                                                          ((prefix << 3) + (uint32_t)o) << shift)
+                                              : end;
+        const int32_t next = __shfl_down(first, 1, kSplitLanes);
+        const bool child = split && o < 8 && next > first;
+        // the block's children in node and octant order, with one atomic (they
+        // serialise on the word, some 7 ns each)
+        const uint64_t all = __ballot(child);
+        const uint64_t own = all >> (kSplitLanes * sub) & ((1ull << kSplitLanes) - 1ull);
+        const int32_t nch = __popcll(own);
+        if ((threadIdx.x & 63) == 0) wch[wave] = __popcll(all);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const int32_t sum = wch[0] + wch[1] + wch[2] + wch[3];
+            first_child = sum ? atomicAdd(&lvl[12 + l + 1], sum) : 0;
         }
-        int j = 0;
-        for (uint32_t o = 0; o < 8; ++o) {
-            if (b[o + 1] == b[o]) continue;
+        __syncthreads();
+        int32_t at = first_child + (int32_t)__popcll(all & ((1ull << (kSplitLanes * sub)) - 1ull));
+        for (int w = 0; w < wave; ++w) at += wch[w];
+        const bool room = (int64_t)base_next + at + nch <= node_cap;
+        if (split && !room && o == 0) atomicOr(flags, 1u);
+        if (child && room) {
             GNode c{};
-            c.start = b[o];
-            c.end = b[o + 1];
+            c.start = first;
+            c.end = next;
             c.child0 = -1;
             c.nchild = 0;
-            c.prefix = (N.prefix << 3) | o;
+            c.prefix = (prefix << 3) | (uint32_t)o;
             c.level = l + 1;
-            nodes[base_next + at + j] = c;
-            ++j;
+            nodes[base_next + at + __popcll(own & ((1ull << o) - 1ull))] = c;
         }
-        N.child0 = base_next + at;
-        N.nchild = nch;
+        if (node && o == 0) {
+            N.child0 = split && room ? base_next + at : -1;
+            N.nchild = split && room ? nch : 0;
+        }
+        __syncthreads();  // (before the next pass's counts)
     }
 }
 
@@ -474,7 +500,34 @@ __device__ __forceinline__ void lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// One wave per group of 64 sorted particles (persistent waves). The nodes
+// An accepted node as the terms use it: centre of mass, -M and Q.
+struct NodeTerm {
+    double c[3], negm, q[6];
+};
+
+// The acceleration of one particle by an accepted node at d = x - c,
+//   -M d / r^3 + Q d / r^5 - 5/2 (d.Q d) d / r^7
+//   = (Q d + (-M r^2 - 5/2 (d.Q d) / r^2) d) / r^5.
+__device__ __forceinline__ void node_term(const DensRec &me, const NodeTerm &N, double &ax,
+                                          double &ay, double &az)
+{
+    const double d0 = me.x - N.c[0], d1 = me.y - N.c[1], d2 = me.z - N.c[2];
+    const double r2 = __builtin_fma(d2, d2, __builtin_fma(d1, d1, d0 * d0));
+    const double rinv = rsq_newton(r2);  // r2 > 0: the node was accepted
+    const double rinv2 = rinv * rinv;
+    const double rinv5 = rinv2 * rinv2 * rinv;
+    const double Qd0 = __builtin_fma(N.q[2], d2, __builtin_fma(N.q[1], d1, N.q[0] * d0));
+    const double Qd1 = __builtin_fma(N.q[4], d2, __builtin_fma(N.q[3], d1, N.q[1] * d0));
+    const double Qd2 = __builtin_fma(N.q[5], d2, __builtin_fma(N.q[4], d1, N.q[2] * d0));
+    const double dQd = __builtin_fma(d2, Qd2, __builtin_fma(d1, Qd1, d0 * Qd0));
+    const double rad = __builtin_fma(-2.5 * rinv2, dQd, N.negm * r2);
+    ax = __builtin_fma(rinv5, __builtin_fma(rad, d0, Qd0), ax);
+    ay = __builtin_fma(rinv5, __builtin_fma(rad, d1, Qd1), ay);
+    az = __builtin_fma(rinv5, __builtin_fma(rad, d2, Qd2), az);
+}
+
+// One wave per group of up to 64 sorted particles; the resident waves take the
+// groups from a counter (lvl[25]) until none is left. The nodes
 // still to visit sit on a per-wave stack in global scratch: each round pops
 // up to 64 of them, one per lane, tests them against the group's box,
 // pushes the children of the opened internal nodes and evaluates the
@@ -484,31 +537,42 @@ __device__ __forceinline__ void lds_sync()
 // definition (the test does not depend on the order), each term is the
 // definition's, and only the order of the per-particle sums differs.
 // Each lane loads its node whole; the accepted nodes' moments are handed to
-// all lanes through LDS, and an opened leaf's particles are staged in LDS by
-// one coalesced load, so no term waits on a memory round trip of its own.
-__global__ void __launch_bounds__(256)
+// all lanes through LDS, packed to the front and read two nodes at a time, and
+// an opened leaf's particles are staged in the same LDS by one coalesced load,
+// so no term waits on a memory round trip of its own.
+//
+// Bound by FP64 issue: a group of the 1M Evrard sphere has 1,330 accepted nodes
+// of 35 instructions and 1,150 leaf particles of 19 for its 45 particles, and the
+// node loop runs at 138 cycles a node and SIMD. 5.29 -> 4.4 ms: three waves per
+// SIMD, of which a third started late, became four that end together.
+__global__ void __launch_bounds__(256, 4)
 gravity_tree_kernel(const DensRec *__restrict__ pos, const int32_t *__restrict__ order,
                     const GNode *__restrict__ nodes, const int2 *__restrict__ groups,
-                    const int32_t *__restrict__ lvl, int32_t *__restrict__ stack_all,
+                    int32_t *__restrict__ lvl, int32_t *__restrict__ stack_all,
                     int64_t fcap, double e2, double *__restrict__ gx, double *__restrict__ gy,
                     double *__restrict__ gz, uint32_t *__restrict__ flags)
 {
-    __shared__ double nd_all[4][10][64];  // per wave: c, M, Q of each lane's node
-    __shared__ DensRec lr_all[4][64];     // per wave: staged leaf particles
+    union Stage {
+        NodeTerm node[64];  // a round's accepted nodes
+        DensRec leaf[64];   // then its leaf particles, 64 at a time
+    };
+    __shared__ __attribute__((aligned(16))) Stage st_all[4];
     __shared__ int32_t lk_all[4][3][64];  // per wave: their positions; leaf starts, ends
     if (flags[0] & 1u) return;  // the tree is incomplete
     const int lane = threadIdx.x & 63;
     const int w = threadIdx.x >> 6;
-    double (*nd)[64] = nd_all[w];
-    DensRec *lr = lr_all[w];
+    Stage &st = st_all[w];
     int32_t *lpos = lk_all[w][0], *lstart = lk_all[w][1], *lend = lk_all[w][2];
-    const int64_t wid = (int64_t)blockIdx.x * 4 + w;
-    const int64_t nw = (int64_t)gridDim.x * 4;
-    int32_t *stk = stack_all + wid * fcap;
-    const int64_t ngroup = lvl[24];
-    for (int64_t g = wid; g < ngroup; g += nw) {
+    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    int32_t *stk = stack_all + ((int64_t)blockIdx.x * 4 + w) * fcap;
+    const int32_t ngroup = lvl[24];
+    for (;;) {
+        int32_t g = 0;
+        if (lane == 0) g = atomicAdd(&lvl[25], 1);
+        g = __builtin_amdgcn_readfirstlane(g);
+        if (g >= ngroup) break;
         const int2 gr = groups[g];
-        const int64_t k = gr.x + lane;
+        const int32_t k = gr.x + lane;
         const bool active = k < gr.y;
         const DensRec me = pos[active ? k : gr.x];
         double blo[3] = {me.x, me.y, me.z}, bhi[3] = {me.x, me.y, me.z};
@@ -541,14 +605,33 @@ gravity_tree_kernel(const DensRec *__restrict__ pos, const int32_t *__restrict__
             }
             const bool acc = valid && sqrt(dd) > ropen;
             const bool open_int = valid && !acc && nch > 0;
-            // children of the opened internal nodes onto the stack
-            const int cnt = open_int ? nch : 0;
-            int incl = cnt;
-            for (int o = 1; o < 64; o <<= 1) {
-                const int v = __shfl_up(incl, o, 64);
-                if (lane >= o) incl += v;
+            // moments of the accepted nodes into LDS
+            const uint64_t use = __ballot(acc);
+            lds_sync();
+            if (acc) {
+                NodeTerm &T = st.node[__popcll(use & lt)];
+                T.c[0] = c[0];
+                T.c[1] = c[1];
+                T.c[2] = c[2];
+                T.negm = -N.M;
+                for (int q = 0; q < 6; ++q) T.q[q] = N.q[q];
             }
-            const int total = __shfl(incl, 63, 64);
+            // children of the opened internal nodes onto the stack, and the
+            // opened leaves' particles as one run: lane t's leaf covers
+            // [lend[t] - its count, lend[t]) of the run
+            const int cnt = open_int ? nch : 0;
+            const bool leaf = valid && !acc && nch == 0;
+            const int lcnt = leaf ? nend - nstart : 0;
+            int incl = cnt, lincl = lcnt;
+            for (int o = 1; o < 64; o <<= 1) {
+                const int v = __shfl_up(incl, o, 64), lv = __shfl_up(lincl, o, 64);
+                if (lane >= o) {
+                    incl += v;
+                    lincl += lv;
+                }
+            }
+            const int total = __builtin_amdgcn_readlane(incl, 63);
+            const int ltotal = __builtin_amdgcn_readlane(lincl, 63);
             if (sp + total > fcap) {
                 if (lane == 0) atomicOr(flags, 2u);
                 break;
@@ -558,61 +641,22 @@ gravity_tree_kernel(const DensRec *__restrict__ pos, const int32_t *__restrict__
                 for (int q = 0; q < cnt; ++q) stk[at + q] = child0 + q;
             }
             sp += total;
-            // moments of the accepted nodes into LDS
-            lds_sync();
-            if (acc) {
-                nd[0][lane] = c[0];
-                nd[1][lane] = c[1];
-                nd[2][lane] = c[2];
-                nd[3][lane] = N.M;
-                for (int q = 0; q < 6; ++q) nd[4 + q][lane] = N.q[q];
-            }
-            lds_sync();
-            // the opened leaves' particles, as one run: lane t's leaf covers
-            // [lend[t] - its count, lend[t]) of the run
-            const bool leaf = valid && !acc && nch == 0;
-            const int lcnt = leaf ? nend - nstart : 0;
-            int lincl = lcnt;
-            for (int o = 1; o < 64; o <<= 1) {
-                const int v = __shfl_up(lincl, o, 64);
-                if (lane >= o) lincl += v;
-            }
-            const int ltotal = __shfl(lincl, 63, 64);
             lstart[lane] = nstart;
             lend[lane] = lincl;
+            lds_sync();
             // accepted nodes in lane order
-            uint64_t use = __ballot(acc);
-            while (use) {
-                const int tl = __builtin_ctzll(use);
-                use &= use - 1;
-                {
-                    // -M d / r^3 + Q d / r^5 - 5/2 (d.Q d) d / r^7, as
-                    // (Q d) / r^5 + (-M / r^3 - 5/2 (d.Q d) / r^7) d with fused
-                    // multiply-adds
-                    const double d0 = me.x - nd[0][tl], d1 = me.y - nd[1][tl],
-                                 d2 = me.z - nd[2][tl];
-                    const double M = nd[3][tl];
-                    const double q0 = nd[4][tl], q1 = nd[5][tl], q2 = nd[6][tl],
-                                 q3 = nd[7][tl], q4 = nd[8][tl], q5 = nd[9][tl];
-                    const double r2 = __builtin_fma(d2, d2, __builtin_fma(d1, d1, d0 * d0));
-                    const double rinv = rsq_newton(r2);  // r2 > 0: the node was accepted
-                    const double rinv2 = rinv * rinv;
-                    const double rinv3 = rinv * rinv2;
-                    const double rinv5 = rinv3 * rinv2;
-                    const double rinv7 = rinv5 * rinv2;
-                    const double Qd0 = __builtin_fma(q2, d2, __builtin_fma(q1, d1, q0 * d0));
-                    const double Qd1 = __builtin_fma(q4, d2, __builtin_fma(q3, d1, q1 * d0));
-                    const double Qd2 = __builtin_fma(q5, d2, __builtin_fma(q4, d1, q2 * d0));
-                    const double dQd = __builtin_fma(d2, Qd2, __builtin_fma(d1, Qd1, d0 * Qd0));
-                    const double rad = __builtin_fma(-2.5 * dQd, rinv7, -M * rinv3);
-                    ax = __builtin_fma(Qd0, rinv5, __builtin_fma(rad, d0, ax));
-                    ay = __builtin_fma(Qd1, rinv5, __builtin_fma(rad, d1, ay));
-                    az = __builtin_fma(Qd2, rinv5, __builtin_fma(rad, d2, az));
-                }
+            const int nacc = __popcll(use);
+            int t = 0;
+            for (; t + 2 <= nacc; t += 2) {
+                const NodeTerm A = st.node[t], B = st.node[t + 1];
+                node_term(me, A, ax, ay, az);
+                node_term(me, B, ax, ay, az);
             }
+            if (t < nacc) node_term(me, st.node[t], ax, ay, az);
             // then the leaves' particles, staged 64 at a time by one load each
             for (int base = 0; base < ltotal; base += 64) {
                 const int m = min(64, ltotal - base);
+                int32_t q = gr.y;
                 lds_sync();
                 if (lane < m) {
                     const int r = base + lane;
@@ -622,21 +666,34 @@ gravity_tree_kernel(const DensRec *__restrict__ pos, const int32_t *__restrict__
                         if (lend[mid] > r) hi = mid; else lo = mid + 1;
                     }
                     const int first = lo == 0 ? 0 : lend[lo - 1];
-                    const int32_t q = lstart[lo] + (r - first);
+                    q = lstart[lo] + (r - first);
                     lpos[lane] = q;
-                    lr[lane] = pos[q];
+                    st.leaf[lane] = pos[q];
                 }
+                // a particle is left out of its own sum: only where the group's
+                // own ones are among the staged
+                const bool own = __ballot(q >= gr.x && q < gr.y) != 0ull;
                 lds_sync();
-                for (int j = 0; j < m; ++j) {
-                    const DensRec o = lr[j];
+                auto add = [&](const DensRec &o, bool self) {
                     const double dx = me.x - o.x, dy = me.y - o.y, dz = me.z - o.z;
                     const double d2 =
                         __builtin_fma(dz, dz, __builtin_fma(dy, dy, __builtin_fma(dx, dx, e2)));
                     const double w = mass_rsq3(o.m, __builtin_amdgcn_rsq(d2), d2);
-                    const double t = lpos[j] == k ? 0.0 : w;
-                    ax = __builtin_fma(-t, dx, ax);
-                    ay = __builtin_fma(-t, dy, ay);
-                    az = __builtin_fma(-t, dz, az);
+                    const double f = self ? 0.0 : w;
+                    ax = __builtin_fma(-f, dx, ax);
+                    ay = __builtin_fma(-f, dy, ay);
+                    az = __builtin_fma(-f, dz, az);
+                };
+                if (own) {
+                    for (int j = 0; j < m; ++j) add(st.leaf[j], lpos[j] == k);
+                } else {
+                    int j = 0;
+                    for (; j + 2 <= m; j += 2) {
+                        const DensRec A = st.leaf[j], B = st.leaf[j + 1];
+                        add(A, false);
+                        add(B, false);
+                    }
+                    if (j < m) add(st.leaf[j], false);
                 }
             }
             // the pushed entries are read by other lanes next round
@@ -726,7 +783,7 @@ hipError_t gt_reserve_all(sph_ctx ctx)
     if ((e = gt_alloc(ctx, &ctx->gt_vals[1], n)) != hipSuccess) return e;
     if ((e = gt_alloc(ctx, &ctx->gt_pos, n)) != hipSuccess) return e;
     if ((e = gt_alloc(ctx, &ctx->gt_nodes, ctx->gt_node_cap)) != hipSuccess) return e;
-    if ((e = gt_alloc(ctx, &ctx->gt_lvl, 25)) != hipSuccess) return e;
+    if ((e = gt_alloc(ctx, &ctx->gt_lvl, 26)) != hipSuccess) return e;
     if ((e = gt_alloc(ctx, &ctx->gt_groups, n + 1)) != hipSuccess) return e;
     if ((e = gt_alloc(ctx, &ctx->gt_front, (int64_t)ctx->gt_waves * ctx->gt_fcap)) !=
         hipSuccess)
@@ -782,19 +839,17 @@ hipError_t launch_gravity_tree(sph_ctx ctx, const sph_particles &p, double eps, 
                                                      ctx->gt_pos);
     gtree_init_kernel<<<1, 64, 0, s>>>(n, ctx->gt_nodes, ctx->gt_lvl, ctx->gt_flags);
     // level l has at most min(8^l, node_cap) nodes
-    auto level_blocks = [&](int l) {
+    auto level_blocks = [&](int l, int lanes) {
         int64_t most = ctx->gt_node_cap;
         if (l < 8) most = std::min<int64_t>(most, (int64_t)1 << (3 * l));
-        return std::max(1u, std::min(4096u, blocks_for(most, 256)));
+        return std::max(1u, std::min(4096u, blocks_for(most * lanes, 256)));
     };
     for (int l = 0; l <= kGLevels; ++l)
-        gtree_split_kernel<<<level_blocks(l), 256, 0, s>>>(l, keys, ctx->gt_nodes, ctx->gt_lvl,
-                                                           ctx->gt_node_cap, leaf_size,
-                                                           ctx->gt_flags);
+        gtree_split_kernel<<<level_blocks(l, kSplitLanes), 256, 0, s>>>(
+            l, keys, ctx->gt_nodes, ctx->gt_lvl, ctx->gt_node_cap, leaf_size, ctx->gt_flags);
     for (int l = kGLevels; l >= 0; --l)
-        gtree_moments_kernel<<<level_blocks(l), 256, 0, s>>>(l, ctx->gt_pos, ctx->gt_nodes,
-                                                             ctx->gt_lvl, ctx->gt_box, theta,
-                                                             ctx->gt_flags);
+        gtree_moments_kernel<<<level_blocks(l, 1), 256, 0, s>>>(
+            l, ctx->gt_pos, ctx->gt_nodes, ctx->gt_lvl, ctx->gt_box, theta, ctx->gt_flags);
     gtree_groups_kernel<<<std::min(4096u, blocks_for(ctx->gt_node_cap, 256)), 256, 0, s>>>(
         n, ctx->gt_nodes, ctx->gt_lvl, ctx->gt_groups, ctx->gt_flags);
     if ((e = hipGetLastError()) != hipSuccess) return e;

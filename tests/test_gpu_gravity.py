@@ -40,3 +40,26 @@ def test_direct_sum_shares(n, eps):
     scale = np.where(scale > 0, scale, 1.0)
     for a, b in (("gx", gx), ("gy", gy), ("gz", gz)):
         assert np.max(np.abs(got[a][sel] - b) / scale) <= 1e-13
+
+
+@pytest.mark.parametrize("leaf", [8, 16, 64])
+@pytest.mark.parametrize("n", [1, 2, 64, 65, 130, 9001])
+def test_tree_groups_and_leaves(n, leaf):
+    """The octree at the edges of its groups (64 particles), with the smallest, the
+    usual and the largest leaves: within 1e-12 of the terms'
+    magnitudes, the accuracy of the node terms' eight FP64 factors over a few
+    hundred terms."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    torch.cuda.set_device(0)
+    print(f"tree n={n} leaf={leaf}", flush=True)
+    ic = I.evrard(n, seed=4)
+    gx, gy, gz, scale, _ = O.gravity_tree(ic.x, ic.y, ic.z, ic.m, 0.01, 0.6, leaf)
+    ctx = S.Context(n, 16)
+    st = S.SphState(ic, 16)
+    S.sph_gravity_tree(ctx, st, 0.01, 0.6, leaf)
+    S.sph_ctx_check(ctx)
+    got = st.host(["gx", "gy", "gz"])
+    scale = np.where(scale > 0, scale, 1.0)
+    for a, b in (("gx", gx), ("gy", gy), ("gz", gz)):
+        assert np.max(np.abs(got[a] - b) / scale) <= 1e-12
