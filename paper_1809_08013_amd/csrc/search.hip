@@ -155,64 +155,65 @@ __device__ __forceinline__ bool related(const SearchRec &me, const SearchRec &o,
     return (r2 < me.s2) | (r2 < o.s2);
 }
 
-// Window of a cell for an extent [lo, hi] and a reach r (no periodic image in
-// play): the sub-range of the cell's particles that can hold a point within r.
-// - The whole cell is skipped when its x or y range lies more than r + a
-//   millionth of a cell beyond the extent on that axis: every candidate is
-//   then farther than r (a particle's cell index comes from the same
-//   arithmetic, whose rounding is some 1e-13 of a cell).
-// - Otherwise only the z slices within r + (one slice) of the z extent are
-//   kept, by the same argument; a cell's keys are ordered by slice, so the
-//   window is found by binary search.
+// Window of cell (cx, cy, cz) for the sphere of radius r around pt (no periodic
+// image in play): the sub-range of the cell's particles that can hold a point
+// within r. The cell's x and y ranges leave sqrt(r^2 - dx^2 - dy^2) of the radius
+// along z, dx and dy being the distances to them less a millionth of a cell (a
+// particle's cell index comes from the same arithmetic, whose rounding is some
+// 1e-13 of a cell); without any left the cell is skipped, else only the z slices
+// within that + (one slice) are kept. A cell's keys are ordered by slice, so the
+// window is found by binary search.
 // The first and last cell of an axis also hold the particles clamped into
 // them from outside the box, so their range is taken as unbounded on the
 // outer side, and their outer slice is always kept.
-__device__ __forceinline__ int2 z_window_r(int2 cr, uint32_t p, const Grid &g,
-                                           const double (&tlo)[3], const double (&thi)[3],
-                                           double r, const uint32_t *__restrict__ keys)
+__device__ __forceinline__ int2 sphere_window(int2 cr, int cx, int cy, int cz, const Grid &g,
+                                              const double (&pt)[3], double r,
+                                              const uint32_t *__restrict__ keys)
 {
     if (cr.x >= cr.y) return cr;
-    const int x = (int)(p & 1023u), y = (int)((p >> 10) & 1023u), z = (int)(p >> 20);
-    const int cxy[2] = {x, y};
+    const int cxy[2] = {cx, cy};
+    double left = r * r;
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
-        const double fl = (tlo[a] - g.lo[a]) * g.inv_s[a], fh = (thi[a] - g.lo[a]) * g.inv_s[a];
-        const double ra = r * g.inv_s[a] + 1e-6;
-        const bool above = cxy[a] > 0 && (double)cxy[a] - fh > ra;
-        const bool below = cxy[a] < g.nc[a] - 1 && fl - (double)(cxy[a] + 1) > ra;
-        if (above || below) return make_int2(cr.x, cr.x);
+        const double f = (pt[a] - g.lo[a]) * g.inv_s[a] - (double)cxy[a];
+        const double below = cxy[a] > 0 ? -f : 0.0;
+        const double above = cxy[a] < g.nc[a] - 1 ? f - 1.0 : 0.0;
+        const double d = fmax(fmax(below, above) - 1e-6, 0.0) / g.inv_s[a];
+        left -= d * d;
     }
-    const double zlo = tlo[2], zhi = thi[2];
+    if (left < 0.0) return make_int2(cr.x, cr.x);
+    const double rz = sqrt(left) * (1.0 + 1e-6);
     const double ns = (double)(1 << g.zbits);
-    const double fl = ((zlo - r) - g.lo[2]) * g.inv_s[2] - (double)z;
-    const double fh = ((zhi + r) - g.lo[2]) * g.inv_s[2] - (double)z;
+    const double fl = ((pt[2] - rz) - g.lo[2]) * g.inv_s[2] - (double)cz;
+    const double fh = ((pt[2] + rz) - g.lo[2]) * g.inv_s[2] - (double)cz;
     double ql = fmax(floor(fl * ns) - 1.0, 0.0);
     double qh = fmin(floor(fh * ns) + 1.0, ns - 1.0);
-    if (z == 0) qh = fmax(qh, 0.0);
-    if (z == g.nc[2] - 1) ql = fmin(ql, ns - 1.0);
+    if (cz == 0) qh = fmax(qh, 0.0);
+    if (cz == g.nc[2] - 1) ql = fmin(ql, ns - 1.0);
     if (ql > qh) return make_int2(cr.x, cr.x);
     if (ql == 0.0 && qh == ns - 1.0) return cr;
     const uint32_t base = keys[cr.x] & ~((1u << g.zbits) - 1u);
     const uint32_t klo = base | (uint32_t)ql, khi = base | (uint32_t)qh;
-    int a = cr.x, e = cr.y;
-    while (a < e) {  // first key >= klo
-        const int mid = (a + e) >> 1;
-        if (keys[mid] < klo) a = mid + 1; else e = mid;
+    // first key >= klo and first key > khi, side by side
+    int a = cr.x, e = cr.y, p = cr.x, q = cr.y;
+    while (a < e || p < q) {
+        const int m = (a + e) >> 1, n = (p + q) >> 1;
+        const uint32_t km = keys[min(m, cr.y - 1)], kn = keys[min(n, cr.y - 1)];
+        if (a < e) {
+            if (km < klo) a = m + 1; else e = m;
+        }
+        if (p < q) {
+            if (kn <= khi) p = n + 1; else q = n;
+        }
     }
-    const int first = a;
-    e = cr.y;
-    while (a < e) {  // first key > khi
-        const int mid = (a + e) >> 1;
-        if (keys[mid] <= khi) a = mid + 1; else e = mid;
-    }
-    return make_int2(first, a);
+    return make_int2(a, p);
 }
 
 // Window of a union cell (coordinates cc) for a tile of the given centre and
 // half extents and a reach r, on images nearest to the centre: an empty range
 // when the cell lies more than r + a millionth of a cell beyond the tile on
 // some axis, else the z slices within r + (one slice) of the tile's z extent.
-// The same bounds as z_window_r, and as there the outer side of an open axis'
+// As in sphere_window, the outer side of an open axis'
 // border cells is unbounded. Only a cell of kWindowMin particles or more is
 // searched for its slices: a shorter one costs less tested whole.
 constexpr int kWindowMin = 48;
@@ -1047,165 +1048,44 @@ find_neighbors_kernel(int64_t n, int64_t ld, const SearchRec *__restrict__ srec,
 // rule of IEEE operations (cbrt_newton), so that any implementation of the
 // same rule gets the same h.
 
-// Offsets -k..k on one axis, without repeating a cell when a periodic axis
-// has fewer than 2k + 1 cells.
-__device__ __forceinline__ int axis_offsets(int nc, int periodic, int k, int (&off)[5])
+// Cells walked on one axis for a reach of r: those the sphere meets on an open
+// axis; the own one and k (1 or 2) to either side on a periodic one, or every cell
+// once where it has fewer than that (all).
+struct AxisCells {
+    int first, n;
+    bool all;
+};
+__device__ __forceinline__ AxisCells axis_cells(const Grid &g, int a, int own, double x, double r)
 {
-    if (periodic && nc < 2 * k + 1) {
-        for (int d = 0; d < nc; ++d) off[d] = d;
-        return nc;
+    if (!g.periodic[a]) {
+        const double f = (x - g.lo[a]) * g.inv_s[a], fr = r * g.inv_s[a] + 1e-6;
+        const double top = (double)(g.nc[a] - 1);
+        const int lo = (int)fmin(fmax(floor(f - fr), 0.0), top);
+        const int hi = (int)fmin(fmax(floor(f + fr), 0.0), top);
+        return AxisCells{lo, hi - lo + 1, false};
     }
-    for (int d = -k; d <= k; ++d) off[d + k] = d;
-    return 2 * k + 1;
+    const int k = r * g.inv_s[a] * (1.0 + 1e-12) <= 1.0 ? 1 : 2;
+    if (g.nc[a] < 2 * k + 1) return AxisCells{0, g.nc[a], true};
+    return AxisCells{own - k, 2 * k + 1, false};
 }
 
-// Words of the on-device iteration (ctx->it_words): [0] nonzero when a
-// particle is outside the band, [1] length of the list of particles that the
-// next sweep counts with lane groups, [2] done (the last sweep's counts are final),
-// [3] sweeps counted, [4] a particle outside the grid's reach (2 h > 2
-// cells): the host rebuilds the cells and continues.
-enum { IT_BAD = 0, IT_NLIST = 1, IT_DONE = 2, IT_SWEEP = 3, IT_REACH = 4, IT_WORDS = 5 };
+// Words of the on-device iteration (ctx->it_words): [1] the first sweep at which
+// a particle outgrew the grid's reach, [2] done (the counts are final), [3]
+// sweeps counted, [4] a particle outside the grid's reach (2 h > 2 cells): the
+// host rebuilds the cells and continues.
+enum { IT_STOP = 1, IT_DONE = 2, IT_SWEEP = 3, IT_REACH = 4, IT_WORDS = 5 };
 
-// After the first sweep on a cell build, a wave whose particles include
-// fewer than kSweepDense to recount leaves them to the lane-group kernel
-// (its slowest lane would set its time); kSweepGroup lanes share each such
-// particle's cells.
-constexpr int kSweepDense = 32;
-constexpr int kSweepGroup = 32;
-
-// Gather count of the lane's particle over the particles [w.x, w.y): the
-// records are loaded four at a time, so that a test waits for its load once
-// per four (a record per iteration left each test waiting for its own load;
-// the next four in flight as well cost the kernel half its occupancy).
-template <int Mode>
-__device__ __forceinline__ int count_window(const SearchRec &me, const SearchRec *__restrict__ srec,
-                                            int2 w, int self, const Grid &g,
-                                            const double (&sh)[3])
+__global__ void h_begin_kernel(uint32_t *words, int32_t first)
 {
-    int cnt = 0;
-    auto test = [&](const SearchRec &o, int j) {
-        cnt += (j != self && related<Mode, true>(me, o, g, sh)) ? 1 : 0;
-    };
-    int j = w.x;
-    for (; w.y - j >= 4; j += 4) {
-        const SearchRec a0 = srec[j], a1 = srec[j + 1], a2 = srec[j + 2], a3 = srec[j + 3];
-        test(a0, j);
-        test(a1, j + 1);
-        test(a2, j + 2);
-        test(a3, j + 3);
-    }
-    for (; j < w.y; ++j) test(srec[j], j);
-    return cnt;
+    words[0] = words[IT_DONE] = words[IT_REACH] = 0u;
+    words[IT_STOP] = 0x7FFFFFFFu;
+    words[IT_SWEEP] = (uint32_t)first;
 }
 
-// Gather counts of one sweep: N_i = #{j != i : r^2 < (2 h_i)^2}. The cells
-// were built for a largest h that the sweeps may outgrow: a particle with
-// 2 h_i up to two cells walks the 5^3 cells around its own, beyond that the
-// sweep raises IT_REACH and counts nothing. Each cell reached without a
-// periodic image is walked only in its window for the own sphere (a point
-// box of reach 2 h_i): cells beyond it in x or y are skipped, in the others
-// only the z slices within reach. Does nothing once IT_DONE or IT_REACH is
-// set. Periodic: some axis of the box is periodic (then each pair takes the
-// minimum image; else the separation is used as it is).
-// recount_all = 0 (every sweep after the first of a run of sweeps on one
-// cell build): a particle whose previous count was inside the band kept its
-// h, so its count cannot change; a wave holding fewer than kSweepDense
-// particles to recount keeps its counts and exits (after the first sweeps
-// most waves do), its particles to recount being on the lane-group list.
-template <bool Periodic>
-__global__ void __launch_bounds__(256)
-gather_count_kernel(int64_t n, const SearchRec *__restrict__ srec,
-                    const uint32_t *__restrict__ keys, const int32_t *__restrict__ cstart,
-                    const int32_t *__restrict__ cend, Grid g, int32_t *__restrict__ count,
-                    int32_t lo_count, int32_t hi_count, uint32_t *words, int recount_all)
+__global__ void h_end_kernel(uint32_t *words)
 {
-    if (words[IT_DONE] || words[IT_REACH]) return;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    bool active = i < n;
-    if (!recount_all) {
-        const int prev = active ? count[i] : lo_count;
-        const uint64_t redo = __ballot(prev < lo_count || prev > hi_count);
-        if (__popcll(redo) < kSweepDense) return;  // the whole wave
-    }
-    const SearchRec me = active ? srec[i] : SearchRec{0.0, 0.0, 0.0, 0.0};
-    const double R = sqrt(me.s2);
-    int k[3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const double reach = R * g.inv_s[a] * (1.0 + 1e-12);
-        k[a] = reach <= 1.0 ? 1 : (reach <= 2.0 ? 2 : 3);
-    }
-    const bool outgrown = active && (k[0] > 2 || k[1] > 2 || k[2] > 2);
-    if (__ballot(outgrown) != 0ull) {
-        if ((threadIdx.x & 63) == 0) atomicOr(&words[IT_REACH], 1u);
-        return;  // (the whole wave: the sweep is discarded)
-    }
-    int cnt = 0;
-    if (active) {
-        const uint32_t key = keys[i] >> g.zbits;
-        const int myc[3] = {(int)compact3(key), (int)compact3(key >> 1),
-                            (int)compact3(key >> 2)};
-        int ox[5], oy[5], oz[5];
-        const int nx = axis_offsets(g.nc[0], g.periodic[0], k[0], ox);
-        const int ny = axis_offsets(g.nc[1], g.periodic[1], k[1], oy);
-        const int nz = axis_offsets(g.nc[2], g.periodic[2], k[2], oz);
-        const double no_shift[3] = {0.0, 0.0, 0.0};
-        const double pt[3] = {me.x, me.y, me.z};
-        // a periodic axis with fewer than 2k + 1 cells: every cell, once
-        const bool all_x = g.periodic[0] && g.nc[0] < 2 * k[0] + 1;
-        const bool all_y = g.periodic[1] && g.nc[1] < 2 * k[1] + 1;
-        const bool all_z = g.periodic[2] && g.nc[2] < 2 * k[2] + 1;
-        for (int c = 0; c < nz; ++c) {
-            bool okz = true;
-            const int zr = all_z ? oz[c] : myc[2] + oz[c];
-            const int z = all_z ? zr : wrap_or_clip(zr, g.nc[2], g.periodic[2], okz);
-            if (!okz) continue;
-            for (int b = 0; b < ny; ++b) {
-                bool oky = true;
-                const int yr = all_y ? oy[b] : myc[1] + oy[b];
-                const int y = all_y ? yr : wrap_or_clip(yr, g.nc[1], g.periodic[1], oky);
-                if (!oky) continue;
-                for (int a = 0; a < nx; ++a) {
-                    bool okx = true;
-                    const int xr = all_x ? ox[a] : myc[0] + ox[a];
-                    const int x = all_x ? xr : wrap_or_clip(xr, g.nc[0], g.periodic[0], okx);
-                    if (!okx) continue;
-                    const int64_t cell = ((int64_t)z * g.nc[1] + y) * g.nc[0] + x;
-                    int2 w = make_int2(cstart[cell], cend[cell]);
-                    // reached without a periodic image: only the window
-                    const bool direct = !all_x && !all_y && !all_z && x == xr && y == yr &&
-                                        z == zr;
-                    if (direct && g.zbits > 0)
-                        w = z_window_r(w, (uint32_t)x | ((uint32_t)y << 10) |
-                                              ((uint32_t)z << 20),
-                                       g, pt, pt, R, keys);
-                    cnt += count_window<Periodic ? WRAP_PAIR : WRAP_NONE>(me, srec, w, (int)i,
-                                                                           g, no_shift);
-                }
-            }
-        }
-        count[i] = cnt;
-    }
-    // Only whether some particle is outside the band matters: a wave with
-    // one sets the flag unless it is already set. (An atomic from every wave
-    // to the one word serialises in its L2 channel: ~10 ns each.) The word
-    // is only ever set within a sweep, so a stale read costs one atomic.
-    const uint64_t bad = __ballot(active && (cnt < lo_count || cnt > hi_count));
-    if ((threadIdx.x & 63) == 0 && bad &&
-        __hip_atomic_load(&words[IT_BAD], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u)
-        atomicOr(&words[IT_BAD], 1u);
-}
-
-// End of a sweep (one thread): the counts of this sweep are final when every
-// particle is inside the band or this is sweep max_iter; else the h update
-// follows. Clears the band flag for the next sweep.
-__global__ void sweep_end_kernel(uint32_t *words, int32_t max_iter)
-{
-    if (words[IT_DONE] || words[IT_REACH]) return;
-    if (words[IT_BAD] == 0 || (int32_t)words[IT_SWEEP] == max_iter) words[IT_DONE] = 1u;
-    else words[IT_SWEEP] += 1u;
-    words[IT_BAD] = 0u;
-    words[IT_NLIST] = 0u;
+    if (words[IT_REACH]) words[IT_SWEEP] = words[IT_STOP];
+    else words[IT_DONE] = 1u;
 }
 
 // Cube root of a > 0 by Newton's iteration for y^3 = a in correctly rounded
@@ -1230,117 +1110,163 @@ __device__ __forceinline__ double cbrt_newton(double a)
     return ldexp(y, k);
 }
 
-// h <- 2 h for an empty sphere, else (h / 2) (1 + (n_target / N)^(1/3)), for
-// the particles outside the band; their search records take the new
-// (2 h)^2. Does nothing once the counts are final.
-// The updated particles of a wave with fewer than kSweepDense of them go on
-// the list of the next sweep's lane-group kernel (list, words[IT_NLIST],
-// cleared by the sweep's end; one atomic per block).
-__global__ void __launch_bounds__(256)
-update_h_kernel(int64_t n, const int32_t *__restrict__ count, double *__restrict__ h,
-                SearchRec *__restrict__ srec, int32_t lo_count, int32_t hi_count,
-                double n_target, uint32_t *words, int32_t *__restrict__ list)
-{
-    if (words[IT_DONE] || words[IT_REACH]) return;
-    __shared__ uint32_t s_cnt[4];
-    __shared__ uint32_t s_base;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int c = i < n ? count[i] : lo_count;
-    const bool upd = c < lo_count || c > hi_count;
-    if (upd) {
-        const double hn = c == 0 ? 2.0 * h[i]
-                                 : (h[i] * 0.5) * (1.0 + cbrt_newton(n_target / (double)c));
-        h[i] = hn;
-        const double s = 2.0 * hn;
-        srec[i].s2 = s * s;
-    }
-    const uint64_t m = __ballot(upd);
-    const uint32_t nw = (uint32_t)__popcll(m);
-    const uint32_t listed = nw < (uint32_t)kSweepDense ? nw : 0u;
-    if (lane == 0) s_cnt[wave] = listed;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const uint32_t tot = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
-        s_base = tot ? atomicAdd(&words[IT_NLIST], tot) : 0u;
-    }
-    __syncthreads();
-    if (listed && upd) {
-        uint32_t off = s_base;
-        for (int w = 0; w < wave; ++w) off += s_cnt[w];
-        off += (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-        list[off] = (int32_t)i;
-    }
-}
-
-// Gather counts of the listed particles (the lane-group half of a sweep):
-// kSweepGroup lanes per particle, which take its cells in turn and add
-// their counts. Same cells, windows and test as gather_count_kernel.
+// All sweeps of a particle in one go: kHLanes lanes per particle. The sweeps of
+// the definition - count every particle's neighbours, change the h of those
+// outside the band, until none is (or sweep max_iter) - only meet in the number
+// of the last one, as a count depends on the particle's own h alone.
+//
+// The lanes gather the squares of the distances within kHMargin times the
+// particle's reach into LDS, and count from there for as long as h stays within
+// it and they fit; else they gather again. The cells were built for a largest h
+// that the sweeps may outgrow: a particle with 2 h_i up to two cells walks the
+// cells its sphere meets, beyond that it raises IT_REACH and stops. Each cell
+// reached without a periodic image is walked only in its window for the sphere. Periodic: some axis of the box is periodic (then each pair takes
+// the minimum image; else the separation is used as it is).
+//
+// redo = 0: h goes to `tmp`. redo = 1: to `h`; from tmp, unless a particle
+// outgrew the reach at some sweep: then every particle stops before that sweep,
+// as the sweeps in order do, and h is what the updates until then made of it.
+//
+// Bound by the latency of the first gather (table, window searches and records
+// one after the other), so six waves per SIMD. 300,000 particles of the Evrard
+// sphere, 11 sweeps: 0.7 ms, where a counting and an update kernel per sweep took
+// 3.5 (and 32 kernels). Lanes per particle 8, 16, 32: 1790, 1503, 1476 us a call
+// before the windows took the sphere's shape (1180 then, 1185 with 32); margins
+// 1.06 and 1.3 against 1.15: 4% more each; at six waves 1.1 against 1.15: 3% less.
+constexpr int kHLanes = 16;
+constexpr int kHList = 192;
+constexpr double kHMargin = 1.1;
 template <bool Periodic>
-__global__ void __launch_bounds__(256)
-gather_count_list_kernel(const int32_t *__restrict__ list, const SearchRec *__restrict__ srec,
-                         const uint32_t *__restrict__ keys, const int32_t *__restrict__ cstart,
-                         const int32_t *__restrict__ cend, Grid g, int32_t *__restrict__ count,
-                         int32_t lo_count, int32_t hi_count, uint32_t *words)
+__global__ void __launch_bounds__(256, 6)
+h_iteration_kernel(int64_t n, const SearchRec *__restrict__ srec,
+                   const uint32_t *__restrict__ keys, const int32_t *__restrict__ cstart,
+                   const int32_t *__restrict__ cend, Grid g, double *__restrict__ h,
+                   double *__restrict__ tmp, int32_t *__restrict__ count, int32_t lo_count,
+                   int32_t hi_count, double n_target, int32_t first, int32_t max_iter,
+                   uint32_t *words, int redo)
 {
-    if (words[IT_DONE] || words[IT_REACH]) return;
-    const int64_t nl = words[IT_NLIST];
-    const int sub = threadIdx.x % kSweepGroup;
-    const int64_t groups = (int64_t)gridDim.x * (blockDim.x / kSweepGroup);
-    for (int64_t e = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kSweepGroup; e < nl;
-         e += groups) {
-        const int64_t i = list[e];
-        const SearchRec me = srec[i];
-        const double R = sqrt(me.s2);
-        int k[3];
+    __shared__ double list_all[256 / kHLanes][kHList + kHLanes];  // (padded for the banks)
+    const int sub = threadIdx.x % kHLanes, grp = threadIdx.x / kHLanes;
+    double *list = list_all[grp];
+    const int64_t i = xcd_block() * (256 / kHLanes) + grp;
+    const bool active = i < n;
+    if (redo && !words[IT_REACH]) {
+        if (active && sub == 0) h[i] = tmp[i];
+        return;
+    }
+    const int32_t stop = redo ? (int32_t)words[IT_STOP] : 0x7FFFFFFF;
+    const int64_t ii = active ? i : n - 1;
+    const SearchRec me = srec[ii];
+    double hh = h[ii];
+    const uint32_t key = keys[ii] >> g.zbits;
+    const int myc[3] = {(int)compact3(key), (int)compact3(key >> 1), (int)compact3(key >> 2)};
+    const double pt[3] = {me.x, me.y, me.z};
+    // the particle's lanes in a ballot
+    const int gshift = threadIdx.x & 63 & ~(kHLanes - 1);
+    const uint32_t lt = (1u << sub) - 1u;
+    int32_t sweep = first;
+    int cnt = 0, nlist = 0;
+    double rc2 = -1.0;  // the list holds every r^2 below this
+    bool run = active && sweep < stop;
+    while (run) {
+        const double s = 2.0 * hh, s2 = s * s;
+        const double R = sqrt(s2);
+        cnt = 0;
+        if (s2 <= rc2) {
+            for (int q = sub; q < nlist; q += kHLanes) cnt += list[q] < s2 ? 1 : 0;
+        } else {
+            double Rc = kHMargin * R;
+            bool outgrown = false;
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const double reach = R * g.inv_s[a] * (1.0 + 1e-12);
-            k[a] = reach <= 1.0 ? 1 : (reach <= 2.0 ? 2 : 3);
-        }
-        if (k[0] > 2 || k[1] > 2 || k[2] > 2) {
-            if (sub == 0) atomicOr(&words[IT_REACH], 1u);
-            continue;  // (the sweep is discarded)
-        }
-        const uint32_t key = keys[i] >> g.zbits;
-        const int myc[3] = {(int)compact3(key), (int)compact3(key >> 1), (int)compact3(key >> 2)};
-        int ox[5], oy[5], oz[5];
-        const int nx = axis_offsets(g.nc[0], g.periodic[0], k[0], ox);
-        const int ny = axis_offsets(g.nc[1], g.periodic[1], k[1], oy);
-        const int nz = axis_offsets(g.nc[2], g.periodic[2], k[2], oz);
-        const double no_shift[3] = {0.0, 0.0, 0.0};
-        const double pt[3] = {me.x, me.y, me.z};
-        const bool all_x = g.periodic[0] && g.nc[0] < 2 * k[0] + 1;
-        const bool all_y = g.periodic[1] && g.nc[1] < 2 * k[1] + 1;
-        const bool all_z = g.periodic[2] && g.nc[2] < 2 * k[2] + 1;
-        int cnt = 0;
-        for (int f = sub; f < nx * ny * nz; f += kSweepGroup) {
-            const int c = f / (nx * ny), bb = (f / nx) % ny, a = f % nx;
-            bool okx = true, oky = true, okz = true;
-            const int zr = all_z ? oz[c] : myc[2] + oz[c];
-            const int z = all_z ? zr : wrap_or_clip(zr, g.nc[2], g.periodic[2], okz);
-            const int yr = all_y ? oy[bb] : myc[1] + oy[bb];
-            const int y = all_y ? yr : wrap_or_clip(yr, g.nc[1], g.periodic[1], oky);
-            const int xr = all_x ? ox[a] : myc[0] + ox[a];
-            const int x = all_x ? xr : wrap_or_clip(xr, g.nc[0], g.periodic[0], okx);
-            if (!okx || !oky || !okz) continue;
-            const int64_t cell = ((int64_t)z * g.nc[1] + y) * g.nc[0] + x;
-            int2 w = make_int2(cstart[cell], cend[cell]);
-            const bool direct = !all_x && !all_y && !all_z && x == xr && y == yr && z == zr;
-            if (direct && g.zbits > 0)
-                w = z_window_r(w, (uint32_t)x | ((uint32_t)y << 10) | ((uint32_t)z << 20), g, pt,
-                               pt, R, keys);
-            cnt += count_window<Periodic ? WRAP_PAIR : WRAP_NONE>(me, srec, w, (int)i, g,
-                                                                   no_shift);
+            for (int a = 0; a < 3; ++a) {
+                const double c = g.inv_s[a] * (1.0 + 1e-12);
+                // (an open axis of one cell holds every reach: no rebuild would
+                // give it a larger cell)
+                const bool holds = g.nc[a] == 1 && !g.periodic[a] ? R < INFINITY : R * c <= 2.0;
+                outgrown = outgrown || !holds;
+                if (!(Rc * c <= 2.0)) Rc = R;
+            }
+            if (outgrown) {
+                if (sub == 0) {
+                    atomicMin(&words[IT_STOP], (uint32_t)sweep);
+                    atomicOr(&words[IT_REACH], 1u);
+                }
+                break;
+            }
+            rc2 = Rc == R ? s2 : Rc * Rc;
+            const AxisCells X = axis_cells(g, 0, myc[0], me.x, Rc);
+            const AxisCells Y = axis_cells(g, 1, myc[1], me.y, Rc);
+            const AxisCells Z = axis_cells(g, 2, myc[2], me.z, Rc);
+            nlist = 0;
+            const int ncell = X.n * Y.n * Z.n;
+            for (int f0 = 0; f0 < ncell; f0 += kHLanes) {
+                // a cell's window per lane
+                const int f = f0 + sub;
+                int2 w = make_int2(0, 0);
+                if (f < ncell) {
+                    const int c = f / (X.n * Y.n), r = f - c * (X.n * Y.n), b = r / X.n;
+                    const int raw[3] = {X.first + r - b * X.n, Y.first + b, Z.first + c};
+                    bool ok[3] = {true, true, true};
+                    const int x = wrap_or_clip(raw[0], g.nc[0], g.periodic[0], ok[0]);
+                    const int y = wrap_or_clip(raw[1], g.nc[1], g.periodic[1], ok[1]);
+                    const int z = wrap_or_clip(raw[2], g.nc[2], g.periodic[2], ok[2]);
+                    if (ok[0] && ok[1] && ok[2]) {
+                        const int64_t cell = ((int64_t)z * g.nc[1] + y) * g.nc[0] + x;
+                        w = make_int2(cstart[cell], cend[cell]);
+                        const bool direct = !X.all && !Y.all && !Z.all && x == raw[0] &&
+                                            y == raw[1] && z == raw[2];
+                        if (direct && g.zbits > 0)
+                            w = sphere_window(w, x, y, z, g, pt, Rc, keys);
+                    }
+                }
+                uint32_t some = (uint32_t)(__ballot(w.x < w.y) >> gshift) & ((1u << kHLanes) - 1u);
+                while (some) {
+                    const int t = __builtin_ctz(some);
+                    some &= some - 1u;
+                    const int j1 = __shfl(w.y, t, kHLanes);
+                    for (int j0 = __shfl(w.x, t, kHLanes); j0 < j1; j0 += kHLanes) {
+                        const int j = j0 + sub;
+                        const SearchRec o = srec[j < j1 ? j : j0];
+                        double dx = me.x - o.x, dy = me.y - o.y, dz = me.z - o.z;
+                        if (Periodic) {
+                            if (g.periodic[0]) dx = min_image_sel(dx, g.len[0], g.half[0]);
+                            if (g.periodic[1]) dy = min_image_sel(dy, g.len[1], g.half[1]);
+                            if (g.periodic[2]) dz = min_image_sel(dz, g.len[2], g.half[2]);
+                        }
+                        const double r2 =
+                            __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
+                        const bool other = j < j1 && j != (int)i;
+                        cnt += other && r2 < s2 ? 1 : 0;
+                        const bool near = other && r2 < rc2;
+                        const uint32_t m =
+                            (uint32_t)(__ballot(near) >> gshift) & ((1u << kHLanes) - 1u);
+                        const int at = nlist + __popc(m & lt);
+                        if (near && at < kHList) list[at] = r2;
+                        nlist += __popc(m);
+                    }
+                }
+            }
+            if (nlist > kHList) rc2 = -1.0;  // did not fit: gather again next time
+            wave_sync();
         }
 #pragma unroll
-        for (int o = kSweepGroup / 2; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, kSweepGroup);
-        if (sub == 0) {
+        for (int o = kHLanes / 2; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, kHLanes);
+        if ((cnt >= lo_count && cnt <= hi_count) || sweep == max_iter) break;
+        hh = cnt == 0 ? 2.0 * hh : (hh * 0.5) * (1.0 + cbrt_newton(n_target / (double)cnt));
+        ++sweep;
+        run = sweep < stop;
+    }
+    if (active && sub == 0) {
+        if (redo) {
+            h[i] = hh;
+        } else {
+            tmp[i] = hh;
             count[i] = cnt;
-            if ((cnt < lo_count || cnt > hi_count) &&
-                __hip_atomic_load(&words[IT_BAD], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-                    0u)
-                atomicOr(&words[IT_BAD], 1u);
+            // (atomics on one word serialise in its L2 channel: only where it
+            // would grow)
+            if ((uint32_t)sweep >
+                __hip_atomic_load(&words[IT_SWEEP], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                atomicMax(&words[IT_SWEEP], (uint32_t)sweep);
         }
     }
 }
@@ -1376,8 +1302,6 @@ __global__ void clear_words_kernel(uint32_t *a, int k)
 {
     if ((int)threadIdx.x < k) a[threadIdx.x] = 0u;
 }
-
-__global__ void set_word_kernel(uint32_t *a, uint32_t v) { *a = v; }
 
 }  // namespace
 
@@ -1428,51 +1352,28 @@ hipError_t launch_max_h(sph_ctx ctx, const sph_particles &p, unsigned long long 
     return hipGetLastError();
 }
 
-static void launch_gather(sph_ctx ctx, const sph_particles &p, int32_t *count, int32_t lo_count,
-                   int32_t hi_count, uint32_t *words, unsigned blocks, int recount_all)
-{
-    const Grid &g = ctx->grid;
-    // the list kernel's grid: enough lane groups for the lists of the late
-    // sweeps (a few thousand particles), the rest loop. The list lives in
-    // the reorder scratch's id array (n_max entries), which no kernel uses
-    // between two cell builds.
-    const unsigned lblocks = std::min<unsigned>(blocks, 1024u);
-    if (g.periodic[0] || g.periodic[1] || g.periodic[2]) {
-        gather_count_kernel<true><<<blocks, 256, 0, ctx->stream>>>(
-            p.n, ctx->srec, ctx->sorted_keys, ctx->cell_start, ctx->cell_end, g, count,
-            lo_count, hi_count, words, recount_all);
-        gather_count_list_kernel<true><<<lblocks, 256, 0, ctx->stream>>>(
-            ctx->perm_tmp_id, ctx->srec, ctx->sorted_keys, ctx->cell_start, ctx->cell_end, g,
-            count, lo_count, hi_count, words);
-    } else {
-        gather_count_kernel<false><<<blocks, 256, 0, ctx->stream>>>(
-            p.n, ctx->srec, ctx->sorted_keys, ctx->cell_start, ctx->cell_end, g, count,
-            lo_count, hi_count, words, recount_all);
-        gather_count_list_kernel<false><<<lblocks, 256, 0, ctx->stream>>>(
-            ctx->perm_tmp_id, ctx->srec, ctx->sorted_keys, ctx->cell_start, ctx->cell_end, g,
-            count, lo_count, hi_count, words);
-    }
-}
-
 hipError_t launch_h_iteration(sph_ctx ctx, const sph_particles &p, int32_t *count,
                               int32_t lo_count, int32_t hi_count, double n_target,
                               int32_t first_sweep, int32_t max_iter, uint32_t *words)
 {
-    // words: IT_WORDS counters, cleared here; sweeps counted from first_sweep
-    clear_words_kernel<<<1, 64, 0, ctx->stream>>>(words, IT_WORDS);
-    set_word_kernel<<<1, 1, 0, ctx->stream>>>(words + IT_SWEEP, (uint32_t)first_sweep);
-    const unsigned blocks = (unsigned)((p.n + 255) / 256);
-    for (int32_t it = first_sweep; it <= max_iter; ++it) {
-        // the first sweep on these cells counts every particle (the counts
-        // in memory may belong to another order); later ones only recount
-        // the waves holding a particle whose h was just updated
-        launch_gather(ctx, p, count, lo_count, hi_count, words, blocks, it == first_sweep);
-        sweep_end_kernel<<<1, 1, 0, ctx->stream>>>(words, max_iter);
-        if (it < max_iter)
-            update_h_kernel<<<blocks, 256, 0, ctx->stream>>>(p.n, count, p.h, ctx->srec,
-                                                            lo_count, hi_count, n_target,
-                                                            words, ctx->perm_tmp_id);
+    // words: IT_WORDS counters; sweeps counted from first_sweep. The new h wait
+    // in the reorder scratch, which no kernel uses between two cell builds.
+    const Grid &g = ctx->grid;
+    const unsigned blocks = (unsigned)((p.n + 256 / kHLanes - 1) / (256 / kHLanes));
+    h_begin_kernel<<<1, 1, 0, ctx->stream>>>(words, first_sweep);
+    for (int redo = 0; redo < 2; ++redo) {
+        if (g.periodic[0] || g.periodic[1] || g.periodic[2])
+            h_iteration_kernel<true><<<blocks, 256, 0, ctx->stream>>>(
+                p.n, ctx->srec, ctx->sorted_keys, ctx->cell_start, ctx->cell_end, g, p.h,
+                ctx->perm_tmp, count, lo_count, hi_count, n_target, first_sweep, max_iter, words,
+                redo);
+        else
+            h_iteration_kernel<false><<<blocks, 256, 0, ctx->stream>>>(
+                p.n, ctx->srec, ctx->sorted_keys, ctx->cell_start, ctx->cell_end, g, p.h,
+                ctx->perm_tmp, count, lo_count, hi_count, n_target, first_sweep, max_iter, words,
+                redo);
     }
+    h_end_kernel<<<1, 1, 0, ctx->stream>>>(words);
     return hipGetLastError();
 }
 

@@ -340,7 +340,7 @@ struct sph_ctx_s {
     int64_t cell_cap = 0;
     double *cell_s2max = nullptr;    // per cell: largest (2h)^2 of its particles
     double *iad_c = nullptr;         // IAD matrices, 6 per particle (xx xy xz yy yz zz)
-    uint32_t *it_words = nullptr;    // h iteration: out-of-band count, largest count
+    uint32_t *it_words = nullptr;    // h iteration (kItWords)
     unsigned long long *it_hmax = nullptr;  // h iteration: largest h (bit pattern)
 
     sph::SearchRec *srec = nullptr;  // search records, cell order
@@ -477,10 +477,8 @@ Grid make_grid(const sph_box &b, double h_max, int64_t cell_cap, int max_axis);
 hipError_t launch_max_h(sph_ctx ctx, const sph_particles &p, unsigned long long *out);
 // Sweeps first_sweep..max_iter of the count-based h iteration on the cells
 // last built, on the device: counts, the band test and the h update, with no
-// host work between sweeps. words (kItWords): [0] nonzero when a particle
-// is outside the band, [1] length of the next sweep's list of particles
-// counted by lane groups, [2] done, [3] last sweep, [4] a particle outgrew
-// the cells (the host rebuilds and calls again from sweep [3]).
+// host work between sweeps. words (kItWords): [2] done, [3] last sweep, [4] a
+// particle outgrew the cells (the host rebuilds and calls again from sweep [3]).
 constexpr int kItWords = 5;
 // Reorders an int32 per-particle array as the last cell build reordered the
 // particles (its sort permutation).
