@@ -463,10 +463,10 @@ sph_status sph_ctx_check(sph_ctx ctx)
 
 namespace {
 
-// sph_build_cells, with up to 6 extra per-particle arrays reordered alongside and,
-// if kd.dt_dev is set, a kick-drift of the (not yet reordered) particles first.
+// sph_build_cells, with up to 10 extra per-particle arrays reordered alongside.
 sph_status build_cells(sph_ctx ctx, const sph_particles *p, const sph_box *box, double h_max,
-                       double *const *extra, int n_extra, const KickDrift &kd = KickDrift{})
+                       double *const *extra, int n_extra,
+                       const BuildWith &with = BuildWith{})
 {
     if (!ctx) return fail(nullptr, SPH_E_INVALID, "ctx is NULL");
     sph_status s;
@@ -480,7 +480,7 @@ sph_status build_cells(sph_ctx ctx, const sph_particles *p, const sph_box *box, 
     ctx->grid = make_grid(*box, h_max, ctx->cell_cap, kMaxAxisCells);
     ctx->n_built = p->n;
     if (p->n == 0) return SPH_OK;
-    SPH_HIP(ctx, launch_build_cells(ctx, *p, ctx->grid, h_max, extra, n_extra, kd));
+    SPH_HIP(ctx, launch_build_cells(ctx, *p, ctx->grid, h_max, extra, n_extra, with));
     return SPH_OK;
 }
 
@@ -525,8 +525,13 @@ sph_status sph_find_neighbors(sph_ctx ctx, const sph_particles *p, const sph_box
     return SPH_OK;
 }
 
-sph_status sph_density(sph_ctx ctx, const sph_particles *p, const sph_box *box,
-                       const sph_nbrs *nb, const sph_params *prm, double *rho)
+}  // extern "C"
+
+namespace {
+
+// sph_density; packed: the build has written the density records.
+sph_status density(sph_ctx ctx, const sph_particles *p, const sph_box *box, const sph_nbrs *nb,
+                   const sph_params *prm, double *rho, bool packed)
 {
     if (!ctx) return fail(nullptr, SPH_E_INVALID, "ctx is NULL");
     sph_status s;
@@ -541,8 +546,19 @@ sph_status sph_density(sph_ctx ctx, const sph_particles *p, const sph_box *box,
     const bool gve = prm->volume == SPH_VOLUME_GENERALISED;
     if (gve && !p->xw)
         return fail(ctx, SPH_E_INVALID, "generalised volume elements need p->xw");
-    SPH_HIP(ctx, launch_density(ctx, *p, *nb, prm->precision, kernel_sel(*prm), gve, rho));
+    SPH_HIP(ctx, launch_density(ctx, *p, *nb, prm->precision, kernel_sel(*prm), gve, rho,
+                                StepMask{}, packed));
     return SPH_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+sph_status sph_density(sph_ctx ctx, const sph_particles *p, const sph_box *box,
+                       const sph_nbrs *nb, const sph_params *prm, double *rho)
+{
+    return density(ctx, p, box, nb, prm, rho, false);
 }
 
 sph_status sph_density_noalloc(const sph_particles *p, const sph_box *box, const sph_nbrs *nb,
@@ -625,8 +641,13 @@ sph_status sph_gravity_tree(sph_ctx ctx, const sph_particles *p, double eps, dou
     return SPH_OK;
 }
 
-sph_status sph_eos(sph_ctx ctx, const sph_particles *p, const sph_params *prm,
-                   const sph_fields *f)
+}  // extern "C"
+
+namespace {
+
+// The checks of sph_eos.
+sph_status check_eos(sph_ctx ctx, const sph_particles *p, const sph_params *prm,
+                     const sph_fields *f)
 {
     if (!ctx) return fail(nullptr, SPH_E_INVALID, "ctx is NULL");
     sph_status s;
@@ -640,13 +661,12 @@ sph_status sph_eos(sph_ctx ctx, const sph_particles *p, const sph_params *prm,
         return fail(ctx, SPH_E_INVALID, "the Tait EOS needs rho_ref and p_bg");
     if (prm->eos == SPH_EOS_IDEAL && !p->u)
         return fail(ctx, SPH_E_INVALID, "the ideal-gas EOS needs u");
-    SPH_HIP(ctx, launch_eos(ctx, *p, *prm, *f));
     return SPH_OK;
 }
 
-sph_status sph_momentum_energy(sph_ctx ctx, const sph_particles *p, const sph_box *box,
-                               const sph_nbrs *nb, const sph_params *prm,
-                               const sph_fields *f, const sph_accel *a)
+// sph_momentum_energy; eos: after sph_eos (whose checks have passed).
+sph_status momentum(sph_ctx ctx, const sph_particles *p, const sph_box *box, const sph_nbrs *nb,
+                    const sph_params *prm, const sph_fields *f, const sph_accel *a, bool eos)
 {
     if (!ctx) return fail(nullptr, SPH_E_INVALID, "ctx is NULL");
     sph_status s;
@@ -662,8 +682,28 @@ sph_status sph_momentum_energy(sph_ctx ctx, const sph_particles *p, const sph_bo
         return fail(ctx, SPH_E_INVALID, "rho, c, pr2, ax, ay, az, dudt, mumax are required");
     if (prm->volume == SPH_VOLUME_GENERALISED && !p->xw)
         return fail(ctx, SPH_E_INVALID, "generalised volume elements need p->xw");
-    SPH_HIP(ctx, launch_momentum(ctx, *p, *nb, *prm, *f, *a));
+    SPH_HIP(ctx, launch_momentum(ctx, *p, *nb, *prm, *f, *a, eos));
     return SPH_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+sph_status sph_eos(sph_ctx ctx, const sph_particles *p, const sph_params *prm,
+                   const sph_fields *f)
+{
+    const sph_status s = check_eos(ctx, p, prm, f);
+    if (s != SPH_OK || p->n == 0) return s;
+    SPH_HIP(ctx, launch_eos(ctx, *p, *prm, *f));
+    return SPH_OK;
+}
+
+sph_status sph_momentum_energy(sph_ctx ctx, const sph_particles *p, const sph_box *box,
+                               const sph_nbrs *nb, const sph_params *prm,
+                               const sph_fields *f, const sph_accel *a)
+{
+    return momentum(ctx, p, box, nb, prm, f, a, false);
 }
 
 sph_status sph_integrate(sph_ctx ctx, const sph_particles *p, const sph_box *box,
@@ -675,9 +715,14 @@ sph_status sph_integrate(sph_ctx ctx, const sph_particles *p, const sph_box *box
     return SPH_OK;
 }
 
-sph_status sph_timestep(sph_ctx ctx, const sph_particles *p, const sph_params *prm,
-                        const sph_fields *f, const sph_accel *a, double *dt_dev,
-                        double *diag_dev)
+}  // extern "C"
+
+namespace {
+
+// sph_timestep; kick: after sph_integrate(SPH_KICK) (whose checks have passed).
+sph_status timestep(sph_ctx ctx, const sph_particles *p, const sph_params *prm,
+                    const sph_fields *f, const sph_accel *a, double *dt_dev, double *diag_dev,
+                    bool kick)
 {
     if (!ctx) return fail(nullptr, SPH_E_INVALID, "ctx is NULL");
     sph_status s;
@@ -686,8 +731,19 @@ sph_status sph_timestep(sph_ctx ctx, const sph_particles *p, const sph_params *p
     if (!f || !a || !dt_dev) return fail(ctx, SPH_E_INVALID, "fields, accel, dt_dev required");
     if (p->n > 0 && (!f->c || !a->ax || !a->ay || !a->az || !a->mumax))
         return fail(ctx, SPH_E_INVALID, "c, ax, ay, az, mumax are required");
-    SPH_HIP(ctx, launch_timestep(ctx, *p, *prm, *f, *a, dt_dev, diag_dev));
+    SPH_HIP(ctx, launch_timestep(ctx, *p, *prm, *f, *a, dt_dev, diag_dev, kick));
     return SPH_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+sph_status sph_timestep(sph_ctx ctx, const sph_particles *p, const sph_params *prm,
+                        const sph_fields *f, const sph_accel *a, double *dt_dev,
+                        double *diag_dev)
+{
+    return timestep(ctx, p, prm, f, a, dt_dev, diag_dev, false);
 }
 
 sph_status sph_init_forces(sph_ctx ctx, const sph_particles *p, const sph_box *box,
@@ -696,7 +752,9 @@ sph_status sph_init_forces(sph_ctx ctx, const sph_particles *p, const sph_box *b
                            double *dt_dev, double *diag_dev)
 {
     sph_status s;
-    if ((s = sph_build_cells(ctx, p, box, h_max)) != SPH_OK) return s;
+    BuildWith with;
+    with.dens = BuildWith::MASS;
+    if ((s = build_cells(ctx, p, box, h_max, nullptr, 0, with)) != SPH_OK) return s;
     if ((s = sph_find_neighbors(ctx, p, box, nb)) != SPH_OK) return s;
     if (!f) return fail(ctx, SPH_E_INVALID, "fields is NULL");
     if ((s = check_params(ctx, prm)) != SPH_OK) return s;
@@ -704,16 +762,18 @@ sph_status sph_init_forces(sph_ctx ctx, const sph_particles *p, const sph_box *b
         // no previous density yet: seed the weights from the standard one
         sph_params std_prm = *prm;
         std_prm.volume = SPH_VOLUME_STANDARD;
-        if ((s = sph_density(ctx, p, box, nb, &std_prm, f->rho)) != SPH_OK) return s;
+        if ((s = density(ctx, p, box, nb, &std_prm, f->rho, true)) != SPH_OK) return s;
         if ((s = sph_volume_weights(ctx, p, f->rho, prm->volume_p)) != SPH_OK) return s;
     }
-    if ((s = sph_density(ctx, p, box, nb, prm, f->rho)) != SPH_OK) return s;
+    if ((s = density(ctx, p, box, nb, prm, f->rho, prm->volume != SPH_VOLUME_GENERALISED)) !=
+        SPH_OK)
+        return s;
     if (set_rho_ref && p->n > 0) {
         if (!p->rho_ref) return fail(ctx, SPH_E_INVALID, "set_rho_ref needs rho_ref");
         SPH_HIP(ctx, launch_copy(ctx, p->rho_ref, f->rho, p->n));
     }
-    if ((s = sph_eos(ctx, p, prm, f)) != SPH_OK) return s;
-    if ((s = sph_momentum_energy(ctx, p, box, nb, prm, f, a)) != SPH_OK) return s;
+    if ((s = check_eos(ctx, p, prm, f)) != SPH_OK) return s;
+    if ((s = momentum(ctx, p, box, nb, prm, f, a, true)) != SPH_OK) return s;
     return sph_timestep(ctx, p, prm, f, a, dt_dev, diag_dev);
 }
 
@@ -730,19 +790,19 @@ sph_status sph_step(sph_ctx ctx, const sph_particles *p, const sph_box *box, dou
     if ((s = check_integrate(ctx, p, box, SPH_KICK_DRIFT, dt_dev, a)) != SPH_OK) return s;
     // the kick-drift is taken by the build's first kernel; where the build
     // refuses its arguments, by its own
-    if ((s = build_cells(ctx, p, box, h_max, nullptr, 0,
-                         KickDrift{dt_dev, a->ax, a->ay, a->az, a->dudt})) != SPH_OK) {
+    BuildWith with{dt_dev, a->ax, a->ay, a->az, a->dudt, BuildWith::MASS};
+    if (prm->volume == SPH_VOLUME_GENERALISED) with.dens = BuildWith::WEIGHT;
+    if ((s = build_cells(ctx, p, box, h_max, nullptr, 0, with)) != SPH_OK) {
         if (s != SPH_E_HIP && p->n > 0)
             SPH_HIP(ctx, launch_integrate(ctx, *p, box_grid(*box), SPH_KICK_DRIFT, dt_dev, *a));
         return s;
     }
     if ((s = sph_find_neighbors(ctx, p, box, nb)) != SPH_OK) return s;
     if (!f) return fail(ctx, SPH_E_INVALID, "fields is NULL");
-    if ((s = sph_density(ctx, p, box, nb, prm, f->rho)) != SPH_OK) return s;
-    if ((s = sph_eos(ctx, p, prm, f)) != SPH_OK) return s;
-    if ((s = sph_momentum_energy(ctx, p, box, nb, prm, f, a)) != SPH_OK) return s;
-    if ((s = sph_integrate(ctx, p, box, SPH_KICK, dt_dev, a)) != SPH_OK) return s;
-    return sph_timestep(ctx, p, prm, f, a, dt_dev, diag_dev);
+    if ((s = density(ctx, p, box, nb, prm, f->rho, true)) != SPH_OK) return s;
+    if ((s = check_eos(ctx, p, prm, f)) != SPH_OK) return s;
+    if ((s = momentum(ctx, p, box, nb, prm, f, a, true)) != SPH_OK) return s;
+    return timestep(ctx, p, prm, f, a, dt_dev, diag_dev, true);
 }
 
 sph_status sph_step_capture(sph_ctx ctx, const sph_particles *p, const sph_box *box,
@@ -844,12 +904,13 @@ sph_status sph_step_blocks(sph_ctx ctx, const sph_particles *p, const sph_box *b
         if (gve) SPH_HIP(ctx, launch_volume_weights(ctx, *p, f->rho, prm->volume_p));
         SPH_HIP(ctx, launch_kick_bins(ctx, *p, 0, sub, B, dt_dev, bin, *a));
         SPH_HIP(ctx, launch_drift(ctx, *p, box_grid(*box), B, dt_dev));
-        if ((s = build_cells(ctx, p, box, h_max, extra, 10)) != SPH_OK) return s;
+        BuildWith with;
+        with.dens = gve ? BuildWith::WEIGHT : BuildWith::MASS;
+        if ((s = build_cells(ctx, p, box, h_max, extra, 10, with)) != SPH_OK) return s;
         // lists, density and EOS only where a step closes; the others keep theirs
         SPH_HIP(ctx, launch_find_neighbors(ctx, *p, *nb, mask));
-        SPH_HIP(ctx, launch_density(ctx, *p, *nb, prm->precision, ks, gve, f->rho, mask));
-        SPH_HIP(ctx, launch_eos(ctx, *p, *prm, *f, mask));
-        SPH_HIP(ctx, launch_momentum(ctx, *p, *nb, *prm, *f, *a, bin, sub, B));
+        SPH_HIP(ctx, launch_density(ctx, *p, *nb, prm->precision, ks, gve, f->rho, mask, true));
+        SPH_HIP(ctx, launch_momentum(ctx, *p, *nb, *prm, *f, *a, true, bin, sub, B));
         SPH_HIP(ctx, launch_kick_bins(ctx, *p, 1, sub, B, dt_dev, bin, *a));
     }
     *substeps = 1 << B;

@@ -64,6 +64,7 @@ struct HistAt {
 struct BuildArrays {
     PermFields f;
     int h, g;               // index of h, and of gx (-1: absent)
+    int w;                  // index of the density records' weight (-1: no records)
     double *tmp;            // rows of `stride`
     int64_t stride;
     int32_t *tmp_id;
@@ -78,7 +79,7 @@ struct BuildArrays {
 // state.
 template <bool Drift, int Threads, int Items>
 __global__ void __launch_bounds__(Threads)
-build_head_kernel(int64_t n, BuildArrays A, Grid g, double h_max, KickDrift kd,
+build_head_kernel(int64_t n, BuildArrays A, Grid g, double h_max, BuildWith kd,
                   uint32_t *__restrict__ keys, uint32_t *__restrict__ hist, HistAt at,
                   uint32_t *__restrict__ flag_part, uint32_t *status, int64_t ncell,
                   int32_t *__restrict__ cstart, int32_t *__restrict__ cend,
@@ -529,7 +530,7 @@ permute_store_kernel(int64_t n, const int64_t *n_dev, int64_t stride, PermFields
 
 // Last kernel of a build: gathers every field from the scratch rows into the
 // caller's arrays in cell order, writes the search records (position and
-// (2h)^2) and the cell table (a particle whose predecessor lies in another cell
+// (2h)^2), the density records if asked for and the cell table (a particle whose predecessor lies in another cell
 // ends that one and starts its own; cells without particles stay empty). With
 // varying h also each cell's largest (2h)^2, as the ordered bit pattern of a
 // positive double: a segmented maximum over the wave's lanes (a cell's
@@ -537,7 +538,7 @@ permute_store_kernel(int64_t n, const int64_t *n_dev, int64_t stride, PermFields
 __global__ void __launch_bounds__(256)
 build_tail_kernel(int64_t n, const int32_t *__restrict__ perm, const uint32_t *__restrict__ keys,
                   BuildArrays A, Grid g, SearchRec *__restrict__ srec,
-                  int32_t *__restrict__ cstart, int32_t *__restrict__ cend,
+                  DensRec *__restrict__ drec, int32_t *__restrict__ cstart, int32_t *__restrict__ cend,
                   const uint32_t *__restrict__ hflag, unsigned long long *__restrict__ s2max)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -553,6 +554,7 @@ build_tail_kernel(int64_t n, const int32_t *__restrict__ perm, const uint32_t *_
     const int32_t id = A.tmp_id[j];
     const double s = 2.0 * A.tmp[A.h * A.stride + j];
     const double s2 = s * s;
+    const double dw = A.w >= 0 ? A.tmp[A.w * A.stride + j] : 0.0;
     auto cell = [&](uint32_t c) -> int64_t {
         return ((int64_t)compact3(c >> 2) * g.nc[1] + compact3(c >> 1)) * g.nc[0] + compact3(c);
     };
@@ -562,6 +564,7 @@ build_tail_kernel(int64_t n, const int32_t *__restrict__ perm, const uint32_t *_
             if (k < A.f.nf) A.f.f[k][i] = w[k];
         A.f.id[i] = id;
         srec[i] = SearchRec{w[0], w[1], w[2], s2};
+        if (A.w >= 0) drec[i] = DensRec{w[0], w[1], w[2], dw};
         const uint32_t pk = i > 0 ? keys[i - 1] >> g.zbits : 0u;
         if (i == 0 || pk != ck) {
             cstart[cell(ck)] = (int32_t)i;
@@ -772,7 +775,7 @@ hipError_t radix_sort_pairs(sph_ctx ctx, uint32_t *k[2], int32_t *v[2], int64_t 
 // (the drift included).
 hipError_t launch_build_cells(sph_ctx ctx, const sph_particles &p, const Grid &g,
                               double h_max, double *const *extra, int n_extra,
-                              const KickDrift &kd)
+                              const BuildWith &with)
 {
     const int64_t n = p.n;
     hipStream_t s = ctx->stream;
@@ -781,11 +784,13 @@ hipError_t launch_build_cells(sph_ctx ctx, const sph_particles &p, const Grid &g
     double *fields[kPermFields] = {p.x, p.y, p.z, p.vx, p.vy, p.vz, p.u, p.h, p.m,
                                    p.rho_ref, p.p_bg, p.gx, p.gy, p.gz, p.xw};
     for (int k = 0; k < n_extra && 15 + k < kPermFields; ++k) fields[15 + k] = extra[k];
-    A.h = A.g = -1;
+    A.h = A.g = A.w = -1;
     for (int k = 0; k < kPermFields; ++k) {
         if (!fields[k]) continue;
         if (k == 7) A.h = A.f.nf;
         if (k == 11) A.g = A.f.nf;
+        if ((k == 8 && with.dens == BuildWith::MASS) || (k == 14 && with.dens == BuildWith::WEIGHT))
+            A.w = A.f.nf;
         A.f.f[A.f.nf++] = fields[k];
     }
     A.f.id = p.id;
@@ -799,13 +804,13 @@ hipError_t launch_build_cells(sph_ctx ctx, const sph_particles &p, const Grid &g
     uint32_t *hist = small ? nullptr : ctx->hist;
     unsigned nb = (unsigned)sp.tiles;
 #define SPH_HEAD_D(D, T, I)                                                                \
-    build_head_kernel<D, T, I><<<nb, T, 0, s>>>(n, A, g, h_max, kd, ctx->keys[0], hist,    \
+    build_head_kernel<D, T, I><<<nb, T, 0, s>>>(n, A, g, h_max, with, ctx->keys[0], hist,  \
                                                 sp.at(), ctx->flag_part,                   \
                                                 ctx->status_dev, ncell, ctx->cell_start,   \
                                                 ctx->cell_end, s2max)
 #define SPH_HEAD(T, I)                                                                     \
     do {                                                                                   \
-        if (kd.dt_dev) SPH_HEAD_D(true, T, I);                                             \
+        if (with.dt_dev) SPH_HEAD_D(true, T, I);                                           \
         else SPH_HEAD_D(false, T, I);                                                      \
     } while (0)
     if (small) {
@@ -837,7 +842,7 @@ hipError_t launch_build_cells(sph_ctx ctx, const sph_particles &p, const Grid &g
     }
     ctx->sorted_keys = ctx->keys[cur];
     build_tail_kernel<<<blocks_for(n, 256), 256, 0, s>>>(n, ctx->vals[cur], ctx->sorted_keys, A, g,
-                                                         ctx->srec, ctx->cell_start,
+                                                         ctx->srec, ctx->drec, ctx->cell_start,
                                                          ctx->cell_end, ctx->hflag_dev, s2max);
     return hipGetLastError();
 }

@@ -506,32 +506,42 @@ gve_density_kernel(int64_t n, const double *__restrict__ m, const double *__rest
 }
 
 // ---------------------------------------------------------------------------
-// EOS.
+// EOS: pressure P, sound speed C and P / rho^2 of a particle from its density r.
+struct EosArgs {
+    int eos;
+    double rho0, c0, gamma_tait, gamma_gas;
+    const double *u, *rho_ref, *p_bg;
+    double *p, *c, *pr2;
+};
+
+__device__ __forceinline__ void eos_point(const EosArgs &E, int64_t i, double r, double &C,
+                                          double &PR2)
+{
+    double P;
+    if (E.eos == SPH_EOS_TAIT) {
+        const double B = E.rho0 * E.c0 * E.c0 / E.gamma_tait;
+        const double xr = r / E.rho_ref[i];
+        const double x2 = xr * xr, x4 = x2 * x2, x6 = x4 * x2, x7 = x6 * xr;
+        const double x3 = x2 * xr;
+        P = E.p_bg[i] + B * (x7 - 1.0);
+        C = E.c0 * x3;
+    } else {
+        P = (E.gamma_gas - 1.0) * r * E.u[i];
+        C = sqrt(E.gamma_gas * (E.gamma_gas - 1.0) * E.u[i]);
+    }
+    PR2 = P / (r * r);
+    E.p[i] = P;
+    E.c[i] = C;
+    E.pr2[i] = PR2;
+}
+
 __global__ void __launch_bounds__(256)
-eos_kernel(int64_t n, int eos, double rho0, double c0, double gamma_tait,
-           double gamma_gas, const double *__restrict__ rho, const double *__restrict__ u,
-           const double *__restrict__ rho_ref, const double *__restrict__ p_bg,
-           double *__restrict__ p, double *__restrict__ c, double *__restrict__ pr2,
-           StepMask mask)
+eos_kernel(int64_t n, EosArgs E, const double *__restrict__ rho, StepMask mask)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n || !step_closes(mask, i)) return;
-    const double r = rho[i];
-    double P, C;
-    if (eos == SPH_EOS_TAIT) {
-        const double B = rho0 * c0 * c0 / gamma_tait;
-        const double xr = r / rho_ref[i];
-        const double x2 = xr * xr, x4 = x2 * x2, x6 = x4 * x2, x7 = x6 * xr;
-        const double x3 = x2 * xr;
-        P = p_bg[i] + B * (x7 - 1.0);
-        C = c0 * x3;
-    } else {
-        P = (gamma_gas - 1.0) * r * u[i];
-        C = sqrt(gamma_gas * (gamma_gas - 1.0) * u[i]);
-    }
-    p[i] = P;
-    c[i] = C;
-    pr2[i] = P / (r * r);
+    double C, PR2;
+    eos_point(E, i, rho[i], C, PR2);
 }
 
 // ---------------------------------------------------------------------------
@@ -1036,16 +1046,18 @@ momentum_kernel(int64_t n, int64_t ld, const PairRec *__restrict__ rec,
 // generalised volume elements (xw not null) {X, Q = m^2 (P/rho^2) / X}.
 // R32 (the FP32-pair form, kernel derivatives): PairRec32 records, the
 // fields after the position and velocity rounded to FP32 (1/h from the FP64
-// h, Q from the FP64 fields).
-template <bool R32>
+// h, Q from the FP64 fields). Eos: P, c and P/rho^2 of the particles whose step
+// closes are formed here (c and pr2 hold the others'), which saves a launch and a
+// pass over rho, c and pr2.
+template <bool R32, bool Eos>
 __global__ void __launch_bounds__(256)
 pack_pair_kernel(int64_t n, const int64_t *n_dev, const double *__restrict__ x,
                  const double *__restrict__ y, const double *__restrict__ z,
                  const double *__restrict__ vx, const double *__restrict__ vy,
                  const double *__restrict__ vz, const double *__restrict__ h,
                  const double *__restrict__ m, const double *__restrict__ rho,
-                 const double *__restrict__ c, const double *__restrict__ pr2,
-                 const double *__restrict__ xw, void *__restrict__ out)
+                 const double *c, const double *pr2, const double *__restrict__ xw,
+                 void *__restrict__ out, EosArgs E, StepMask mask)
 {
     // Each wave forms the records of 64 consecutive particles in LDS (one
     // per lane, stride 17 doubles), then stores them as 16-byte chunks with
@@ -1070,16 +1082,24 @@ pack_pair_kernel(int64_t n, const int64_t *n_dev, const double *__restrict__ x,
             double *r = buf + lane * kStride;
             r[0] = x[i]; r[1] = y[i]; r[2] = z[i];
             r[3] = vx[i]; r[4] = vy[i]; r[5] = vz[i];
-            const double q = xw ? m[i] * m[i] * pr2[i] / xw[i] : 0.0;
+            double ci, pri;
+            const double rhoi = rho[i];
+            if (Eos && step_closes(mask, i)) {
+                eos_point(E, i, rhoi, ci, pri);
+            } else {
+                ci = c[i];
+                pri = pr2[i];
+            }
+            const double q = xw ? m[i] * m[i] * pri / xw[i] : 0.0;
             if constexpr (R32) {
                 float *f = reinterpret_cast<float *>(r + 6);
                 f[0] = (float)hi; f[1] = (float)(1.0 / hi); f[2] = (float)m[i];
-                f[3] = (float)rho[i]; f[4] = (float)c[i]; f[5] = (float)pr2[i];
+                f[3] = (float)rhoi; f[4] = (float)ci; f[5] = (float)pri;
                 f[6] = xw ? (float)xw[i] : 0.0f;
                 f[7] = (float)q;
             } else {
                 r[6] = hi; r[7] = 1.0 / hi; r[8] = m[i];
-                r[9] = rho[i]; r[10] = c[i]; r[11] = pr2[i];
+                r[9] = rhoi; r[10] = ci; r[11] = pri;
                 if (xw) {
                     r[12] = xw[i];
                     r[13] = q;
@@ -1282,14 +1302,15 @@ void momentum_launch(hipStream_t st, unsigned blocks, int precision, bool big, i
 
 hipError_t launch_density(sph_ctx ctx, const sph_particles &p, const sph_nbrs &nb,
                           int precision, const KernelSel &ks, bool gve, double *rho,
-                          const StepMask &mask)
+                          const StepMask &mask, bool packed)
 {
     const int split = split_of(p.n);
     const unsigned nblk = pair_blocks(p.n, split);
     // generalised volume elements: the records carry X in place of m, the
     // kernel leaves k_i in rho, which is then scaled by m_i / X_i
-    pack_dens_kernel<<<blocks_for(p.n, 256), 256, 0, ctx->stream>>>(
-        p.n, nullptr, p.x, p.y, p.z, gve ? p.xw : p.m, ctx->drec);
+    if (!packed)
+        pack_dens_kernel<<<blocks_for(p.n, 256), 256, 0, ctx->stream>>>(
+            p.n, nullptr, p.x, p.y, p.z, gve ? p.xw : p.m, ctx->drec);
     const int tk = ktime_begin(ctx, TK_DENSITY);
     density_launch<false>(ctx->stream, nblk, precision, big_records(p.n, sizeof(DensRec)), split, p.n,
                           p.n, ctx->drec, p.h, nb.count, nb.idx, nb.max_nb, ctx->grid, rho,
@@ -1359,18 +1380,23 @@ hipError_t launch_volume_weights(sph_ctx ctx, const sph_particles &p, const doub
     return hipGetLastError();
 }
 
+static EosArgs eos_args(const sph_particles &p, const sph_params &prm, const sph_fields &f)
+{
+    return EosArgs{prm.eos, prm.rho0, prm.c0, prm.gamma_tait, prm.gamma_gas, p.u, p.rho_ref,
+                   p.p_bg, f.p, f.c, f.pr2};
+}
+
 hipError_t launch_eos(sph_ctx ctx, const sph_particles &p, const sph_params &prm,
                       const sph_fields &f, const StepMask &mask)
 {
-    eos_kernel<<<blocks_for(p.n, 256), 256, 0, ctx->stream>>>(
-        p.n, prm.eos, prm.rho0, prm.c0, prm.gamma_tait, prm.gamma_gas, f.rho, p.u, p.rho_ref,
-        p.p_bg, f.p, f.c, f.pr2, mask);
+    eos_kernel<<<blocks_for(p.n, 256), 256, 0, ctx->stream>>>(p.n, eos_args(p, prm, f), f.rho,
+                                                              mask);
     return hipGetLastError();
 }
 
 hipError_t launch_momentum(sph_ctx ctx, const sph_particles &p, const sph_nbrs &nb,
                            const sph_params &prm, const sph_fields &f, const sph_accel &a,
-                           const double *bin, int sub, int B)
+                           bool eos, const double *bin, int sub, int B)
 {
     const KernelSel ks = kernel_sel(prm);
     const bool iad = prm.gradient == SPH_GRAD_IAD;
@@ -1393,14 +1419,20 @@ hipError_t launch_momentum(sph_ctx ctx, const sph_particles &p, const sph_nbrs &
     const bool gve = prm.volume == SPH_VOLUME_GENERALISED;
     const int split = iad || gve ? 1 : split_of(p.n);
     const bool r32 = prm.precision == SPH_FP32_PAIR && !iad;  // PairRec32 records
-    if (r32)
-        pack_pair_kernel<true><<<blocks_for(p.n, 256), 256, 0, ctx->stream>>>(
-            p.n, nullptr, p.x, p.y, p.z, p.vx, p.vy, p.vz, p.h, p.m, f.rho, f.c, f.pr2,
-            gve ? p.xw : nullptr, ctx->prec);
-    else
-        pack_pair_kernel<false><<<blocks_for(p.n, 256), 256, 0, ctx->stream>>>(
-            p.n, nullptr, p.x, p.y, p.z, p.vx, p.vy, p.vz, p.h, p.m, f.rho, f.c, f.pr2,
-            gve ? p.xw : nullptr, ctx->prec);
+    const EosArgs E = eos ? eos_args(p, prm, f) : EosArgs{};
+    const StepMask mask{bin, sub, B};
+#define SPH_PACK(R, E_)                                                                    \
+    pack_pair_kernel<R, E_><<<blocks_for(p.n, 256), 256, 0, ctx->stream>>>(                \
+        p.n, nullptr, p.x, p.y, p.z, p.vx, p.vy, p.vz, p.h, p.m, f.rho, f.c, f.pr2,        \
+        gve ? p.xw : nullptr, ctx->prec, E, mask)
+    if (r32) {
+        if (eos) SPH_PACK(true, true);
+        else SPH_PACK(true, false);
+    } else {
+        if (eos) SPH_PACK(false, true);
+        else SPH_PACK(false, false);
+    }
+#undef SPH_PACK
     const int tk = ktime_begin(ctx, TK_MOMENTUM);
     momentum_launch<false>(ctx->stream, pair_blocks(p.n, split), prm.precision,
                            big_records(p.n, r32 ? sizeof(PairRec32) : sizeof(PairRec)), split,
@@ -1453,13 +1485,15 @@ hipError_t launch_momentum_batch(sph_ctx ctx, const BatchDev &b, int precision,
     const unsigned g2 = ens_pair_blocks(cap);
     const bool r32 = precision == SPH_FP32_PAIR;  // PairRec32 records
     if (r32)
-        pack_pair_kernel<true><<<g1, 256, 0, ctx->stream>>>(
+        pack_pair_kernel<true, false><<<g1, 256, 0, ctx->stream>>>(
             0, n_out, F + 0 * cap, F + 1 * cap, F + 2 * cap, F + 3 * cap, F + 4 * cap,
-            F + 5 * cap, F + 7 * cap, F + 8 * cap, rho, c, pr2, nullptr, ctx->prec);
+            F + 5 * cap, F + 7 * cap, F + 8 * cap, rho, c, pr2, nullptr, ctx->prec, EosArgs{},
+            StepMask{});
     else
-        pack_pair_kernel<false><<<g1, 256, 0, ctx->stream>>>(
+        pack_pair_kernel<false, false><<<g1, 256, 0, ctx->stream>>>(
             0, n_out, F + 0 * cap, F + 1 * cap, F + 2 * cap, F + 3 * cap, F + 4 * cap,
-            F + 5 * cap, F + 7 * cap, F + 8 * cap, rho, c, pr2, nullptr, ctx->prec);
+            F + 5 * cap, F + 7 * cap, F + 8 * cap, rho, c, pr2, nullptr, ctx->prec, EosArgs{},
+            StepMask{});
     momentum_launch<true>(ctx->stream, g2, precision,
                           big_records(cap, r32 ? sizeof(PairRec32) : sizeof(PairRec)), 1, 0, cap,
                           ctx->prec, count, idx, max_nb, Grid{}, MomParams{}, ax, ay, az, dudt,

@@ -395,15 +395,17 @@ namespace sph {
 // Launchers (defined in the .hip files); each returns hipSuccess or the
 // launch error.
 // extra: up to 10 more per-particle FP64 arrays reordered with the particles.
-// kd: the particles take a kick-drift with the dt in device memory first
-// (sph_integrate(SPH_KICK_DRIFT), in the build's first kernel).
-struct KickDrift {
-    const double *dt_dev = nullptr;
+// with: what the build does besides, on its way over the particles: a kick-drift
+// with the dt in device memory before the sort (sph_integrate(SPH_KICK_DRIFT)), and
+// the density records {x, y, z, w} after it, w = m or the volume weights xw.
+struct BuildWith {
+    const double *dt_dev = nullptr;  // (null: no kick-drift)
     const double *ax = nullptr, *ay = nullptr, *az = nullptr, *dudt = nullptr;
+    enum { NONE, MASS, WEIGHT } dens = NONE;
 };
 hipError_t launch_build_cells(sph_ctx ctx, const sph_particles &p, const Grid &g,
                               double h_max, double *const *extra = nullptr, int n_extra = 0,
-                              const KickDrift &kd = KickDrift{});
+                              const BuildWith &with = BuildWith{});
 hipError_t launch_find_neighbors(sph_ctx ctx, const sph_particles &p,
                                  const sph_nbrs &nb, const StepMask &mask = StepMask{});
 // The interpolation kernel of a pair call: family (SPH_KERNEL_*), sinc
@@ -415,10 +417,11 @@ struct KernelSel {
 };
 KernelSel kernel_sel(const sph_params &prm);
 
-// gve: generalised volume elements with the weights p.xw.
+// gve: generalised volume elements with the weights p.xw. packed: the build has
+// written the density records (BuildWith).
 hipError_t launch_density(sph_ctx ctx, const sph_particles &p, const sph_nbrs &nb,
                           int precision, const KernelSel &ks, bool gve, double *rho,
-                          const StepMask &mask = StepMask{});
+                          const StepMask &mask = StepMask{}, bool packed = false);
 hipError_t launch_volume_weights(sph_ctx ctx, const sph_particles &p, const double *rho,
                                  double exponent);
 // The density without allocation: the device address of the static record
@@ -447,16 +450,18 @@ hipError_t radix_sort_pairs(sph_ctx ctx, uint32_t *k[2], int32_t *v[2], int64_t 
 hipError_t launch_eos(sph_ctx ctx, const sph_particles &p, const sph_params &prm,
                       const sph_fields &f, const StepMask &mask = StepMask{});
 // bin (not null): only the particles whose step closes at substep sub of
-// 2^B get new accelerations (individual time steps).
+// 2^B get new accelerations (individual time steps). eos: the pair records' pass
+// forms pressure and sound speed first, as launch_eos with the same bins does.
 hipError_t launch_momentum(sph_ctx ctx, const sph_particles &p, const sph_nbrs &nb,
                            const sph_params &prm, const sph_fields &f,
-                           const sph_accel &a, const double *bin = nullptr, int sub = 0,
-                           int B = 0);
+                           const sph_accel &a, bool eos = false, const double *bin = nullptr,
+                           int sub = 0, int B = 0);
 hipError_t launch_integrate(sph_ctx ctx, const sph_particles &p, const Grid &g,
                             int stage, const double *dt_dev, const sph_accel &a);
+// kick: the second half kick (sph_integrate(SPH_KICK)) first, in the same pass.
 hipError_t launch_timestep(sph_ctx ctx, const sph_particles &p,
                            const sph_params &prm, const sph_fields &f,
-                           const sph_accel &a, double *dt_dev, double *diag_dev);
+                           const sph_accel &a, double *dt_dev, double *diag_dev, bool kick = false);
 hipError_t launch_copy(sph_ctx ctx, double *dst, const double *src, int64_t n);
 // Individual time steps: per-particle criterion, the largest step D into
 // dt_dev[0], the bins into bin (as doubles) and the deepest bin into

@@ -1,5 +1,7 @@
 """The cell build at the edges of its sorts: one block, tiles of every size,
 and more tiles than a block adds up by itself."""
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -87,6 +89,58 @@ def test_step_is_its_parts(n_side, nz, gravity):
                 S.sph_density(ctx, st, prm)
                 S.sph_eos(ctx, st, prm)
                 S.sph_momentum_energy(ctx, st, prm)
+                S.sph_integrate(ctx, st, S.SPH_KICK)
+                S.sph_timestep(ctx, st, prm)
+            else:
+                S.sph_step(ctx, st, prm)
+        S.sph_ctx_check(ctx)
+        o = st.host(original_order=False)
+        o["dt"], o["diag"] = st.dt, st.diag
+        out.append(o)
+    for k in out[0]:
+        assert np.array_equal(out[0][k], out[1][k], equal_nan=True), k
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("volume,gradient", [(0, 0), (1, 0), (0, 1), (1, 1)])
+def test_step_options_are_their_parts(volume, gradient, precision):
+    """The same with the ideal gas, uneven h and the options of the pair sums;
+    the first forces too."""
+    ic = I.evrard(5000, seed=2)
+    prm = S.make_params(dataclasses.replace(ic.params, volume=volume, gradient=gradient),
+                        precision)
+    ic.params.volume = volume  # (the state carries the weights)
+    out = []
+    print(f"step options volume={volume} gradient={gradient} precision={precision}", flush=True)
+    for parts in (False, True):
+        ctx = S.Context(ic.n, 512)
+        st = S.SphState(ic, 512)
+
+        def forces(first):
+            S.sph_find_neighbors(ctx, st)
+            if volume and first:
+                std = S.make_params(dataclasses.replace(ic.params, volume=0), precision)
+                S.sph_density(ctx, st, std)
+                S.sph_volume_weights(ctx, st, ic.params.volume_p)
+            S.sph_density(ctx, st, prm)
+            if first:
+                st.t["rho_ref"].copy_(st.t["rho"][: ic.n])
+            S.sph_eos(ctx, st, prm)
+            S.sph_momentum_energy(ctx, st, prm)
+
+        if parts:
+            S.sph_build_cells(ctx, st)
+            forces(True)
+            S.sph_timestep(ctx, st, prm)
+        else:
+            S.sph_init_forces(ctx, st, prm)
+        for _ in range(2):
+            if parts:
+                if volume:
+                    S.sph_volume_weights(ctx, st, ic.params.volume_p)
+                S.sph_integrate(ctx, st, S.SPH_KICK_DRIFT)
+                S.sph_build_cells(ctx, st)
+                forces(False)
                 S.sph_integrate(ctx, st, S.SPH_KICK)
                 S.sph_timestep(ctx, st, prm)
             else:
