@@ -362,7 +362,7 @@ sph_status sph_ctx_create(sph_ctx *out, int64_t n_max, int32_t max_nb, sph_strea
     ctx->stream = (hipStream_t)stream;
     ctx->n_max = n_max;
     ctx->max_nb = max_nb;
-    ctx->scan_len_max = sort_tiles_max(n_max) * kRadixBins;
+    ctx->scan_len_max = sort_counts_max(n_max);
     ctx->cell_cap = std::max<int64_t>(n_max / 8 + 64, 65536);
     sph_status s = SPH_OK;
 #define ALLOC(ptr, count)                                   \
@@ -373,7 +373,7 @@ sph_status sph_ctx_create(sph_ctx *out, int64_t n_max, int32_t max_nb, sph_strea
     ALLOC(ctx->vals[1], n_max);
     ALLOC(ctx->hist, ctx->scan_len_max);
     ALLOC(ctx->scan_part, (ctx->scan_len_max + kScanChunk - 1) / kScanChunk + 1);
-    ALLOC(ctx->flag_part, sort_tiles_max(n_max) + kSortSmall / 256);
+    ALLOC(ctx->flag_part, sort_tiles_max(n_max));
     ALLOC(ctx->cell_start, ctx->cell_cap);
     ALLOC(ctx->cell_end, ctx->cell_cap);
     ALLOC(ctx->cell_s2max, ctx->cell_cap);

@@ -77,7 +77,7 @@ struct BuildArrays {
 // table, flags h > h_max and notes whether some h differs from h[0]. Drift: the
 // particles take their kick-drift on the way, which saves a pass over the
 // state.
-template <bool Drift, int Threads, int Items>
+template <bool Drift, int Threads, int Items, int Bits>
 __global__ void __launch_bounds__(Threads)
 build_head_kernel(int64_t n, BuildArrays A, Grid g, double h_max, BuildWith kd,
                   uint32_t *__restrict__ keys, uint32_t *__restrict__ hist, HistAt at,
@@ -86,9 +86,10 @@ build_head_kernel(int64_t n, BuildArrays A, Grid g, double h_max, BuildWith kd,
                   unsigned long long *__restrict__ s2max)
 {
     constexpr int kFirst = 11;  // fields in flight together: x .. p_bg
-    __shared__ uint32_t cnt[kRadixBins];
+    constexpr int kBins = 1 << Bits;
+    __shared__ uint32_t cnt[kBins];
     const int tid = threadIdx.x;
-    if (tid < kRadixBins) cnt[tid] = 0;
+    if (tid < kBins) cnt[tid] = 0;
     for (int64_t c = (int64_t)blockIdx.x * Threads + tid; c < ncell;
          c += (int64_t)gridDim.x * Threads) {
         cstart[c] = 0;
@@ -140,7 +141,7 @@ build_head_kernel(int64_t n, BuildArrays A, Grid g, double h_max, BuildWith kd,
         const uint32_t key =
             ((spread3(cx) | (spread3(cy) << 1) | (spread3(cz) << 2)) << g.zbits) | zq;
         keys[i] = key;
-        atomicAdd(&cnt[key & (kRadixBins - 1)], 1u);
+        atomicAdd(&cnt[key & (kBins - 1)], 1u);
 #pragma unroll 4
         for (int k = kFirst; k < A.f.nf; ++k) A.tmp[k * A.stride + i] = A.f.f[k][i];
     }
@@ -150,133 +151,30 @@ build_head_kernel(int64_t n, BuildArrays A, Grid g, double h_max, BuildWith kd,
         flag_part[blockIdx.x] = any_differs ? 1u : 0u;
         if (any_above) atomicOr(status, ST_DOMAIN);
     }
-    if (hist && tid < kRadixBins) hist[at(tid, blockIdx.x)] = cnt[tid];
-}
-
-// Sorts n <= 1024 Items keys in one block: stable LSD passes of 8 bits with the
-// keys and their indices in registers, exchanged through LDS. Each wave takes a
-// contiguous run of the keys and ranks it 64 at a time (one ballot per digit
-// bit matches the lanes of equal digits) against its own digit counts, so the
-// order within a digit is kept and a pass has four barriers. Also reduces the
-// first kernel's h flags.
-template <int Items>
-__global__ void __launch_bounds__(1024)
-sort_small_kernel(int n, int key_bits, const uint32_t *__restrict__ kin,
-                  uint32_t *__restrict__ kout, int32_t *__restrict__ vout, int nflag,
-                  const uint32_t *__restrict__ flag_part, uint32_t *__restrict__ hflag)
-{
-    constexpr int kWaves = 16;
-    __shared__ uint32_t kbuf[1024 * Items];
-    __shared__ uint16_t vbuf[1024 * Items];
-    __shared__ uint32_t wcnt[kWaves][kRadixBins];
-    __shared__ uint32_t wtot[4];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int any = __syncthreads_or(tid < nflag && flag_part[tid] != 0u);
-    if (tid == 0) hflag[0] = any ? 1u : 0u;
-    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-    const int base = wave * (64 * Items) + lane;
-    uint32_t key[Items];
-    uint32_t val[Items];
-#pragma unroll
-    for (int it = 0; it < Items; ++it) {
-        const int i = base + it * 64;
-        key[it] = i < n ? kin[i] : 0xffffffffu;
-        val[it] = (uint32_t)i;
-    }
-    for (int shift = 0; shift < key_bits; shift += kRadixBits) {
-        const int bits = min(kRadixBits, key_bits - shift);  // (no key has more)
-        for (int d = lane; d < kRadixBins; d += 64) wcnt[wave][d] = 0;
-        uint32_t at[Items];  // rank within the wave's keys of the same digit
-#pragma unroll
-        for (int it = 0; it < Items; ++it) {
-            const bool valid = base + it * 64 < n;  // (the invalid ones stay at the end)
-            const uint32_t d = (key[it] >> shift) & (kRadixBins - 1);
-            uint64_t same = __ballot(valid);
-            for (int b = 0; b < bits; ++b) {
-                const bool bit = (d >> b) & 1u;
-                const uint64_t ones = __ballot(bit);
-                same &= bit ? ones : ~ones;
-            }
-            const uint32_t rank = __popcll(same & lt);
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            const uint32_t before = wcnt[wave][d];
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            if (valid && rank == 0) wcnt[wave][d] = before + __popcll(same);
-            at[it] = before + rank;
-        }
-        __syncthreads();
-        // first position of each (digit, wave)
-        uint32_t run = 0, tot = 0;
-        if (tid < kRadixBins) {
-            for (int w = 0; w < kWaves; ++w) {
-                const uint32_t c = wcnt[w][tid];
-                wcnt[w][tid] = tot;
-                tot += c;
-            }
-            run = tot;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const uint32_t t = __shfl_up(run, o, 64);
-                if (lane >= o) run += t;
-            }
-            if (lane == 63) wtot[wave] = run;
-        }
-        __syncthreads();
-        if (tid < kRadixBins) {
-            uint32_t first = run - tot;
-            for (int w = 0; w < wave; ++w) first += wtot[w];
-            for (int w = 0; w < kWaves; ++w) wcnt[w][tid] += first;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int it = 0; it < Items; ++it) {
-            if (base + it * 64 < n) {
-                const uint32_t d = (key[it] >> shift) & (kRadixBins - 1);
-                const uint32_t pos = wcnt[wave][d] + at[it];
-                kbuf[pos] = key[it];
-                vbuf[pos] = (uint16_t)val[it];
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int it = 0; it < Items; ++it) {
-            const int i = base + it * 64;
-            if (i < n) {
-                key[it] = kbuf[i];
-                val[it] = vbuf[i];
-            }
-        }
-    }
-#pragma unroll
-    for (int it = 0; it < Items; ++it) {
-        const int i = base + it * 64;
-        if (i < n) {
-            kout[i] = key[it];
-            vout[i] = (int32_t)val[it];
-        }
-    }
+    if (tid < kBins) hist[at(tid, blockIdx.x)] = cnt[tid];
 }
 
 // Per-tile digit histogram.
-template <int Threads, int Items>
+template <int Threads, int Items, int Bits>
 __global__ void __launch_bounds__(Threads)
 radix_hist_kernel(const uint32_t *__restrict__ keys, int64_t n, const int64_t *n_dev, int shift,
                   uint32_t *__restrict__ hist, HistAt at)
 {
-    __shared__ uint32_t cnt[kRadixBins];
+    constexpr int kBins = 1 << Bits;
+    __shared__ uint32_t cnt[kBins];
     if (n_dev) n = *n_dev;
     const int tid = threadIdx.x;
     const int64_t base = (int64_t)blockIdx.x * (Threads * Items);
     if (base >= n && at.digit == 1) return;  // (the scatter skips these tiles)
-    if (tid < kRadixBins) cnt[tid] = 0;
+    if (tid < kBins) cnt[tid] = 0;
     __syncthreads();
 #pragma unroll
     for (int it = 0; it < Items; ++it) {
         const int64_t i = base + it * Threads + tid;
-        if (i < n) atomicAdd(&cnt[(keys[i] >> shift) & (kRadixBins - 1)], 1u);
+        if (i < n) atomicAdd(&cnt[(keys[i] >> shift) & (kBins - 1)], 1u);
     }
     __syncthreads();
-    if (tid < kRadixBins) hist[at(tid, blockIdx.x)] = cnt[tid];
+    if (tid < kBins) hist[at(tid, blockIdx.x)] = cnt[tid];
 }
 
 // Block-wide exclusive scan of one value per thread (256 threads, wave64).
@@ -367,9 +265,10 @@ scan_down_kernel(uint32_t *__restrict__ a, int64_t len,
 // up into the offsets it needs; else they have been scanned (digit-major). vin
 // null: the values are the indices. flag_part (not null): block 0 also reduces
 // the build's h flags into hflag.
-// A pass over 1M keys takes 18.5 us in 2 launches (33 in 5 with the scan), over
-// 104,000 12 us (28); a launch alone is 4.5.
-template <int Threads, int Items, bool Self>
+// A pass over 1M keys takes 18.7 us in 2 launches (33 in 5 with the scan), over
+// 104,000 10.4 us (28), of which the scatter 5.9; blocks of 256 threads, with four
+// waves to add up the counts, took 7.7.
+template <int Threads, int Items, bool Self, int Bits>
 __global__ void __launch_bounds__(Threads)
 radix_scatter_kernel(const uint32_t *__restrict__ kin, const int32_t *__restrict__ vin,
                      int64_t n, const int64_t *n_dev, int shift, int bits,
@@ -380,9 +279,9 @@ radix_scatter_kernel(const uint32_t *__restrict__ kin, const int32_t *__restrict
     if (n_dev) n = *n_dev;
     const int64_t tile0 = (int64_t)blockIdx.x * (Threads * Items);
     if (tile0 >= n) return;
-    constexpr int kWaves = Threads / 64;
-    __shared__ uint32_t wcnt[kWaves][kRadixBins];
-    __shared__ uint32_t base[kRadixBins];
+    constexpr int kWaves = Threads / 64, kBins = 1 << Bits, kQuads = kBins / 256;
+    __shared__ uint32_t wcnt[kWaves][kBins];
+    __shared__ uint32_t base[kBins];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (flag_part && blockIdx.x == 0) {
         bool f = false;
@@ -402,29 +301,32 @@ radix_scatter_kernel(const uint32_t *__restrict__ kin, const int32_t *__restrict
     }
     if constexpr (Self) {
         // every wave adds up its share of the tiles, four digits a lane
-        __shared__ uint32_t wbefore[kWaves][kRadixBins];
-        __shared__ uint32_t wsum[4];
-        const uint4 *row = reinterpret_cast<const uint4 *>(hist) + lane;
-        uint4 total = {0, 0, 0, 0}, before = {0, 0, 0, 0};
+        __shared__ uint32_t wbefore[kWaves][kBins];
+        __shared__ uint32_t wsum[kBins / 64];
         const int live = (int)((n + Threads * Items - 1) / (Threads * Items));
+#pragma unroll
+        for (int k = 0; k < kQuads; ++k) {
+            const uint4 *row = reinterpret_cast<const uint4 *>(hist) + 64 * k + lane;
+            uint4 total = {0, 0, 0, 0}, before = {0, 0, 0, 0};
 #pragma unroll 8
-        for (int t = wave; t < live; t += kWaves) {
-            const uint4 c = row[t * (kRadixBins / 4)];
-            const uint32_t m = t < (int)blockIdx.x ? ~0u : 0u;
-            total.x += c.x;
-            total.y += c.y;
-            total.z += c.z;
-            total.w += c.w;
-            before.x += c.x & m;
-            before.y += c.y & m;
-            before.z += c.z & m;
-            before.w += c.w & m;
+            for (int t = wave; t < live; t += kWaves) {
+                const uint4 c = row[t * (kBins / 4)];
+                const uint32_t m = t < (int)blockIdx.x ? ~0u : 0u;
+                total.x += c.x;
+                total.y += c.y;
+                total.z += c.z;
+                total.w += c.w;
+                before.x += c.x & m;
+                before.y += c.y & m;
+                before.z += c.z & m;
+                before.w += c.w & m;
+            }
+            reinterpret_cast<uint4 *>(wcnt[wave])[64 * k + lane] = total;
+            reinterpret_cast<uint4 *>(wbefore[wave])[64 * k + lane] = before;
         }
-        reinterpret_cast<uint4 *>(wcnt[wave])[lane] = total;
-        reinterpret_cast<uint4 *>(wbefore[wave])[lane] = before;
         __syncthreads();
         uint32_t sum = 0, off = 0, run = 0;
-        if (tid < kRadixBins) {
+        if (tid < kBins) {
 #pragma unroll
             for (int w = 0; w < kWaves; ++w) {
                 sum += wcnt[w][tid];
@@ -440,21 +342,21 @@ radix_scatter_kernel(const uint32_t *__restrict__ kin, const int32_t *__restrict
             if (lane == 63) wsum[wave] = run;
         }
         __syncthreads();
-        if (tid < kRadixBins) {
+        if (tid < kBins) {
             off += run - sum;
             for (int w = 0; w < wave; ++w) off += wsum[w];
             base[tid] = off;
         }
     } else {
-        for (int d = lane; d < kRadixBins; d += 64) wcnt[wave][d] = 0;
-        if (tid < kRadixBins) base[tid] = hist[(int64_t)tid * tiles + blockIdx.x];
+        for (int d = lane; d < kBins; d += 64) wcnt[wave][d] = 0;
+        if (tid < kBins) base[tid] = hist[(int64_t)tid * tiles + blockIdx.x];
     }
     const uint64_t lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     uint32_t at[Items];  // rank within the wave's keys of the same digit
 #pragma unroll
     for (int it = 0; it < Items; ++it) {
         const bool valid = first + it * 64 < n;
-        const uint32_t d = (key[it] >> shift) & (kRadixBins - 1);
+        const uint32_t d = (key[it] >> shift) & (kBins - 1);
         uint64_t same = __ballot(valid);
         for (int b = 0; b < bits; ++b) {
             const bool bit = (d >> b) & 1u;
@@ -470,7 +372,7 @@ radix_scatter_kernel(const uint32_t *__restrict__ kin, const int32_t *__restrict
     }
     __syncthreads();
     // first position of each (digit, wave)
-    if (tid < kRadixBins) {
+    if (tid < kBins) {
         uint32_t run = base[tid];
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) {
@@ -483,7 +385,7 @@ radix_scatter_kernel(const uint32_t *__restrict__ kin, const int32_t *__restrict
 #pragma unroll
     for (int it = 0; it < Items; ++it) {
         if (first + it * 64 < n) {
-            const uint32_t pos = wcnt[wave][(key[it] >> shift) & (kRadixBins - 1)] + at[it];
+            const uint32_t pos = wcnt[wave][(key[it] >> shift) & (kBins - 1)] + at[it];
             kout[pos] = key[it];
             vout[pos] = val[it];
         }
@@ -686,33 +588,39 @@ hipError_t exclusive_scan(sph_ctx ctx, uint32_t *a, int64_t len)
     return hipGetLastError();
 }
 
-// Tiles of a sort of up to n keys: the smallest of 256 x 2, 256 x 4, 512 x 4 and
+// Tiles of a sort of up to n keys: the smallest of 512 x 1, 1024 x 1, 1024 x 2 and
 // 1024 x 4 keys (threads x keys of one) that give at most kSortSelfTiles of
-// them, as small tiles keep more of the chip busy; the largest beyond.
+// them, as small tiles keep more of the chip busy; the largest beyond. Digits of 9
+// bits where they save a pass of 8 and the tiles are few: a block then reads at
+// most 128 KB of counts (a pass of 8,000 keys takes two launches, 7 us).
 struct SortPlan {
-    int tile;
+    int tile, bits;
     int64_t tiles;
     bool self;
-    HistAt at() const { return self ? HistAt{1, kRadixBins} : HistAt{tiles, 1}; }
+    HistAt at() const { return self ? HistAt{1, 1 << bits} : HistAt{tiles, 1}; }
 };
 
-SortPlan sort_plan(int64_t n)
+SortPlan sort_plan(int64_t n, int key_bits)
 {
-    SortPlan p{kSortTileMin, 0, true};
+    SortPlan p{kSortTileMin, kRadixBits, 0, true};
     while ((p.tiles = (n + p.tile - 1) / p.tile) > kSortSelfTiles && p.tile < kSortTile)
         p.tile *= 2;
     p.self = p.tiles <= kSortSelfTiles;
+    if (p.tiles <= kSortWideTiles && (key_bits + 8) / 9 < (key_bits + 7) / 8) p.bits = 9;
     return p;
 }
 
-// CALL(threads, items) for a plan's tile
-#define SPH_SORT_TILE(tile, CALL)                                                          \
+// CALL(threads, items, bits) for a plan
+#define SPH_SORT_TILE(sp, CALL)                                                            \
     do {                                                                                   \
-        switch (tile) {                                                                    \
-        case 512: CALL(256, 2); break;                                                     \
-        case 1024: CALL(256, 4); break;                                                    \
-        case 2048: CALL(512, 4); break;                                                    \
-        default: CALL(1024, 4); break;                                                     \
+        switch ((sp).tile) {                                                               \
+        case 512:                                                                          \
+            if ((sp).bits == 9) CALL(512, 1, 9);                                           \
+            else CALL(512, 1, 8);                                                          \
+            break;                                                                         \
+        case 1024: CALL(1024, 1, 8); break;                                                \
+        case 2048: CALL(1024, 2, 8); break;                                                \
+        default: CALL(1024, 4, 8); break;                                                  \
         }                                                                                  \
     } while (0)
 
@@ -726,29 +634,29 @@ hipError_t sort_passes(sph_ctx ctx, uint32_t *const k[2], int32_t *const v[2], i
     hipStream_t s = ctx->stream;
     const unsigned nb = (unsigned)sp.tiles;
     hipError_t e;
-    for (int shift = 0; shift < key_bits; shift += kRadixBits) {
+    for (int shift = 0; shift < key_bits; shift += sp.bits) {
         const bool head = shift == 0;
-        const int bits = std::min(kRadixBits, key_bits - shift);
+        const int bits = std::min(sp.bits, key_bits - shift);
         if (!(head && counted)) {
-#define SPH_HIST(T, I)                                                                     \
-    radix_hist_kernel<T, I><<<nb, T, 0, s>>>(k[*cur], n, n_dev, shift, ctx->hist, sp.at())
-            SPH_SORT_TILE(sp.tile, SPH_HIST);
+#define SPH_HIST(T, I, B)                                                                  \
+    radix_hist_kernel<T, I, B><<<nb, T, 0, s>>>(k[*cur], n, n_dev, shift, ctx->hist, sp.at())
+            SPH_SORT_TILE(sp, SPH_HIST);
 #undef SPH_HIST
             if ((e = hipGetLastError()) != hipSuccess) return e;
         }
         const int32_t *vin = head && identity ? nullptr : v[*cur];
         const uint32_t *fp = head && flags ? ctx->flag_part : nullptr;
         if (sp.self) {
-#define SPH_SCATTER(T, I)                                                                  \
-    radix_scatter_kernel<T, I, true><<<nb, T, 0, s>>>(                                     \
+#define SPH_SCATTER(T, I, B)                                                               \
+    radix_scatter_kernel<T, I, true, B><<<nb, T, 0, s>>>(                                  \
         k[*cur], vin, n, n_dev, shift, bits, ctx->hist, sp.tiles, k[*cur ^ 1],             \
         v[*cur ^ 1], fp, ctx->hflag_dev)
-            SPH_SORT_TILE(sp.tile, SPH_SCATTER);
+            SPH_SORT_TILE(sp, SPH_SCATTER);
 #undef SPH_SCATTER
         } else {
             if ((e = exclusive_scan(ctx, ctx->hist, sp.tiles * kRadixBins)) != hipSuccess)
                 return e;
-            radix_scatter_kernel<1024, 4, false><<<nb, 1024, 0, s>>>(
+            radix_scatter_kernel<1024, 4, false, 8><<<nb, 1024, 0, s>>>(
                 k[*cur], vin, n, n_dev, shift, bits, ctx->hist, sp.tiles, k[*cur ^ 1],
                 v[*cur ^ 1], fp, ctx->hflag_dev);
         }
@@ -763,16 +671,17 @@ hipError_t sort_passes(sph_ctx ctx, uint32_t *const k[2], int32_t *const v[2], i
 hipError_t radix_sort_pairs(sph_ctx ctx, uint32_t *k[2], int32_t *v[2], int64_t n,
                             int key_bits, int *cur)
 {
-    return sort_passes(ctx, k, v, n, nullptr, key_bits, sort_plan(n), false, false, false, cur);
+    return sort_passes(ctx, k, v, n, nullptr, key_bits, sort_plan(n, key_bits), false, false, false, cur);
 }
 
 // A build is: the head kernel (scratch copies, keys, first digit counts), the
-// sort (one block for a small run, else count and scatter per 8 bits), and the
-// tail kernel (gather, search records, cell table). Bound by launches up to
-// 100,000 particles (no kernel is under 4.5 us here) and by the two passes over
-// the state, 92 B each way a particle, beyond. 21 launches before: 8,000
-// particles 101 -> 31 us in 3, 104,000 127 -> 49 us in 7, 1M 234 -> 143 us in 7
-// (the drift included).
+// sort's passes (count and scatter, the first without its count), and the tail
+// kernel (gather, search records, cell table). Bound by launches up to 100,000
+// particles (no kernel is under 2 to 4.5 us here) and by the two passes over the
+// state, 92 B each way a particle, beyond. With the drift (and the density
+// records) a build of 8,000 particles takes 26 us in 5 launches, of 104,000 45 us
+// and of 1M 154 us in 7; in the 21 launches of one kernel per job 101, 127 and 234.
+// A sort of up to 12,288 keys in one block's LDS took 20 us (bound by its one CU).
 hipError_t launch_build_cells(sph_ctx ctx, const sph_particles &p, const Grid &g,
                               double h_max, double *const *extra, int n_extra,
                               const BuildWith &with)
@@ -799,47 +708,25 @@ hipError_t launch_build_cells(sph_ctx ctx, const sph_particles &p, const Grid &g
     A.tmp_id = ctx->perm_tmp_id;
     unsigned long long *s2max = reinterpret_cast<unsigned long long *>(ctx->cell_s2max);
     const int key_bits = std::max(1, 3 * g.bits + g.zbits);
-    const bool small = n <= kSortSmall;
-    const SortPlan sp = sort_plan(n);
-    uint32_t *hist = small ? nullptr : ctx->hist;
-    unsigned nb = (unsigned)sp.tiles;
-#define SPH_HEAD_D(D, T, I)                                                                \
-    build_head_kernel<D, T, I><<<nb, T, 0, s>>>(n, A, g, h_max, with, ctx->keys[0], hist,  \
-                                                sp.at(), ctx->flag_part,                   \
-                                                ctx->status_dev, ncell, ctx->cell_start,   \
-                                                ctx->cell_end, s2max)
-#define SPH_HEAD(T, I)                                                                     \
+    const SortPlan sp = sort_plan(n, key_bits);
+#define SPH_HEAD_D(D, T, I, B)                                                             \
+    build_head_kernel<D, T, I, B><<<(unsigned)sp.tiles, T, 0, s>>>(                        \
+        n, A, g, h_max, with, ctx->keys[0], ctx->hist, sp.at(), ctx->flag_part,            \
+        ctx->status_dev, ncell, ctx->cell_start, ctx->cell_end, s2max)
+#define SPH_HEAD(T, I, B)                                                                  \
     do {                                                                                   \
-        if (with.dt_dev) SPH_HEAD_D(true, T, I);                                           \
-        else SPH_HEAD_D(false, T, I);                                                      \
+        if (with.dt_dev) SPH_HEAD_D(true, T, I, B);                                        \
+        else SPH_HEAD_D(false, T, I, B);                                                   \
     } while (0)
-    if (small) {
-        nb = (unsigned)blocks_for(n, 256);
-        SPH_HEAD(256, 1);
-    } else {
-        SPH_SORT_TILE(sp.tile, SPH_HEAD);
-    }
+    SPH_SORT_TILE(sp, SPH_HEAD);
 #undef SPH_HEAD_D
 #undef SPH_HEAD
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     int cur = 0;
-    if (small) {
-#define SPH_SMALL(I)                                                                       \
-    sort_small_kernel<I><<<1, 1024, 0, s>>>((int)n, key_bits, ctx->keys[0], ctx->keys[1],  \
-                                            ctx->vals[1], (int)nb, ctx->flag_part,   \
-                                            ctx->hflag_dev)
-        if (n <= 2 * 1024) SPH_SMALL(2);
-        else if (n <= 4 * 1024) SPH_SMALL(4);
-        else if (n <= 8 * 1024) SPH_SMALL(8);
-        else SPH_SMALL(12);
-#undef SPH_SMALL
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        cur = 1;
-    } else if ((e = sort_passes(ctx, ctx->keys, ctx->vals, n, nullptr, key_bits, sp, true, true,
-                                true, &cur)) != hipSuccess) {
+    if ((e = sort_passes(ctx, ctx->keys, ctx->vals, n, nullptr, key_bits, sp, true, true, true,
+                         &cur)) != hipSuccess)
         return e;
-    }
     ctx->sorted_keys = ctx->keys[cur];
     build_tail_kernel<<<blocks_for(n, 256), 256, 0, s>>>(n, ctx->vals[cur], ctx->sorted_keys, A, g,
                                                          ctx->srec, ctx->drec, ctx->cell_start,
@@ -890,7 +777,7 @@ hipError_t launch_build_cells_batch(sph_ctx ctx, const BatchDev &b, double *F, i
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     int cur = 0;
-    if ((e = sort_passes(ctx, ctx->keys, ctx->vals, cap, n_in, kEnsKeyBits, sort_plan(cap), true,
+    if ((e = sort_passes(ctx, ctx->keys, ctx->vals, cap, n_in, kEnsKeyBits, sort_plan(cap, kEnsKeyBits), true,
                          false, false, &cur)) != hipSuccess)
         return e;
     ctx->sorted_keys = ctx->keys[cur];

@@ -27,15 +27,19 @@ constexpr int kSortTile = 4096;                        // keys per tile, at most
 // Up to this many tiles, every scatter block works its offsets out from the
 // tiles' digit counts itself; beyond, a scan over all of them does (3 launches).
 constexpr int kSortSelfTiles = 256;
-// Up to this many keys, one block sorts them all in LDS.
-constexpr int kSortSmall = 12 * 1024;
+constexpr int kSortWideTiles = 64;                     // digits of 9 bits up to this many
 constexpr int kSortTileMin = 512;                      // keys per tile of the smallest sorts
 // Most tiles of a sort of up to n keys (the fewest keys for which the tiles are
-// not yet doubled have the most); each has a count of every digit.
+// not yet doubled have the most), and the most counts.
 inline int64_t sort_tiles_max(int64_t n)
 {
     auto tiles = [&](int64_t tile) { return (n + tile - 1) / tile; };
     return std::max(std::min<int64_t>(kSortSelfTiles, tiles(kSortTileMin)), tiles(kSortTile));
+}
+inline int64_t sort_counts_max(int64_t n)
+{
+    const int64_t t = sort_tiles_max(n);
+    return std::max(t * kRadixBins, std::min<int64_t>(t, kSortWideTiles) * 2 * kRadixBins);
 }
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 16;
@@ -328,7 +332,7 @@ struct sph_ctx_s {
     // radix sort
     uint32_t *keys[2] = {nullptr, nullptr};
     int32_t *vals[2] = {nullptr, nullptr};
-    uint32_t *hist = nullptr;        // kRadixBins * tiles_max
+    uint32_t *hist = nullptr;        // sort_counts_max(n_max) digit counts
     uint32_t *scan_part = nullptr;   // block partials of the scan
     int64_t scan_len_max = 0;
     uint32_t *flag_part = nullptr;   // per block of the build's first kernel: some h differs

@@ -1,5 +1,5 @@
-"""The cell build at the edges of its sorts: one block, tiles of every size,
-and more tiles than a block adds up by itself."""
+"""The cell build at the edges of its sorts: tiles of every size, and more
+tiles than a block adds up by itself."""
 import dataclasses
 
 import numpy as np
@@ -36,9 +36,10 @@ def _sites(n, spread):
     return ic, site
 
 
-# one block of 1024 keys times 2, 4, 8 and 12; tiles of 512, 1024, 2048 and
-# 4096 keys (256 of each); more tiles
-SIZES = [1, 2, 255, 256, 257, 2048, 2049, 4097, 8193, 12287, 12288, 12289,
+# tiles of 512 keys, up to 64 with digits of 9 bits; of 512, 1024, 2048 and 4096
+# keys (256 of each); more tiles
+SIZES = [1, 2, 255, 256, 257, 511, 512, 513, 2048, 2049, 4097, 8193, 12287, 12288, 12289,
+         32767, 32768, 32769,
          131072, 131073, 262144, 262145, 524288, 524289, 1048576, 1048577, 1100000]
 
 
