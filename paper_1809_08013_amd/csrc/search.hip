@@ -63,6 +63,7 @@ constexpr int kWave = 64;
 //   W = 1: one wave does a tile. 22 blocks = 1,408 candidates (the mean union
 //          of the 1M patch is 1,150) leave 11 tiles on a CU.
 //   W = 4: four waves share one, for runs too small to fill the chip.
+//   W = 16: sixteen, for the smallest.
 template <int W>
 struct SearchShape;
 template <>
@@ -74,6 +75,10 @@ template <>
 struct SearchShape<4> {
     static constexpr int kMaxDist = 18, kEntries = 512, kCells = 486, kBlocks = 28;
     typedef uint16_t Cell;
+};
+template <>
+struct SearchShape<16> : SearchShape<4> {
+    static constexpr int kEntries = 1024;
 };
 enum WrapMode { WRAP_NONE = 0, WRAP_CELL = 1, WRAP_PAIR = 2 };
 
@@ -1306,8 +1311,11 @@ __global__ void clear_words_kernel(uint32_t *a, int k)
 }  // namespace
 
 // Waves per tile of the search: four while the tiles would leave most of the
-// chip's 1,024 SIMDs with less than two waves each.
-constexpr int64_t kSharedTiles = 2048;
+// chip's 1,024 SIMDs with less than two waves each, sixteen while they would leave
+// most of the CUs without one. 4, 8 and 16 waves: 8,000 particles 40.4, 37.1, 36.4
+// us, 15,600: 42.7, 41.8, 41.6, 32,800: 53, 54, 75. (A tile's union and the first
+// load of its candidates come one after the other whatever the waves.)
+constexpr int64_t kCuTiles = 256, kSharedTiles = 2048;
 
 hipError_t launch_find_neighbors(sph_ctx ctx, const sph_particles &p, const sph_nbrs &nb,
                                  const StepMask &mask)
@@ -1321,7 +1329,8 @@ hipError_t launch_find_neighbors(sph_ctx ctx, const sph_particles &p, const sph_
         p.n, p.n, ctx->srec, ctx->sorted_keys, ctx->cell_start, ctx->cell_end, ctx->grid,  \
         nb.max_nb, nb.count, nb.idx, ctx->hflag_dev, ctx->status_dev, BatchDev{},          \
         mask, s2max)
-    if (tiles <= kSharedTiles) SPH_SEARCH(4);
+    if (tiles <= kCuTiles) SPH_SEARCH(16);
+    else if (tiles <= kSharedTiles) SPH_SEARCH(4);
     else SPH_SEARCH(1);
 #undef SPH_SEARCH
     ktime_end(ctx, tk);

@@ -53,8 +53,16 @@ def _lattice(jitter):
 
 
 CASES = {
-    # sizes around a tile, with four waves on each tile
+    # sizes around a tile, with sixteen waves on each tile
     **{f"n_{n}": (lambda n=n: _cloud(n, min(40, n)), 512) for n in (1, 63, 64, 65, 129)},
+    # either side of the line between sixteen waves and four per tile
+    "cu_tiles": (lambda: _cloud(16384, 60, 0.3), 256),
+    "more_tiles": (lambda: _cloud(16385, 60, 0.3), 256),
+    # four waves: unions of several chunks, images, few rows
+    "shared_several_chunks": (lambda: _cloud(20000, 700, 0.2), 2048),
+    "shared_chunks_uniform": (lambda: _cloud(20000, 900, 0.0, (0, 1, 0)), 2048),
+    "shared_box": (lambda: _short_box(5, (1, 1, 1), 0.3, 17000), 1024),
+    "shared_short_lists": (lambda: _cloud(17000, 80, 0.2), 24),
     # either side of the line between four waves and one wave per tile
     "shared_tiles": (lambda: _cloud(131072, 40, 0.3), 256),
     "single_tiles": (lambda: _cloud(131073, 40, 0.3), 256),
