@@ -387,7 +387,7 @@ sph_status sph_ctx_create(sph_ctx *out, int64_t n_max, int32_t max_nb, sph_strea
     ALLOC(ctx->perm_tmp_id, n_max);
     ALLOC(ctx->red_part, (int64_t)kRedFields * kRedMaxBlocks);
     ALLOC(ctx->dtc, n_max);
-    ALLOC(ctx->blk_words, 2);
+    ALLOC(ctx->blk_words, kBlockWords);
     ALLOC(ctx->status_dev, 1);
     ALLOC(ctx->hflag_dev, 1);
 #undef ALLOC
@@ -871,7 +871,7 @@ sph_status sph_step_blocks(sph_ctx ctx, const sph_particles *p, const sph_box *b
     if ((s = check_box(ctx, box)) != SPH_OK) return s;
     if ((s = check_nbrs(ctx, nb, p->n)) != SPH_OK) return s;
     if ((s = check_params(ctx, prm)) != SPH_OK) return s;
-    if (max_bin < 0 || max_bin > 16)
+    if (max_bin < 0 || max_bin >= kMaxBins)
         return fail(ctx, SPH_E_INVALID, "max_bin %d outside [0, 16]", max_bin);
     if (!f || !a || !dt_dev || !substeps)
         return fail(ctx, SPH_E_INVALID, "fields, accel, dt_dev and substeps are required");
@@ -888,7 +888,7 @@ sph_status sph_step_blocks(sph_ctx ctx, const sph_particles *p, const sph_box *b
     if (prm->eos == SPH_EOS_TAIT && (!p->rho_ref || !p->p_bg))
         return fail(ctx, SPH_E_INVALID, "the Tait EOS needs rho_ref and p_bg");
     SPH_HIP(ctx, launch_block_bins(ctx, *p, *prm, *f, *a, max_bin, bin, dt_dev));
-    uint32_t words[2] = {0, 0};
+    uint32_t words[kBlockWords] = {};
     SPH_HIP(ctx, hipMemcpyAsync(words, ctx->blk_words, sizeof words, hipMemcpyDeviceToHost,
                                 ctx->stream));
     SPH_HIP(ctx, hipStreamSynchronize(ctx->stream));
@@ -900,7 +900,9 @@ sph_status sph_step_blocks(sph_ctx ctx, const sph_particles *p, const sph_box *b
     const bool gve = prm->volume == SPH_VOLUME_GENERALISED;
     const KernelSel ks = kernel_sel(*prm);
     for (int sub = 0; sub < (1 << B); ++sub) {
-        const StepMask mask{bin, sub, B};
+        StepMask mask{bin, sub, B, 0};
+        for (int b = 0; b <= B; ++b)
+            if (((sub + 1) & ((1 << (B - b)) - 1)) == 0) mask.active += words[1 + b];
         if (gve) SPH_HIP(ctx, launch_volume_weights(ctx, *p, f->rho, prm->volume_p));
         SPH_HIP(ctx, launch_kick_bins(ctx, *p, 0, sub, B, dt_dev, bin, *a));
         SPH_HIP(ctx, launch_drift(ctx, *p, box_grid(*box), B, dt_dev));
@@ -910,7 +912,7 @@ sph_status sph_step_blocks(sph_ctx ctx, const sph_particles *p, const sph_box *b
         // lists, density and EOS only where a step closes; the others keep theirs
         SPH_HIP(ctx, launch_find_neighbors(ctx, *p, *nb, mask));
         SPH_HIP(ctx, launch_density(ctx, *p, *nb, prm->precision, ks, gve, f->rho, mask, true));
-        SPH_HIP(ctx, launch_momentum(ctx, *p, *nb, *prm, *f, *a, true, bin, sub, B));
+        SPH_HIP(ctx, launch_momentum(ctx, *p, *nb, *prm, *f, *a, true, mask));
         SPH_HIP(ctx, launch_kick_bins(ctx, *p, 1, sub, B, dt_dev, bin, *a));
     }
     *substeps = 1 << B;

@@ -382,35 +382,44 @@ block_step_kernel(int nblk, const double *__restrict__ part, int max_bin,
     if (threadIdx.x == 0) dt_dev[0] = fmin(mx, ldexp(mn, max_bin));
 }
 
+// words: [0] the deepest bin, [1 + b] particles of bin b. (One atomic per block
+// and bin, from at most kRedMaxBlocks blocks: they serialise in their L2 channel.)
 __global__ void __launch_bounds__(256)
 block_bins_kernel(int64_t n, const double *__restrict__ dtc, int max_bin,
                   const double *__restrict__ dt_dev, double *__restrict__ bin,
                   uint32_t *__restrict__ words)
 {
+    __shared__ uint32_t cnt[kMaxBins];
+    if (threadIdx.x < kMaxBins) cnt[threadIdx.x] = 0u;
+    __syncthreads();
     const double D = dt_dev[0];
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int b = 0;
-    if (i < n) {
-        b = max_bin;
-        for (int k = max_bin; k >= 0; --k)
-            if (ldexp(D, -k) <= dtc[i]) b = k;
-        bin[i] = (double)b;
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i0 = (int64_t)blockIdx.x * blockDim.x; i0 < n; i0 += step) {
+        const int64_t i = i0 + threadIdx.x;
+        int b = -1;
+        if (i < n) {
+            b = max_bin;
+            const double c = dtc[i];
+            for (int k = max_bin; k >= 0; --k)
+                if (ldexp(D, -k) <= c) b = k;
+            bin[i] = (double)b;
+        }
+        for (int k = 0; k <= max_bin; ++k) {
+            const uint32_t m = (uint32_t)__popcll(__ballot(b == k));
+            if ((threadIdx.x & 63) == 0 && m) atomicAdd(&cnt[k], m);
+        }
     }
-    // deepest bin: one atomic per wave (every lane takes part in the
-    // reduction), and only above the value already there (same-address
-    // atomics serialise in their L2 channel)
-    int m = b;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
-    if ((threadIdx.x & 63) == 0 &&
-        (uint32_t)m > __hip_atomic_load(&words[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-        atomicMax(&words[0], (uint32_t)m);
+    __syncthreads();
+    if (threadIdx.x < kMaxBins && cnt[threadIdx.x]) {
+        atomicAdd(&words[1 + threadIdx.x], cnt[threadIdx.x]);
+        atomicMax(&words[0], threadIdx.x);
+    }
 }
 
 __global__ void __launch_bounds__(64)
-clear_words2_kernel(uint32_t *__restrict__ w)
+clear_block_words_kernel(uint32_t *__restrict__ w)
 {
-    if (threadIdx.x < 2) w[threadIdx.x] = 0u;
+    if (threadIdx.x < kBlockWords) w[threadIdx.x] = 0u;
 }
 
 // Half kick of the particles of bin b whose step opens (stage 0: sub mod
@@ -517,12 +526,12 @@ hipError_t launch_block_bins(sph_ctx ctx, const sph_particles &p, const sph_para
                              double *dt_dev)
 {
     const int nblk = (int)std::min<int64_t>(kRedMaxBlocks, (p.n + 255) / 256);
-    clear_words2_kernel<<<1, 64, 0, ctx->stream>>>(ctx->blk_words);
+    clear_block_words_kernel<<<1, 64, 0, ctx->stream>>>(ctx->blk_words);
     block_criterion_kernel<<<(unsigned)nblk, 256, 0, ctx->stream>>>(
         p.n, p.h, f.c, a.mumax, a.ax, a.ay, a.az, p.gx, p.gy, p.gz, prm.alpha, prm.beta,
         prm.c_cfl, prm.c_force, ctx->dtc, ctx->red_part);
     block_step_kernel<<<1, 64, 0, ctx->stream>>>(nblk, ctx->red_part, max_bin, dt_dev);
-    block_bins_kernel<<<blocks_for(p.n, 256), 256, 0, ctx->stream>>>(
+    block_bins_kernel<<<(unsigned)nblk, 256, 0, ctx->stream>>>(
         p.n, ctx->dtc, max_bin, dt_dev, bin, ctx->blk_words);
     return hipGetLastError();
 }

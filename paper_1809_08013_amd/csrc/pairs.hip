@@ -1217,10 +1217,21 @@ eos_batch_kernel(BatchDev b, const double *__restrict__ rho, const double *__res
 // Record arrays of 4 GiB or more need 64-bit element offsets.
 inline bool big_records(int64_t n, size_t rec) { return (uint64_t)n * rec >= (1ull << 32); }
 
-// Lanes per particle of a single run's gathers. (Records of 4 GiB do not occur
-// at the sizes that are split.)
-inline int split_of(int64_t n) { return n <= kSplit16Max ? 16 : (n <= kSplit4Max ? 4 : 1); }
+// Lanes per particle of a single run's gathers. With individual time steps what
+// counts are the particles evaluated: at 220 of 130,000 particles density and
+// momentum take 46 us with 16 lanes, 119 with one (waves without such a particle
+// exit; at most kSplitBlocks blocks of them are launched, at some 1 us a thousand).
+// Records that need 64-bit offsets are not split.
+constexpr int64_t kSplitBlocks = 16384;
 inline unsigned pair_blocks(int64_t n, int split) { return blocks_for(n, kThreads / split); }
+inline int split_of(int64_t n, const StepMask &mask, bool big)
+{
+    const int64_t work = mask.bin ? mask.active : n;
+    int s = work <= kSplit16Max ? 16 : (work <= kSplit4Max ? 4 : 1);
+    if (s == 16 && pair_blocks(n, 16) > kSplitBlocks) s = 4;
+    if (s == 4 && pair_blocks(n, 4) > kSplitBlocks) s = 1;
+    return big ? 1 : s;
+}
 
 template <bool Multi>
 void density_launch(hipStream_t st, unsigned blocks, int precision, bool big, int split, int64_t n,
@@ -1353,7 +1364,8 @@ hipError_t launch_density(sph_ctx ctx, const sph_particles &p, const sph_nbrs &n
                           int precision, const KernelSel &ks, bool gve, double *rho,
                           const StepMask &mask, bool packed)
 {
-    const int split = split_of(p.n);
+    const bool big = big_records(p.n, sizeof(DensRec));
+    const int split = split_of(p.n, mask, big);
     const unsigned nblk = pair_blocks(p.n, split);
     // generalised volume elements: the records carry X in place of m, the
     // kernel leaves k_i in rho, which is then scaled by m_i / X_i
@@ -1361,7 +1373,7 @@ hipError_t launch_density(sph_ctx ctx, const sph_particles &p, const sph_nbrs &n
         pack_dens_kernel<<<blocks_for(p.n, 256), 256, 0, ctx->stream>>>(
             p.n, nullptr, p.x, p.y, p.z, gve ? p.xw : p.m, ctx->drec);
     const int tk = ktime_begin(ctx, TK_DENSITY);
-    density_launch<false>(ctx->stream, nblk, precision, big_records(p.n, sizeof(DensRec)), split, p.n,
+    density_launch<false>(ctx->stream, nblk, precision, big, split, p.n,
                           p.n, ctx->drec, p.h, nb.count, nb.idx, nb.max_nb, ctx->grid, rho,
                           BatchDev{}, ks, mask);
     ktime_end(ctx, tk);
@@ -1412,7 +1424,7 @@ hipError_t launch_density_noalloc(hipStream_t stream, const sph_particles &p, co
     // the static array) in place of the context's records
     pack_dens_kernel<<<blocks_for(p.n, 256), 256, 0, stream>>>(p.n, nullptr, p.x, p.y, p.z,
                                                                 gve ? p.xw : p.m, recs);
-    const int split = split_of(p.n);
+    const int split = split_of(p.n, StepMask{}, false);
     density_launch<false>(stream, pair_blocks(p.n, split), precision, false, split, p.n, p.n, recs,
                           p.h, nb.count, nb.idx, nb.max_nb, g, rho, BatchDev{}, ks);
     if (gve)
@@ -1445,12 +1457,12 @@ hipError_t launch_eos(sph_ctx ctx, const sph_particles &p, const sph_params &prm
 
 hipError_t launch_momentum(sph_ctx ctx, const sph_particles &p, const sph_nbrs &nb,
                            const sph_params &prm, const sph_fields &f, const sph_accel &a,
-                           bool eos, const double *bin, int sub, int B)
+                           bool eos, const StepMask &mask)
 {
     const KernelSel ks = kernel_sel(prm);
     const bool iad = prm.gradient == SPH_GRAD_IAD;
-    const MomParams mp{prm.alpha, prm.beta, prm.eta2, ks.sigma, ks.sinc_n, ctx->iad_c, bin, sub,
-                       B};
+    const MomParams mp{prm.alpha, prm.beta, prm.eta2, ks.sigma, ks.sinc_n, ctx->iad_c, mask.bin,
+                       mask.sub, mask.B};
     if (iad) {
         pack_vol_kernel<<<blocks_for(p.n, 256), 256, 0, ctx->stream>>>(p.n, p.x, p.y, p.z, p.m,
                                                                        f.rho, ctx->drec);
@@ -1466,10 +1478,10 @@ hipError_t launch_momentum(sph_ctx ctx, const sph_particles &p, const sph_nbrs &
 #undef SPH_IAD
     }
     const bool gve = prm.volume == SPH_VOLUME_GENERALISED;
-    const int split = iad || gve ? 1 : split_of(p.n);
     const bool r32 = prm.precision == SPH_FP32_PAIR && !iad;  // PairRec32 records
+    const bool big = big_records(p.n, r32 ? sizeof(PairRec32) : sizeof(PairRec));
+    const int split = iad || gve ? 1 : split_of(p.n, mask, big);
     const EosArgs E = eos ? eos_args(p, prm, f) : EosArgs{};
-    const StepMask mask{bin, sub, B};
 #define SPH_PACK(R, E_)                                                                    \
     pack_pair_kernel<R, E_><<<blocks_for(p.n, 256), 256, 0, ctx->stream>>>(                \
         p.n, nullptr, p.x, p.y, p.z, p.vx, p.vy, p.vz, p.h, p.m, f.rho, f.c, f.pr2,        \
@@ -1483,8 +1495,7 @@ hipError_t launch_momentum(sph_ctx ctx, const sph_particles &p, const sph_nbrs &
     }
 #undef SPH_PACK
     const int tk = ktime_begin(ctx, TK_MOMENTUM);
-    momentum_launch<false>(ctx->stream, pair_blocks(p.n, split), prm.precision,
-                           big_records(p.n, r32 ? sizeof(PairRec32) : sizeof(PairRec)), split,
+    momentum_launch<false>(ctx->stream, pair_blocks(p.n, split), prm.precision, big, split,
                            p.n, p.n, ctx->prec, nb.count, nb.idx, nb.max_nb, ctx->grid, mp,
                            a.ax, a.ay, a.az, a.dudt, a.mumax, BatchDev{}, ctx->hflag_dev,
                            ks.family, iad, gve);

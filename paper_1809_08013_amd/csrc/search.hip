@@ -1329,7 +1329,9 @@ hipError_t launch_find_neighbors(sph_ctx ctx, const sph_particles &p, const sph_
         p.n, p.n, ctx->srec, ctx->sorted_keys, ctx->cell_start, ctx->cell_end, ctx->grid,  \
         nb.max_nb, nb.count, nb.idx, ctx->hflag_dev, ctx->status_dev, BatchDev{},          \
         mask, s2max)
-    if (tiles <= kCuTiles) SPH_SEARCH(16);
+    // (tiles without a particle whose step closes exit at once)
+    const int64_t live = mask.bin ? std::min(tiles, mask.active) : tiles;
+    if (live <= kCuTiles && tiles <= 32 * kCuTiles) SPH_SEARCH(16);
     else if (tiles <= kSharedTiles) SPH_SEARCH(4);
     else SPH_SEARCH(1);
 #undef SPH_SEARCH

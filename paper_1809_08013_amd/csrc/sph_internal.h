@@ -193,9 +193,11 @@ static_assert(sizeof(GNode) == 128, "GNode is one cache line");
 // Individual time steps: with bin set, a call works only on the particles
 // of bin b whose step closes at substep sub of 2^B, ((sub + 1) mod 2^(B-b))
 // == 0; the others are left as they are.
+constexpr int kMaxBins = 17, kBlockWords = 1 + kMaxBins;  // bins 0 .. 16
 struct StepMask {
     const double *bin = nullptr;
     int sub = 0, B = 0;
+    int64_t active = 0;  // how many close (host: the launches' shapes go by it)
 };
 __device__ __forceinline__ bool step_closes(const StepMask &m, int64_t i)
 {
@@ -453,13 +455,13 @@ hipError_t radix_sort_pairs(sph_ctx ctx, uint32_t *k[2], int32_t *v[2], int64_t 
                             int key_bits, int *cur);
 hipError_t launch_eos(sph_ctx ctx, const sph_particles &p, const sph_params &prm,
                       const sph_fields &f, const StepMask &mask = StepMask{});
-// bin (not null): only the particles whose step closes at substep sub of
-// 2^B get new accelerations (individual time steps). eos: the pair records' pass
-// forms pressure and sound speed first, as launch_eos with the same bins does.
+// mask: only the particles whose step closes get new accelerations (individual
+// time steps). eos: the pair records' pass forms pressure and sound speed first, as
+// launch_eos with the same mask does.
 hipError_t launch_momentum(sph_ctx ctx, const sph_particles &p, const sph_nbrs &nb,
                            const sph_params &prm, const sph_fields &f,
-                           const sph_accel &a, bool eos = false, const double *bin = nullptr,
-                           int sub = 0, int B = 0);
+                           const sph_accel &a, bool eos = false,
+                           const StepMask &mask = StepMask{});
 hipError_t launch_integrate(sph_ctx ctx, const sph_particles &p, const Grid &g,
                             int stage, const double *dt_dev, const sph_accel &a);
 // kick: the second half kick (sph_integrate(SPH_KICK)) first, in the same pass.
@@ -468,8 +470,8 @@ hipError_t launch_timestep(sph_ctx ctx, const sph_particles &p,
                            const sph_accel &a, double *dt_dev, double *diag_dev, bool kick = false);
 hipError_t launch_copy(sph_ctx ctx, double *dst, const double *src, int64_t n);
 // Individual time steps: per-particle criterion, the largest step D into
-// dt_dev[0], the bins into bin (as doubles) and the deepest bin into
-// ctx->blk_words[0].
+// dt_dev[0], the bins into bin (as doubles), the deepest bin into
+// ctx->blk_words[0] and the particles of bin b into ctx->blk_words[1 + b].
 hipError_t launch_block_bins(sph_ctx ctx, const sph_particles &p, const sph_params &prm,
                              const sph_fields &f, const sph_accel &a, int max_bin, double *bin,
                              double *dt_dev);

@@ -73,3 +73,56 @@ def test_shared_particle_sums(n, precision, kernel, spread):
         assert np.array_equal(got[k], want[k]), k
     if n > 1000:
         assert got["count"].mean() > 20 and np.abs(got["ax"]).max() > 0
+
+
+def _stepping(n, total):
+    """_cloud with a few hot particles (deep bins) and the others of the total
+    alone on a lattice, at rest, with a step in the middle of the range."""
+    ic = _cloud(n, n, 0.0)
+    ic.u[: max(1, n // 100)] *= 9.0
+    for axis in "xyz":
+        getattr(ic, "v" + axis)[:] *= 0.1
+    if total == n:
+        return ic
+    more = total - n
+    side = int(np.ceil((more / 0.25) ** (1 / 3)))
+    k = np.arange(more)
+    big = I.random_cloud(total, seed=0, h_min=ic.h[0], h_max=ic.h[0])
+    for name, a in ic.arrays().items():
+        if name != "id":
+            getattr(big, name)[:n] = a
+    big.x[n:] = 0.7 + (k // side ** 2 + 0.5) / side
+    big.y[n:] = (k // side % side + 0.5) / side
+    big.z[n:] = (k % side + 0.5) / side
+    big.h[n:] = 0.3 * ic.h[0]
+    big.u[n:] = 0.09 * 1.5
+    for axis in "xyz":
+        getattr(big, "v" + axis)[n:] = 0.0
+    return big
+
+
+@pytest.mark.parametrize("n", [300, 3001])
+def test_block_steps_by_what_closes(n):
+    """Individual time steps choose their launches by how many particles close:
+    bit for bit the same particles with few others and with many, which close
+    only with the shallow bins."""
+    print(f"block steps n={n}", flush=True)
+    out = []
+    for total in (n, ONE_LANE):
+        ic = _stepping(n, total)
+        assert ic.x.max() < 1.0
+        prm = S.make_params(ic.params)
+        ctx = S.Context(ONE_LANE, 160)
+        st = S.SphState(ic, 160)
+        S.sph_init_forces(ctx, st, prm)
+        subs = [S.sph_step_blocks(ctx, st, prm, 4) for _ in range(2)]
+        S.sph_ctx_check(ctx)
+        got = {k: v[:n] for k, v in st.host(["x", "vx", "u", "rho", "ax", "dudt", "bin"]).items()}
+        if total > n:  # alone, and in a shallower bin than the hot ones
+            full = st.host(["count", "bin"])
+            assert full["count"][n:].max() == 0
+            assert full["bin"][n:].max() < full["bin"][:n].max()
+        out.append((subs, got))
+    assert out[0][0] == out[1][0] and max(out[0][0]) > 1
+    for k in out[0][1]:
+        assert np.array_equal(out[0][1][k], out[1][1][k]), k
