@@ -415,8 +415,8 @@ permute_gather_kernel(int64_t n, const int64_t *n_dev, int64_t stride,
 __global__ void __launch_bounds__(256)
 permute_store_kernel(int64_t n, const int64_t *n_dev, int64_t stride, PermFields f,
                      const double *__restrict__ tmp, const int32_t *__restrict__ tmp_id,
-                     const int32_t *__restrict__ tmp_slot, int h_field,
-                     SearchRec *__restrict__ srec)
+                     const int32_t *__restrict__ tmp_slot, int h_field, int m_field,
+                     SearchRec *__restrict__ srec, DensRec *__restrict__ drec)
 {
     if (n_dev) n = *n_dev;
     const int64_t step = (int64_t)gridDim.x * blockDim.x;
@@ -427,14 +427,15 @@ permute_store_kernel(int64_t n, const int64_t *n_dev, int64_t stride, PermFields
         const double x = tmp[i], y = tmp[stride + i], z = tmp[2 * stride + i];
         const double s = 2.0 * tmp[h_field * stride + i];
         srec[i] = SearchRec{x, y, z, s * s};
+        drec[i] = DensRec{x, y, z, tmp[m_field * stride + i]};
     }
 }
 
 // Last kernel of a build: gathers every field from the scratch rows into the
 // caller's arrays in cell order, writes the search records (position and
-// (2h)^2), the density records if asked for and the cell table (a particle whose predecessor lies in another cell
-// ends that one and starts its own; cells without particles stay empty). With
-// varying h also each cell's largest (2h)^2, as the ordered bit pattern of a
+// (2h)^2), the density records if asked for and the cell table (a particle whose
+// predecessor lies in another cell ends that one and starts its own; cells without
+// particles stay empty). With varying h also each cell's largest (2h)^2, as the ordered bit pattern of a
 // positive double: a segmented maximum over the wave's lanes (a cell's
 // particles are consecutive), then one atomic per cell and wave.
 __global__ void __launch_bounds__(256)
@@ -508,12 +509,15 @@ admit_kernel(BatchDev b)
     }
 }
 
+// Kick-drift of the particles of stepping runs (not at a run's t = 0 evaluation,
+// not when it is being dropped) with their run's dt and box, and the keys.
 __global__ void __launch_bounds__(256)
-keys_batch_kernel(BatchDev b, const double *__restrict__ x, const double *__restrict__ y,
-                  const double *__restrict__ z, const double *__restrict__ h,
-                  uint32_t *__restrict__ keys)
+keys_batch_kernel(BatchDev b, double *__restrict__ F, const double *__restrict__ ax,
+                  const double *__restrict__ ay, const double *__restrict__ az,
+                  const double *__restrict__ dudt, uint32_t *__restrict__ keys)
 {
-    const int64_t n = b.hdr->n_in;
+    const int64_t n = b.hdr->n_in, cap = b.cap;
+    const double *h = F + 7 * cap;
     const int64_t step = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += step) {
         const int s = b.slot[i];
@@ -521,10 +525,24 @@ keys_batch_kernel(BatchDev b, const double *__restrict__ x, const double *__rest
         uint32_t key = kEnsDropKey;
         if (r.phase == RUN_INIT || r.phase == RUN_STEP) {
             const Grid &g = r.grid;
-            const uint32_t cx = (uint32_t)cell_of(x[i], g.lo[0], g.inv_s[0], g.nc[0]);
-            const uint32_t cy = (uint32_t)cell_of(y[i], g.lo[1], g.inv_s[1], g.nc[1]);
-            const uint32_t cz = (uint32_t)cell_of(z[i], g.lo[2], g.inv_s[2], g.nc[2]);
-            const uint32_t zq = slice_of(z[i], g.lo[2], g.inv_s[2], (int)cz, g.zbits);
+            double p[3] = {F[i], F[cap + i], F[2 * cap + i]};
+            if (r.phase == RUN_STEP) {
+                const double dt = b.dt[s];
+                const double t[3] = {ax[i], ay[i], az[i]};
+                double v[3] = {F[3 * cap + i], F[4 * cap + i], F[5 * cap + i]}, u = F[6 * cap + i];
+                half_kick(0.5 * dt, t, dudt[i], v, u);
+                drift(dt, g, v, p);
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    F[a * cap + i] = p[a];
+                    F[(3 + a) * cap + i] = v[a];
+                }
+                F[6 * cap + i] = u;
+            }
+            const uint32_t cx = (uint32_t)cell_of(p[0], g.lo[0], g.inv_s[0], g.nc[0]);
+            const uint32_t cy = (uint32_t)cell_of(p[1], g.lo[1], g.inv_s[1], g.nc[1]);
+            const uint32_t cz = (uint32_t)cell_of(p[2], g.lo[2], g.inv_s[2], g.nc[2]);
+            const uint32_t zq = slice_of(p[2], g.lo[2], g.inv_s[2], (int)cz, g.zbits);
             key = ((uint32_t)s << kEnsSlotShift) |
                   ((spread3(cx) | (spread3(cy) << 1) | (spread3(cz) << 2)) << kSliceBits) |
                   (zq << (kSliceBits - g.zbits));
@@ -766,14 +784,14 @@ hipError_t launch_admit_batch(sph_ctx ctx, const BatchDev &b)
 }
 
 hipError_t launch_build_cells_batch(sph_ctx ctx, const BatchDev &b, double *F, int32_t *id,
-                                    int32_t *slot_tmp)
+                                    int32_t *slot_tmp, const double *ax, const double *ay,
+                                    const double *az, const double *dudt)
 {
     hipStream_t s = ctx->stream;
     const int64_t cap = b.cap;
     const unsigned grid = std::min<unsigned>(blocks_for(cap, 256), 4096u);
     const int64_t *n_in = &b.hdr->n_in;
-    keys_batch_kernel<<<grid, 256, 0, s>>>(b, F + 0 * cap, F + 1 * cap, F + 2 * cap,
-                                           F + 7 * cap, ctx->keys[0]);
+    keys_batch_kernel<<<grid, 256, 0, s>>>(b, F, ax, ay, az, dudt, ctx->keys[0]);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     int cur = 0;
@@ -789,7 +807,7 @@ hipError_t launch_build_cells_batch(sph_ctx ctx, const BatchDev &b, double *F, i
                                                ctx->perm_tmp, ctx->perm_tmp_id, slot_tmp);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     permute_store_kernel<<<grid, 256, 0, s>>>(cap, n_in, ctx->n_max, f, ctx->perm_tmp,
-                                              ctx->perm_tmp_id, slot_tmp, 7, ctx->srec);
+                                              ctx->perm_tmp_id, slot_tmp, 7, 8, ctx->srec, ctx->drec);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const unsigned cgrid = std::min<unsigned>(blocks_for(b.cell_cap, 256), 4096u);
     cell_table_batch_kernel<<<cgrid, 256, 0, s>>>(b, ctx->sorted_keys, ctx->cell_start,

@@ -260,7 +260,7 @@ void free_ens(sph_ens e)
 }
 
 // The launch sequence of one batched step, captured once into a graph:
-// admit, kick-drift, build, search, density, EOS, momentum, kick, dt.
+// admit, kick-drift and build, search, density, EOS and momentum, kick and dt.
 hipError_t capture_step(sph_ens e)
 {
     const BatchDev &b = e->bd;
@@ -271,27 +271,20 @@ hipError_t capture_step(sph_ens e)
     auto run = [&]() -> hipError_t {
         hipError_t q;
         if ((q = launch_admit_batch(e->ctx, b)) != hipSuccess) return q;
-        if ((q = launch_integrate_batch(e->ctx, b, SPH_KICK_DRIFT, e->F, e->ax, e->ay, e->az,
-                                        e->dudt)) != hipSuccess)
-            return q;
-        if ((q = launch_build_cells_batch(e->ctx, b, e->F, e->id, e->slot_tmp)) != hipSuccess)
+        if ((q = launch_build_cells_batch(e->ctx, b, e->F, e->id, e->slot_tmp, e->ax, e->ay,
+                                          e->az, e->dudt)) != hipSuccess)
             return q;
         if ((q = launch_find_neighbors_batch(e->ctx, b, mnb, e->count, e->idx)) != hipSuccess)
             return q;
         if ((q = launch_density_batch(e->ctx, b, prec, e->F, e->count, e->idx, mnb, e->rho)) !=
             hipSuccess)
             return q;
-        if ((q = launch_eos_batch(e->ctx, b, e->F, e->rho, e->p, e->c, e->pr2)) != hipSuccess)
-            return q;
         if ((q = launch_momentum_batch(e->ctx, b, prec, e->F, e->count, e->idx, mnb, e->rho,
-                                       e->c, e->pr2, e->ax, e->ay, e->az, e->dudt,
+                                       e->p, e->c, e->pr2, e->ax, e->ay, e->az, e->dudt,
                                        e->mumax)) != hipSuccess)
             return q;
-        if ((q = launch_integrate_batch(e->ctx, b, SPH_KICK, e->F, e->ax, e->ay, e->az,
-                                        e->dudt)) != hipSuccess)
-            return q;
         return launch_timestep_batch(e->ctx, b, e->F, e->c, e->mumax, e->ax, e->ay, e->az,
-                                     e->red_part);
+                                     e->dudt, e->red_part);
     };
     hipError_t q = run();
     hipGraph_t g = nullptr;

@@ -1097,8 +1097,12 @@ momentum_kernel(int64_t n, int64_t ld, const PairRec *__restrict__ rec,
 // fields after the position and velocity rounded to FP32 (1/h from the FP64
 // h, Q from the FP64 fields). Eos: P, c and P/rho^2 of the particles whose step
 // closes are formed here (c and pr2 hold the others'), which saves a launch and a
-// pass over rho, c and pr2.
-template <bool R32, bool Eos>
+// pass over rho, c and pr2. EOS_RUNS: of an ensemble's particles, each with its
+// run's constants; at a run's t = 0 evaluation with a density reference, rho_ref :=
+// rho first (then the Tait ratio is exactly one, as in the single-run initial
+// evaluation).
+enum { EOS_NONE = 0, EOS_RUN = 1, EOS_RUNS = 2 };
+template <bool R32, int Eos>
 __global__ void __launch_bounds__(256)
 pack_pair_kernel(int64_t n, const int64_t *n_dev, const double *__restrict__ x,
                  const double *__restrict__ y, const double *__restrict__ z,
@@ -1106,7 +1110,8 @@ pack_pair_kernel(int64_t n, const int64_t *n_dev, const double *__restrict__ x,
                  const double *__restrict__ vz, const double *__restrict__ h,
                  const double *__restrict__ m, const double *__restrict__ rho,
                  const double *c, const double *pr2, const double *__restrict__ xw,
-                 void *__restrict__ out, EosArgs E, StepMask mask)
+                 void *__restrict__ out, EosArgs E, StepMask mask, BatchDev b,
+                 double *rho_ref)
 {
     // Each wave forms the records of 64 consecutive particles in LDS (one
     // per lane, stride 17 doubles), then stores them as 16-byte chunks with
@@ -1133,7 +1138,18 @@ pack_pair_kernel(int64_t n, const int64_t *n_dev, const double *__restrict__ x,
             r[3] = vx[i]; r[4] = vy[i]; r[5] = vz[i];
             double ci, pri;
             const double rhoi = rho[i];
-            if (Eos && step_closes(mask, i)) {
+            if (Eos == EOS_RUNS) {
+                const RunDev &rd = b.runs[b.slot[i]];
+                if (rd.phase == RUN_INIT && rd.set_rho_ref) rho_ref[i] = rhoi;
+                EosArgs R = E;
+                R.eos = rd.eos;
+                R.rho0 = rd.rho0;
+                R.c0 = rd.c0;
+                R.gamma_tait = rd.gamma_tait;
+                R.gamma_gas = rd.gamma_gas;
+                R.rho_ref = rho_ref;
+                eos_point(R, i, rhoi, ci, pri);
+            } else if (Eos == EOS_RUN && step_closes(mask, i)) {
                 eos_point(E, i, rhoi, ci, pri);
             } else {
                 ci = c[i];
@@ -1179,39 +1195,6 @@ inline unsigned blocks_for(int64_t n, int t) { return (unsigned)((n + t - 1) / t
 inline unsigned ens_pair_blocks(int64_t cap)
 {
     return blocks_for((cap + 63) / 64 + kEnsMaxSlots, kThreads / 64);
-}
-
-// Ensemble EOS: each particle with its run's constants. At a run's t = 0
-// evaluation with a density reference, rho_ref := rho first (then the Tait
-// ratio is exactly one, as in the single-run initial evaluation).
-__global__ void __launch_bounds__(256)
-eos_batch_kernel(BatchDev b, const double *__restrict__ rho, const double *__restrict__ u,
-                 double *__restrict__ rho_ref, const double *__restrict__ p_bg,
-                 double *__restrict__ p, double *__restrict__ c, double *__restrict__ pr2)
-{
-    const int64_t n = b.hdr->n_out;
-    const int64_t step = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += step) {
-        const RunDev &rd = b.runs[b.slot[i]];
-        const double r = rho[i];
-        if (rd.phase == RUN_INIT && rd.set_rho_ref) rho_ref[i] = r;
-        double P, C;
-        if (rd.eos == SPH_EOS_TAIT) {
-            const double B = rd.rho0 * rd.c0 * rd.c0 / rd.gamma_tait;
-            const double xr = r / rho_ref[i];
-            const double x2 = xr * xr, x4 = x2 * x2, x6 = x4 * x2, x7 = x6 * xr;
-            const double x3 = x2 * xr;
-            P = p_bg[i] + B * (x7 - 1.0);
-            C = rd.c0 * x3;
-        } else {
-            const double g = rd.gamma_gas;
-            P = (g - 1.0) * r * u[i];
-            C = sqrt(g * (g - 1.0) * u[i]);
-        }
-        p[i] = P;
-        c[i] = C;
-        pr2[i] = P / (r * r);
-    }
 }
 
 // Record arrays of 4 GiB or more need 64-bit element offsets.
@@ -1485,13 +1468,13 @@ hipError_t launch_momentum(sph_ctx ctx, const sph_particles &p, const sph_nbrs &
 #define SPH_PACK(R, E_)                                                                    \
     pack_pair_kernel<R, E_><<<blocks_for(p.n, 256), 256, 0, ctx->stream>>>(                \
         p.n, nullptr, p.x, p.y, p.z, p.vx, p.vy, p.vz, p.h, p.m, f.rho, f.c, f.pr2,        \
-        gve ? p.xw : nullptr, ctx->prec, E, mask)
+        gve ? p.xw : nullptr, ctx->prec, E, mask, BatchDev{}, nullptr)
     if (r32) {
-        if (eos) SPH_PACK(true, true);
-        else SPH_PACK(true, false);
+        if (eos) SPH_PACK(true, EOS_RUN);
+        else SPH_PACK(true, EOS_NONE);
     } else {
-        if (eos) SPH_PACK(false, true);
-        else SPH_PACK(false, false);
+        if (eos) SPH_PACK(false, EOS_RUN);
+        else SPH_PACK(false, EOS_NONE);
     }
 #undef SPH_PACK
     const int tk = ktime_begin(ctx, TK_MOMENTUM);
@@ -1511,49 +1494,40 @@ hipError_t launch_density_batch(sph_ctx ctx, const BatchDev &b, int precision, c
                                 const int32_t *count, const int32_t *idx, int max_nb,
                                 double *rho)
 {
+    // (the build has written the density records)
     const int64_t cap = b.cap;
-    const int64_t *n_out = &b.hdr->n_out;
-    const unsigned g1 = std::min<unsigned>(blocks_for(cap, 256), 4096u);
     const unsigned g2 = ens_pair_blocks(cap);
-    pack_dens_kernel<<<g1, 256, 0, ctx->stream>>>(0, n_out, F + 0 * cap, F + 1 * cap,
-                                                  F + 2 * cap, F + 8 * cap, ctx->drec);
     density_launch<true>(ctx->stream, g2, precision, big_records(cap, sizeof(DensRec)), 1, 0, cap,
                          ctx->drec, F + 7 * cap, count, idx, max_nb, Grid{}, rho, b,
                          KernelSel{SPH_KERNEL_M4, 0, 0.0});
     return hipGetLastError();
 }
 
-hipError_t launch_eos_batch(sph_ctx ctx, const BatchDev &b, double *F, const double *rho,
-                            double *p, double *c, double *pr2)
-{
-    const int64_t cap = b.cap;
-    const unsigned g1 = std::min<unsigned>(blocks_for(cap, 256), 4096u);
-    eos_batch_kernel<<<g1, 256, 0, ctx->stream>>>(b, rho, F + 6 * cap, F + 10 * cap,
-                                                  F + 9 * cap, p, c, pr2);
-    return hipGetLastError();
-}
-
-hipError_t launch_momentum_batch(sph_ctx ctx, const BatchDev &b, int precision,
-                                 const double *F, const int32_t *count, const int32_t *idx,
-                                 int max_nb, const double *rho, const double *c,
-                                 const double *pr2, double *ax, double *ay, double *az,
-                                 double *dudt, double *mumax)
+hipError_t launch_momentum_batch(sph_ctx ctx, const BatchDev &b, int precision, double *F,
+                                 const int32_t *count, const int32_t *idx, int max_nb,
+                                 const double *rho, double *p, double *c, double *pr2,
+                                 double *ax, double *ay, double *az, double *dudt,
+                                 double *mumax)
 {
     const int64_t cap = b.cap;
     const int64_t *n_out = &b.hdr->n_out;
     const unsigned g1 = std::min<unsigned>(blocks_for(cap, 256), 4096u);
     const unsigned g2 = ens_pair_blocks(cap);
     const bool r32 = precision == SPH_FP32_PAIR;  // PairRec32 records
-    if (r32)
-        pack_pair_kernel<true, false><<<g1, 256, 0, ctx->stream>>>(
-            0, n_out, F + 0 * cap, F + 1 * cap, F + 2 * cap, F + 3 * cap, F + 4 * cap,
-            F + 5 * cap, F + 7 * cap, F + 8 * cap, rho, c, pr2, nullptr, ctx->prec, EosArgs{},
-            StepMask{});
-    else
-        pack_pair_kernel<false, false><<<g1, 256, 0, ctx->stream>>>(
-            0, n_out, F + 0 * cap, F + 1 * cap, F + 2 * cap, F + 3 * cap, F + 4 * cap,
-            F + 5 * cap, F + 7 * cap, F + 8 * cap, rho, c, pr2, nullptr, ctx->prec, EosArgs{},
-            StepMask{});
+    EosArgs E{};
+    E.u = F + 6 * cap;
+    E.p_bg = F + 9 * cap;
+    E.p = p;
+    E.c = c;
+    E.pr2 = pr2;
+#define SPH_PACK(R)                                                                        \
+    pack_pair_kernel<R, EOS_RUNS><<<g1, 256, 0, ctx->stream>>>(                            \
+        0, n_out, F + 0 * cap, F + 1 * cap, F + 2 * cap, F + 3 * cap, F + 4 * cap,         \
+        F + 5 * cap, F + 7 * cap, F + 8 * cap, rho, c, pr2, nullptr, ctx->prec, E,         \
+        StepMask{}, b, F + 10 * cap)
+    if (r32) SPH_PACK(true);
+    else SPH_PACK(false);
+#undef SPH_PACK
     momentum_launch<true>(ctx->stream, g2, precision,
                           big_records(cap, r32 ? sizeof(PairRec32) : sizeof(PairRec)), 1, 0, cap,
                           ctx->prec, count, idx, max_nb, Grid{}, MomParams{}, ax, ay, az, dudt,

@@ -28,8 +28,8 @@
 // The bits (two 32-bit words a lane and block) stay in LDS, and each lane then
 // walks its own words and writes its list, row k of all lanes together. A
 // union of more candidates than LDS has bits for is taken in several chunks.
-// One wave does a tile; small runs put four on each, every wave taking a
-// quarter of the candidates.
+// One wave does a tile; small runs put four on each, the smallest sixteen, every
+// wave taking its share of the candidates.
 //
 // Periodic axes: every position is taken as its image nearest to the tile's
 // centre. Where the tile's extent from its centre plus the reach stays below
@@ -60,8 +60,8 @@ constexpr int kWave = 64;
 // the union after the cells out of reach are dropped; kBlocks: blocks of 64
 // candidates whose relation bits LDS holds at a time (a larger union is
 // taken in several chunks).
-//   W = 1: one wave does a tile. 22 blocks = 1,408 candidates (the mean union
-//          of the 1M patch is 1,150) leave 11 tiles on a CU.
+//   W = 1: one wave does a tile. 16 blocks = 1,024 candidates (the mean union
+//          of the 1M patch is 1,395) leave four waves to a SIMD; 22 leave three.
 //   W = 4: four waves share one, for runs too small to fill the chip.
 //   W = 16: sixteen, for the smallest.
 template <int W>

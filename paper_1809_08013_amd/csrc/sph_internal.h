@@ -502,25 +502,24 @@ hipError_t launch_h_iteration(sph_ctx ctx, const sph_particles &p, int32_t *coun
 // step header on the device. F is the block of kEnsFields state rows
 // (x y z vx vy vz u h m p_bg rho_ref), each b.cap long.
 hipError_t launch_admit_batch(sph_ctx ctx, const BatchDev &b);
+// The kick-drift of the stepping runs, and the build of all (density records too).
 hipError_t launch_build_cells_batch(sph_ctx ctx, const BatchDev &b, double *F, int32_t *id,
-                                    int32_t *slot_tmp);
+                                    int32_t *slot_tmp, const double *ax, const double *ay,
+                                    const double *az, const double *dudt);
 hipError_t launch_find_neighbors_batch(sph_ctx ctx, const BatchDev &b, int max_nb,
                                        int32_t *count, int32_t *idx);
 hipError_t launch_density_batch(sph_ctx ctx, const BatchDev &b, int precision, const double *F,
                                 const int32_t *count, const int32_t *idx, int max_nb,
                                 double *rho);
-hipError_t launch_eos_batch(sph_ctx ctx, const BatchDev &b, double *F, const double *rho,
-                            double *p, double *c, double *pr2);
-hipError_t launch_momentum_batch(sph_ctx ctx, const BatchDev &b, int precision,
-                                 const double *F, const int32_t *count, const int32_t *idx,
-                                 int max_nb, const double *rho, const double *c,
-                                 const double *pr2, double *ax, double *ay, double *az,
-                                 double *dudt, double *mumax);
-hipError_t launch_integrate_batch(sph_ctx ctx, const BatchDev &b, int stage, double *F,
-                                  const double *ax, const double *ay, const double *az,
-                                  const double *dudt);
-hipError_t launch_timestep_batch(sph_ctx ctx, const BatchDev &b, const double *F,
-                                 const double *c, const double *mumax, const double *ax,
-                                 const double *ay, const double *az, double *part);
+// EOS of every run, then the momentum pass.
+hipError_t launch_momentum_batch(sph_ctx ctx, const BatchDev &b, int precision, double *F,
+                                 const int32_t *count, const int32_t *idx, int max_nb,
+                                 const double *rho, double *p, double *c, double *pr2,
+                                 double *ax, double *ay, double *az, double *dudt,
+                                 double *mumax);
+// Second half kick of the stepping runs, then the reductions.
+hipError_t launch_timestep_batch(sph_ctx ctx, const BatchDev &b, double *F, const double *c,
+                                 const double *mumax, const double *ax, const double *ay,
+                                 const double *az, const double *dudt, double *part);
 
 }  // namespace sph
