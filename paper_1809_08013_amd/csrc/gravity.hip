@@ -572,7 +572,10 @@ gravity_tree_kernel(const DensRec *__restrict__ pos, const int32_t *__restrict__
         g = __builtin_amdgcn_readfirstlane(g);
         if (g >= ngroup) break;
         const int2 gr = groups[g];
-        const int32_t k = gr.x + lane;
+        // a group of up to 32 particles takes two terms at a time, one in each
+        // half of the wave (17% of the Evrard sphere's groups: 4.40 -> 4.25 ms)
+        const bool halves = gr.y - gr.x <= 32;
+        const int32_t k = gr.x + (halves ? lane & 31 : lane);
         const bool active = k < gr.y;
         const DensRec me = pos[active ? k : gr.x];
         double blo[3] = {me.x, me.y, me.z}, bhi[3] = {me.x, me.y, me.z};
@@ -646,13 +649,17 @@ gravity_tree_kernel(const DensRec *__restrict__ pos, const int32_t *__restrict__
             lds_sync();
             // accepted nodes in lane order
             const int nacc = __popcll(use);
-            int t = 0;
-            for (; t + 2 <= nacc; t += 2) {
-                const NodeTerm A = st.node[t], B = st.node[t + 1];
-                node_term(me, A, ax, ay, az);
-                node_term(me, B, ax, ay, az);
+            if (halves) {
+                for (int t = lane >> 5; t < nacc; t += 2) node_term(me, st.node[t], ax, ay, az);
+            } else {
+                int t = 0;
+                for (; t + 2 <= nacc; t += 2) {
+                    const NodeTerm A = st.node[t], B = st.node[t + 1];
+                    node_term(me, A, ax, ay, az);
+                    node_term(me, B, ax, ay, az);
+                }
+                if (t < nacc) node_term(me, st.node[t], ax, ay, az);
             }
-            if (t < nacc) node_term(me, st.node[t], ax, ay, az);
             // then the leaves' particles, staged 64 at a time by one load each
             for (int base = 0; base < ltotal; base += 64) {
                 const int m = min(64, ltotal - base);
@@ -684,7 +691,9 @@ gravity_tree_kernel(const DensRec *__restrict__ pos, const int32_t *__restrict__
                     ay = __builtin_fma(-f, dy, ay);
                     az = __builtin_fma(-f, dz, az);
                 };
-                if (own) {
+                if (halves) {
+                    for (int j = lane >> 5; j < m; j += 2) add(st.leaf[j], lpos[j] == k);
+                } else if (own) {
                     for (int j = 0; j < m; ++j) add(st.leaf[j], lpos[j] == k);
                 } else {
                     int j = 0;
@@ -699,7 +708,12 @@ gravity_tree_kernel(const DensRec *__restrict__ pos, const int32_t *__restrict__
             // the pushed entries are read by other lanes next round
             wave_fence();
         }
-        if (active) {
+        if (halves) {
+            ax += __shfl_xor(ax, 32, 64);
+            ay += __shfl_xor(ay, 32, 64);
+            az += __shfl_xor(az, 32, 64);
+        }
+        if (active && !(halves && lane >= 32)) {
             const int32_t i = order[k];
             gx[i] = ax;
             gy[i] = ay;

@@ -43,9 +43,9 @@ def test_direct_sum_shares(n, eps):
 
 
 @pytest.mark.parametrize("leaf", [8, 16, 64])
-@pytest.mark.parametrize("n", [1, 2, 64, 65, 130, 9001])
+@pytest.mark.parametrize("n", [1, 2, 32, 33, 64, 65, 130, 9001])
 def test_tree_groups_and_leaves(n, leaf):
-    """The octree at the edges of its groups (64 particles), with the smallest, the
+    """The octree at the edges of its groups (32, 64 particles), with the smallest, the
     usual and the largest leaves: within 1e-12 of the terms'
     magnitudes, the accuracy of the node terms' eight FP64 factors over a few
     hundred terms."""
