@@ -260,7 +260,9 @@ scan_down_kernel(uint32_t *__restrict__ a, int64_t len,
 // Stable scatter of one radix pass. Each wave takes a contiguous run of the
 // tile's keys and ranks it 64 at a time (lanes holding the same digit are
 // matched with one ballot per digit bit) against its own digit counts, so the
-// index order within a digit is kept and the block meets only three times.
+// index order within a digit is kept and the block meets only three times. The last
+// pass's digit has fewer bits: the keys have none above them, so the counts, which
+// take the digit at its full width, see the same digits as the ballots.
 // Self: hist holds the tiles' digit counts (tile-major), and the block adds them
 // up into the offsets it needs; else they have been scanned (digit-major). vin
 // null: the values are the indices. flag_part (not null): block 0 also reduces

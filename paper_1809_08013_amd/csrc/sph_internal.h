@@ -82,15 +82,16 @@ constexpr int kSliceBits = 6;
 //   (s << (3 kEnsAxisBits + kSliceBits)) | (Morton(cell) << kSliceBits) | slice,
 // so one stable radix sort over kEnsKeyBits bits groups the particles by run
 // and, inside a run, by cell and by z slice, exactly as the single-run sort
-// does for the same run. A run being dropped gets the all-ones key and sorts
-// behind every live particle.
+// does for the same run. A run being dropped gets the key with all of those bits
+// set (slot 511, which no run has) and sorts behind every live particle; no key has
+// a bit above them, which the sort relies on.
 constexpr int kEnsAxisBits = 5;                     // <= 32 cells per axis per run
 constexpr int kEnsSlotBits = 9;
 constexpr int kEnsMaxSlots = (1 << kEnsSlotBits) - 1;  // slot 511 is the drop key
 constexpr int kEnsSlotShift = 3 * kEnsAxisBits + kSliceBits;
 constexpr int kEnsKeyBits = kEnsSlotBits + kEnsSlotShift;
 constexpr uint32_t kEnsMortonMask = (1u << (3 * kEnsAxisBits)) - 1u;
-constexpr uint32_t kEnsDropKey = 0xFFFFFFFFu;
+constexpr uint32_t kEnsDropKey = (1u << kEnsKeyBits) - 1u;
 constexpr int kEnsFields = 11;  // x y z vx vy vz u h m p_bg rho_ref (rows of one block)
 
 enum : int32_t { RUN_FREE = 0, RUN_INIT = 1, RUN_STEP = 2, RUN_DROP = 3 };
