@@ -62,13 +62,17 @@ constexpr int kWave = 64;
 // taken in several chunks).
 //   W = 1: one wave does a tile. 16 blocks = 1,024 candidates (the mean union
 //          of the 1M patch is 1,395) leave four waves to a SIMD; 22 leave three.
+//          104 cells are what then fits (10,212 of 10,240 B of LDS): a cloud of 52
+//          neighbours on average has a few tiles of 93 to 104, and one tile on the
+//          per-lane path ends 100 us after the others (180,000 particles: 176 us
+//          with 92 cells, 80 with 104; 300,000 of 25 in varying h: 182 and 162).
 //   W = 4: four waves share one, for runs too small to fill the chip.
 //   W = 16: sixteen, for the smallest.
 template <int W>
 struct SearchShape;
 template <>
 struct SearchShape<1> {
-    static constexpr int kMaxDist = 9, kEntries = 256, kCells = 92, kBlocks = 16;
+    static constexpr int kMaxDist = 9, kEntries = 256, kCells = 104, kBlocks = 16;
     typedef uint8_t Cell;
 };
 template <>
@@ -320,6 +324,8 @@ struct SearchLds {
     uint32_t dkeys[S::kMaxDist];
     int wsum[W];
 };
+
+static_assert(sizeof(SearchLds<1>) <= 160 * 1024 / 16, "four waves per SIMD");
 
 // A position relative to the tile's centre, as its nearest image on periodic
 // axes.
