@@ -1321,7 +1321,17 @@ __global__ void clear_words_kernel(uint32_t *a, int k)
 // most of the CUs without one. 4, 8 and 16 waves: 8,000 particles 40.4, 37.1, 36.4
 // us, 15,600: 42.7, 41.8, 41.6, 32,800: 53, 54, 75. (A tile's union and the first
 // load of its candidates come one after the other whatever the waves.)
+// 1 and 4 waves: patch of 91,125 particles 117, 90 us, 132,651: 124, 118, 157,464:
+// 135, 128, 195,112: 133, 146; clouds of 60 neighbours in varying h 90,000: 148,
+// 105, 131,072: 147, 135, 200,000: 213, 204, 260,000: 238, 249, of 110 in uniform h
+// 110,000: 97, 90, 131,072: 100, 102, 160,000: 115, 121. With fewer than 4.5
+// particles per cell nearly every tile takes the per-lane path, where three of four
+// waves only hold their place: 5 neighbours 55,000: 54, 54, 70,000: 62, 61, 110,000:
+// 81, 83, 131,072: 81, 119; 16 neighbours 55,000: 84, 86, 70,000: 95, 108, 131,072:
+// 100, 131.
 constexpr int64_t kCuTiles = 256, kSharedTiles = 2048;
+constexpr int64_t kThinTiles = 1024;
+constexpr double kThinCell = 4.5;
 
 hipError_t launch_find_neighbors(sph_ctx ctx, const sph_particles &p, const sph_nbrs &nb,
                                  const StepMask &mask)
@@ -1337,8 +1347,10 @@ hipError_t launch_find_neighbors(sph_ctx ctx, const sph_particles &p, const sph_
         mask, s2max)
     // (tiles without a particle whose step closes exit at once)
     const int64_t live = mask.bin ? std::min(tiles, mask.active) : tiles;
+    const Grid &g = ctx->grid;
+    const bool thin = (double)p.n < kThinCell * g.nc[0] * g.nc[1] * g.nc[2];
     if (live <= kCuTiles && tiles <= 32 * kCuTiles) SPH_SEARCH(16);
-    else if (tiles <= kSharedTiles) SPH_SEARCH(4);
+    else if (tiles <= (thin ? kThinTiles : kSharedTiles)) SPH_SEARCH(4);
     else SPH_SEARCH(1);
 #undef SPH_SEARCH
     ktime_end(ctx, tk);

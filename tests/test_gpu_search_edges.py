@@ -74,3 +74,12 @@ def test_unions_about_as_large_as_held(spread, k, periodic):
           f"more: {(n > 104).sum()}", flush=True)
     assert (n <= 92).any() and ((n > 92) & (n <= 104)).any()
     _check(ic, int(2.5 * k * (1 + spread) ** 3) + 24)
+
+
+@pytest.mark.parametrize("n", [65_536, 65_537, 131_072])
+@pytest.mark.parametrize("k,spread", [(2, 0.0), (17, 0.0), (22, 0.0), (6, 0.3), (10, 0.3)])
+def test_thin_cells(n, k, spread):
+    """Either side of 4.5 particles per cell and of the tiles from which on a run
+    with fewer takes one wave per tile."""
+    print(f"thin n={n} k={k} spread={spread}", flush=True)
+    _check(_cloud(n, k, spread, (0, 0, 1)), int(3 * k * (1 + spread) ** 3) + 24)
