@@ -1059,9 +1059,10 @@ find_neighbors_kernel(int64_t n, int64_t ld, const SearchRec *__restrict__ srec,
 // rule of IEEE operations (cbrt_newton), so that any implementation of the
 // same rule gets the same h.
 
-// Cells walked on one axis for a reach of r: those the sphere meets on an open
-// axis; the own one and k (1 or 2) to either side on a periodic one, or every cell
-// once where it has fewer than that (all).
+// Cells walked on one axis for a reach of r: those the sphere meets, on a periodic
+// axis of the own one and k (1 or 2) to either side, or every cell once where it has
+// fewer than that (all). (A position outside a periodic axis's range: all of the own
+// one and k.)
 struct AxisCells {
     int first, n;
     bool all;
@@ -1077,7 +1078,13 @@ __device__ __forceinline__ AxisCells axis_cells(const Grid &g, int a, int own, d
     }
     const int k = r * g.inv_s[a] * (1.0 + 1e-12) <= 1.0 ? 1 : 2;
     if (g.nc[a] < 2 * k + 1) return AxisCells{0, g.nc[a], true};
-    return AxisCells{own - k, 2 * k + 1, false};
+    const double f = (x - g.lo[a]) * g.inv_s[a], fr = r * g.inv_s[a] + 1e-6;
+    int lo = own - k, hi = own + k;
+    if (f >= 0.0 && f <= (double)g.nc[a]) {
+        lo = max(lo, (int)floor(f - fr));
+        hi = min(hi, (int)floor(f + fr));
+    }
+    return AxisCells{lo, hi - lo + 1, false};
 }
 
 // Words of the on-device iteration (ctx->it_words): [1] the first sweep at which
