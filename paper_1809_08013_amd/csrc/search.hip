@@ -1135,7 +1135,9 @@ __device__ __forceinline__ double cbrt_newton(double a)
 //
 // The lanes gather the squares of the distances within kHMargin times the
 // particle's reach into LDS, and count from there for as long as h stays within
-// it and they fit; else they gather again. The cells were built for a largest h
+// it and they fit; else they gather again. (For a target whose list would not fit
+// they gather without the margin: 300,000 particles, target 150, 2.29 -> 1.37 ms,
+// periodic 3.52 -> 1.40; 200, 2.54 -> 2.22 and 4.35 -> 3.62.) The cells were built for a largest h
 // that the sweeps may outgrow: a particle with 2 h_i up to two cells walks the
 // cells its sphere meets, beyond that it raises IT_REACH and stops. Each cell
 // reached without a periodic image is walked only in its window for the sphere. Periodic: some axis of the box is periodic (then each pair takes
@@ -1185,6 +1187,8 @@ h_iteration_kernel(int64_t n, const SearchRec *__restrict__ srec,
     int32_t sweep = first;
     int cnt = 0, nlist = 0;
     double rc2 = -1.0;  // the list holds every r^2 below this
+    // a list of the target's neighbours with the margin would not fit
+    const bool margin = n_target * (kHMargin * kHMargin * kHMargin) <= kHList;
     bool run = active && sweep < stop;
     while (run) {
         const double s = 2.0 * hh, s2 = s * s;
@@ -1193,7 +1197,7 @@ h_iteration_kernel(int64_t n, const SearchRec *__restrict__ srec,
         if (s2 <= rc2) {
             for (int q = sub; q < nlist; q += kHLanes) cnt += list[q] < s2 ? 1 : 0;
         } else {
-            double Rc = kHMargin * R;
+            double Rc = margin ? kHMargin * R : R;
             bool outgrown = false;
 #pragma unroll
             for (int a = 0; a < 3; ++a) {

@@ -20,7 +20,7 @@ def check(ic, **opts):
     h, cnt, sweeps = O.smoothing_length(ic.x, ic.y, ic.z, ic.h, ic.lo, ic.hi, ic.periodic, **opts)
     ctx = S.Context(ic.n, 16)
     st = S.SphState(ic, 16)
-    shortest = min([b - a for a, b, p in zip(ic.lo, ic.hi, ic.periodic) if p])
+    shortest = min([b - a for a, b, p in zip(ic.lo, ic.hi, ic.periodic) if p], default=np.inf)
     if 4.0 * h.max() >= shortest:  # (refused as documented: the last h is too large)
         with pytest.raises(S.SphError) as e:
             S.sph_smoothing_length(ctx, st, **opts)
@@ -49,3 +49,15 @@ def test_cells_of_periodic_axes(cells, spread, periodic):
     print(f"periodic lengths cells={cells} spread={spread} {periodic} target={target}", flush=True)
     check(ic, n_target=float(target), lo_count=max(0, target - target // 20),
           hi_count=target + target // 20, max_iter=4)
+
+
+@pytest.mark.parametrize("target", [143, 144, 145, 146, 190, 193, 400])
+@pytest.mark.parametrize("periodic", [(0, 0, 0), (1, 1, 1)])
+def test_targets_about_the_list(target, periodic):
+    """Targets whose list with its margin fits (up to 144), just does not, and whose
+    bare list does not."""
+    n = 6001
+    h = 0.5 * (1.3 * target / (4.18879 * n)) ** (1 / 3)
+    ic = I.random_cloud(n, seed=target, h_min=0.6 * h, h_max=1.1 * h, periodic=periodic)
+    print(f"lengths target={target} periodic={periodic}", flush=True)
+    check(ic, n_target=float(target), lo_count=target - 2, hi_count=target + 2, max_iter=7)
