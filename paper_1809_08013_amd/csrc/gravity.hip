@@ -79,8 +79,11 @@ pack_grav_kernel(int64_t n, const double *__restrict__ x, const double *__restri
 
 // Shares of the sum: the j are cut into up to this many ranges, each summed by
 // its own blocks, so that few particles still fill the chip (the partial sums
-// take three of the reorder scratch's rows each).
+// take three of the reorder scratch's rows each). Up to kDirectAlone particles the
+// launch that adds the shares up takes longer than they save: 64 particles 7.7 us
+// with one share, 9.9 with eight, 100: 10.8 and 9.9, 256: 23 and 10.
 constexpr int kDirectShares = kPermFields / 3;
+constexpr int64_t kDirectAlone = 80;
 
 // What bounds it: FP64 issue, 18 instructions a pair. 40,009 particles (157
 // blocks for 256 CUs when one block did the whole sum, 23 instructions a pair):
@@ -733,7 +736,8 @@ hipError_t launch_gravity_direct(sph_ctx ctx, const sph_particles &p, double eps
                                                                     ctx->drec);
     // eight waves per SIMD (2,048 blocks) where the shares allow it
     const unsigned blocks = blocks_for(p.n, kThreads);
-    const unsigned shares = std::max(1u, std::min<unsigned>(kDirectShares, 2048u / blocks));
+    const unsigned shares =
+        p.n <= kDirectAlone ? 1u : std::max(1u, std::min<unsigned>(kDirectShares, 2048u / blocks));
     const dim3 grid(blocks, shares);
     double *part = ctx->perm_tmp;  // (no build is under way)
     if (eps * eps > 0.0)

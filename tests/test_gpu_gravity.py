@@ -63,3 +63,11 @@ def test_tree_groups_and_leaves(n, leaf):
     scale = np.where(scale > 0, scale, 1.0)
     for a, b in (("gx", gx), ("gy", gy), ("gz", gz)):
         assert np.max(np.abs(got[a] - b) / scale) <= 1e-12
+
+
+@pytest.mark.parametrize("eps", [0.0, 0.01])
+@pytest.mark.parametrize("n", [2, 79, 80, 81, 82])
+def test_direct_sum_of_few(n, eps):
+    """Either side of the particles from which on the sum is cut into shares, within
+    the bound of test_direct_sum_shares."""
+    test_direct_sum_shares(n, eps)
