@@ -664,9 +664,10 @@ sph_status check_eos(sph_ctx ctx, const sph_particles *p, const sph_params *prm,
     return SPH_OK;
 }
 
-// sph_momentum_energy; eos: after sph_eos (whose checks have passed).
-sph_status momentum(sph_ctx ctx, const sph_particles *p, const sph_box *box, const sph_nbrs *nb,
-                    const sph_params *prm, const sph_fields *f, const sph_accel *a, bool eos)
+// The checks of sph_momentum_energy.
+sph_status check_momentum(sph_ctx ctx, const sph_particles *p, const sph_box *box,
+                          const sph_nbrs *nb, const sph_params *prm, const sph_fields *f,
+                          const sph_accel *a)
 {
     if (!ctx) return fail(nullptr, SPH_E_INVALID, "ctx is NULL");
     sph_status s;
@@ -682,7 +683,23 @@ sph_status momentum(sph_ctx ctx, const sph_particles *p, const sph_box *box, con
         return fail(ctx, SPH_E_INVALID, "rho, c, pr2, ax, ay, az, dudt, mumax are required");
     if (prm->volume == SPH_VOLUME_GENERALISED && !p->xw)
         return fail(ctx, SPH_E_INVALID, "generalised volume elements need p->xw");
-    SPH_HIP(ctx, launch_momentum(ctx, *p, *nb, *prm, *f, *a, eos));
+    return SPH_OK;
+}
+
+// sph_eos and sph_momentum_energy, the EOS in the pair records' pass; on its own
+// where the momentum's arguments are refused, as by the two calls.
+sph_status eos_and_momentum(sph_ctx ctx, const sph_particles *p, const sph_box *box,
+                            const sph_nbrs *nb, const sph_params *prm, const sph_fields *f,
+                            const sph_accel *a)
+{
+    sph_status s;
+    if ((s = check_eos(ctx, p, prm, f)) != SPH_OK) return s;
+    if (p->n == 0) return check_momentum(ctx, p, box, nb, prm, f, a);
+    if ((s = check_momentum(ctx, p, box, nb, prm, f, a)) != SPH_OK) {
+        SPH_HIP(ctx, launch_eos(ctx, *p, *prm, *f));
+        return s;
+    }
+    SPH_HIP(ctx, launch_momentum(ctx, *p, *nb, *prm, *f, *a, true));
     return SPH_OK;
 }
 
@@ -703,7 +720,10 @@ sph_status sph_momentum_energy(sph_ctx ctx, const sph_particles *p, const sph_bo
                                const sph_nbrs *nb, const sph_params *prm,
                                const sph_fields *f, const sph_accel *a)
 {
-    return momentum(ctx, p, box, nb, prm, f, a, false);
+    const sph_status s = check_momentum(ctx, p, box, nb, prm, f, a);
+    if (s != SPH_OK || p->n == 0) return s;
+    SPH_HIP(ctx, launch_momentum(ctx, *p, *nb, *prm, *f, *a));
+    return SPH_OK;
 }
 
 sph_status sph_integrate(sph_ctx ctx, const sph_particles *p, const sph_box *box,
@@ -772,8 +792,7 @@ sph_status sph_init_forces(sph_ctx ctx, const sph_particles *p, const sph_box *b
         if (!p->rho_ref) return fail(ctx, SPH_E_INVALID, "set_rho_ref needs rho_ref");
         SPH_HIP(ctx, launch_copy(ctx, p->rho_ref, f->rho, p->n));
     }
-    if ((s = check_eos(ctx, p, prm, f)) != SPH_OK) return s;
-    if ((s = momentum(ctx, p, box, nb, prm, f, a, true)) != SPH_OK) return s;
+    if ((s = eos_and_momentum(ctx, p, box, nb, prm, f, a)) != SPH_OK) return s;
     return sph_timestep(ctx, p, prm, f, a, dt_dev, diag_dev);
 }
 
@@ -800,8 +819,7 @@ sph_status sph_step(sph_ctx ctx, const sph_particles *p, const sph_box *box, dou
     if ((s = sph_find_neighbors(ctx, p, box, nb)) != SPH_OK) return s;
     if (!f) return fail(ctx, SPH_E_INVALID, "fields is NULL");
     if ((s = density(ctx, p, box, nb, prm, f->rho, true)) != SPH_OK) return s;
-    if ((s = check_eos(ctx, p, prm, f)) != SPH_OK) return s;
-    if ((s = momentum(ctx, p, box, nb, prm, f, a, true)) != SPH_OK) return s;
+    if ((s = eos_and_momentum(ctx, p, box, nb, prm, f, a)) != SPH_OK) return s;
     return timestep(ctx, p, prm, f, a, dt_dev, diag_dev, true);
 }
 
