@@ -347,7 +347,7 @@ sph_status sph_ctx_create(sph_ctx *out, int64_t n_max, int32_t max_nb, sph_strea
 {
     if (!out) return fail(nullptr, SPH_E_INVALID, "out is NULL");
     *out = nullptr;
-    if (n_max < 1 || n_max > ((int64_t)1 << 31) - kSortTile)
+    if (n_max < 1 || n_max > kMaxParticles)
         return fail(nullptr, SPH_E_INVALID, "n_max = %lld out of range", (long long)n_max);
     if (max_nb < 1 || max_nb > 4096)
         return fail(nullptr, SPH_E_INVALID, "max_nb = %d out of range [1, 4096]", max_nb);

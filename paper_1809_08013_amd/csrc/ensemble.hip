@@ -723,7 +723,7 @@ sph_status sph_ens_create(sph_ens *out, const sph_ens_config *cfg)
     const int64_t bpp = arena_bytes_per_particle(cfg->max_nb);
     const int64_t fixed = (int64_t)16 << 20;
     int64_t cap = (cfg->hbm_budget_bytes - fixed) / bpp;
-    cap = std::min<int64_t>(cap, ((int64_t)1 << 31) - kSortTile - 1);
+    cap = std::min<int64_t>(cap, kMaxParticles - 1);
     if (cap < cfg->max_n_per_run)
         return efail(nullptr, SPH_E_INVALID,
                      "a budget of %lld bytes holds %lld particles (%lld B each), less than "

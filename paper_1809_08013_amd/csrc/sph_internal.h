@@ -21,6 +21,7 @@ enum : uint32_t {
 };
 
 constexpr int kMaxAxisCells = 1024;   // 10 Morton bits per axis
+constexpr int64_t kMaxParticles = ((int64_t)1 << 31) - 2048;  // of a context
 constexpr int kRadixBits = 8;
 constexpr int kRadixBins = 1 << kRadixBits;
 constexpr int kSortTile = 4096;                        // keys per tile, at most

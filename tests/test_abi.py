@@ -163,3 +163,12 @@ def test_density_noalloc_host_checks():
     assert L.sph_density_noalloc(C.byref(p0), C.byref(box), C.byref(nb), C.byref(prm), None,
                                  None) == S.SPH_OK
 
+
+
+def test_largest_context():
+    """A context of 2^31 - 2048 particles is a matter of memory (or of a device), not
+    of the argument; one more is refused."""
+    L = _lib()
+    h = C.c_void_p()
+    assert L.sph_ctx_create(C.byref(h), (1 << 31) - 2047, 10, None) == S.SPH_E_INVALID
+    assert L.sph_ctx_create(C.byref(h), (1 << 31) - 2048, 10, None) in (S.SPH_E_NOMEM, S.SPH_E_HIP)
