@@ -1202,9 +1202,9 @@ h_iteration_kernel(int64_t n, const SearchRec *__restrict__ srec,
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
                 const double c = g.inv_s[a] * (1.0 + 1e-12);
-                // (an open axis of one cell holds every reach: no rebuild would
-                // give it a larger cell)
-                const bool holds = g.nc[a] == 1 && !g.periodic[a] ? R < INFINITY : R * c <= 2.0;
+                // (an open axis of one cell holds every finite h, also one whose
+                // square is not: no rebuild would give it a larger cell)
+                const bool holds = g.nc[a] == 1 && !g.periodic[a] ? hh < INFINITY : R * c <= 2.0;
                 outgrown = outgrown || !holds;
                 if (!(Rc * c <= 2.0)) Rc = R;
             }

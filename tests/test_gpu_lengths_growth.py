@@ -1,0 +1,37 @@
+"""Smoothing lengths that no count ever brings into the band: they grow at every
+sweep, past the point where their square overflows, to the last sweep or until h is
+no longer finite (SPH_E_NONFINITE)."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle as O  # noqa: E402
+from paper_1809_08013_amd import inputs as I  # noqa: E402
+from paper_1809_08013_amd import sph as S  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n", [1, 3])
+@pytest.mark.parametrize("max_iter", [400, 700, 3000])
+def test_growth_to_the_end(n, max_iter):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    torch.cuda.set_device(0)
+    print(f"growth n={n} max_iter={max_iter}", flush=True)
+    ic = I.random_cloud(n, seed=n, h_min=0.1, h_max=0.1)
+    ctx, st = S.Context(n, 16), S.SphState(ic, 16)
+    # a count stays below the band: h doubles (n = 1) or grows by 1.24 (n = 3)
+    opts = dict(n_target=6.0 if n == 3 else 100.0, lo_count=5, hi_count=10, max_iter=max_iter)
+    ends = max_iter * np.log10(2.0 if n == 1 else 0.5 * (1 + 3 ** (1 / 3)))
+    if ends > 308:
+        with pytest.raises(S.SphError) as e:
+            S.sph_smoothing_length(ctx, st, **opts)
+        assert e.value.status == S.SPH_E_NONFINITE
+        return
+    h, cnt, sweeps = O.smoothing_length(ic.x, ic.y, ic.z, ic.h, ic.lo, ic.hi, ic.periodic, **opts)
+    assert sweeps == max_iter and h.min() > 1e30
+    assert S.sph_smoothing_length(ctx, st, **opts) == sweeps
+    got = st.host(["h", "count"])
+    assert np.array_equal(got["count"], cnt) and np.array_equal(got["h"], h)
