@@ -520,6 +520,7 @@ int64_t orc_neighbors_subset(int64_t n, const double *x, const double *y,
  */
 static double cbrt_newton(double a)
 {
+    if (!(a > 0.0)) return 0.0; /* underflowed: no factor of 8 brings it up */
     int k = 0;
     while (a >= 8.0) { a *= 0.125; ++k; }
     while (a < 1.0) { a *= 8.0; --k; }

@@ -1111,9 +1111,11 @@ __global__ void h_end_kernel(uint32_t *words)
 // operations gets the same number: a is brought into [1, 8) by exact
 // factors of 8, y starts at 3/2 and takes seven steps y <- (2 y + a / y^2) / 3
 // (the relative error 1/2 of the start squares at each step), and the
-// result is scaled back by the matching power of 2.
+// result is scaled back by the matching power of 2. (A quotient that has underflowed
+// to 0, which no factor of 8 would bring up, has the root 0.)
 __device__ __forceinline__ double cbrt_newton(double a)
 {
+    if (!(a > 0.0)) return 0.0;
     int k = 0;
     while (a >= 8.0) {
         a *= 0.125;

@@ -35,3 +35,18 @@ def test_growth_to_the_end(n, max_iter):
     assert S.sph_smoothing_length(ctx, st, **opts) == sweeps
     got = st.host(["h", "count"])
     assert np.array_equal(got["count"], cnt) and np.array_equal(got["h"], h)
+
+
+def test_target_that_underflows():
+    """A target of the smallest positive double: the quotient by a count is 0, its
+    cube root too, and h halves until nothing is inside it, then doubles."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    torch.cuda.set_device(0)
+    ic = I.random_cloud(300, seed=1, h_min=0.1, h_max=0.15)
+    opts = dict(n_target=5e-324, lo_count=0, hi_count=0, max_iter=6)
+    h, cnt, sweeps = O.smoothing_length(ic.x, ic.y, ic.z, ic.h, ic.lo, ic.hi, ic.periodic, **opts)
+    ctx, st = S.Context(ic.n, 16), S.SphState(ic, 16)
+    assert S.sph_smoothing_length(ctx, st, **opts) == sweeps
+    got = st.host(["h", "count"])
+    assert np.array_equal(got["count"], cnt) and np.array_equal(got["h"], h)
