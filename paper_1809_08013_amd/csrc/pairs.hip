@@ -24,6 +24,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "sinc.h"
 #include "sph_internal.h"
 
 namespace sph {
@@ -105,49 +106,9 @@ __device__ __forceinline__ R m4_dw(R q)
 // S(x) = sin(x)/x. Both vanish for q >= 2 and have w(0) = 1, like M4.
 enum { KF_M4 = 0, KF_WENDLAND = 1, KF_SINC = 2 };
 
-// The sinc shape S = sin(x) / x, x = pi q / 2, and dS/dq for q in [0, 2) in FP64,
-// from the Taylor series of S in q^2. S: up to x^22 on [0, 1], where the first
-// omitted term is below 1e-18; beyond, by the reflection S = (2 - q) / q times S at
-// 2 - q, which keeps the relative accuracy where S goes to zero. dS/dq: up to
-// x^30 on all of [0, 2) (it has no zero but at q = 0, where the series is q times
-// a constant). 22 instructions for S and 17 for dS/dq, where sin, sincos and their
-// divisions took some 60 to 100: 262,000
-// particles, exponent 5: density 160 -> 126 us, IAD matrices 361 -> 162, momentum
-// with IAD 414 -> 352.
-struct SincSeries {
-    double s[12], d[15];
-    constexpr SincSeries() : s(), d()
-    {
-        double f = 1.0, p = 1.0;  // (2k + 1)! and (pi / 2)^(2k)
-        for (int k = 0; k < 16; ++k) {
-            if (k > 0) {
-                f *= (double)(2 * k) * (double)(2 * k + 1);
-                p *= 1.5707963267948966 * 1.5707963267948966;
-            }
-            const double c = (k % 2 ? -1.0 : 1.0) * (p / f);
-            if (k < 12) s[k] = c;
-            if (k > 0) d[k - 1] = (double)(2 * k) * c;
-        }
-    }
+struct RcpEstimate {
+    __device__ __forceinline__ double operator()(double q) const { return __builtin_amdgcn_rcp(q); }
 };
-__device__ __forceinline__ double sinc_s(double q)
-{
-    constexpr SincSeries c{};
-    const double y = fmin(q, 2.0 - q), y2 = y * y;
-    double v = c.s[11];
-#pragma unroll
-    for (int k = 10; k >= 0; --k) v = __builtin_fma(v, y2, c.s[k]);
-    return q > 1.0 ? v * (y * fast_rcp(q)) : v;
-}
-__device__ __forceinline__ double sinc_ds(double q)
-{
-    constexpr SincSeries c{};
-    const double q2 = q * q;
-    double v = c.d[14];
-#pragma unroll
-    for (int k = 13; k >= 0; --k) v = __builtin_fma(v, q2, c.d[k]);
-    return q * v;
-}
 
 template <int KF, typename R>
 __device__ __forceinline__ R shape_w(R q, int n)
@@ -162,7 +123,7 @@ __device__ __forceinline__ R shape_w(R q, int n)
         if (!(q < R(2))) return R(0);
         R sx;
         if constexpr (sizeof(R) == 8) {
-            sx = sinc_s(q);
+            sx = sinc_s(q, RcpEstimate{});
         } else {
             const R x = R(1.5707963267948966) * q;
             sx = x < R(1e-4) ? R(1) - x * x * R(1.0 / 6.0) : sin(x) / x;
@@ -185,7 +146,7 @@ __device__ __forceinline__ R shape_dw(R q, int n)
         if (!(q < R(2))) return R(0);
         R sx, dsq;  // S and dS/dq
         if constexpr (sizeof(R) == 8) {
-            sx = sinc_s(q);
+            sx = sinc_s(q, RcpEstimate{});
             dsq = sinc_ds(q);
         } else {
             const R x = R(1.5707963267948966) * q;
@@ -647,7 +608,7 @@ __device__ __forceinline__ double kernel_w_plain(double r, double hh, double sig
         return 21.0 / (16.0 * M_PI * hh * hh * hh) * t * t * t * t * (1.0 + 2.0 * q);
     } else {
         if (q >= 2.0) return 0.0;
-        const double sx = sinc_s(q);
+        const double sx = sinc_s(q, RcpEstimate{});
         double pw = sx;
         for (int k = 1; k < n; ++k) pw *= sx;
         return sigma / (hh * hh * hh) * pw;
