@@ -120,13 +120,22 @@ def square_patch_pressure(x: np.ndarray, y: np.ndarray, L: float = 1.0,
                                     ((mm * np.pi / L) ** 2 + (nn * np.pi / L) ** 2))
     out = np.empty(x.shape[0])
 
+    # The matrix products are taken one at a time: the BLAS at hand gives wrong values
+    # when several threads call it at once (differences of up to 3 here).
+    import os
+    import threading
+    from concurrent.futures import ThreadPoolExecutor
+    blas = threading.Lock()
+
     def rows(a: int, b: int) -> None:
         xs = (x[a:b] + 0.5 * L) / L
         ys = (y[a:b] + 0.5 * L) / L
         sx = np.sin(np.pi * np.outer(xs, ks))  # (rows, K)
         sy = np.sin(np.pi * np.outer(ys, ks))
         # P_i = sum_mn sx[i,m] coef[m,n] sy[i,n]
-        out[a:b] = rho * np.sum((sx @ coef) * sy, axis=1)
+        with blas:
+            sc = sx @ coef
+        out[a:b] = rho * np.sum(sc * sy, axis=1)
 
     # Fixed row chunks bound the (N, K) temporaries; chunks are independent,
     # so the result does not depend on how many threads evaluate them.
@@ -136,8 +145,6 @@ def square_patch_pressure(x: np.ndarray, y: np.ndarray, L: float = 1.0,
         for a, b in spans:
             rows(a, b)
     else:
-        import os
-        from concurrent.futures import ThreadPoolExecutor
         with ThreadPoolExecutor(max_workers=min(16, os.cpu_count() or 1)) as ex:
             list(ex.map(lambda ab: rows(*ab), spans))
     return out
