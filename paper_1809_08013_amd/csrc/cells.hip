@@ -282,7 +282,7 @@ radix_scatter_kernel(const uint32_t *__restrict__ kin, const int32_t *__restrict
     const int64_t tile0 = (int64_t)blockIdx.x * (Threads * Items);
     if (tile0 >= n) return;
     constexpr int kWaves = Threads / 64, kBins = 1 << Bits, kQuads = kBins / 256;
-    __shared__ uint32_t wcnt[kWaves][kBins];
+    __shared__ __attribute__((aligned(16))) uint32_t wcnt[kWaves][kBins];  // (written as uint4)
     __shared__ uint32_t base[kBins];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (flag_part && blockIdx.x == 0) {
@@ -303,7 +303,7 @@ radix_scatter_kernel(const uint32_t *__restrict__ kin, const int32_t *__restrict
     }
     if constexpr (Self) {
         // every wave adds up its share of the tiles, four digits a lane
-        __shared__ uint32_t wbefore[kWaves][kBins];
+        __shared__ __attribute__((aligned(16))) uint32_t wbefore[kWaves][kBins];
         __shared__ uint32_t wsum[kBins / 64];
         const int live = (int)((n + Threads * Items - 1) / (Threads * Items));
 #pragma unroll
