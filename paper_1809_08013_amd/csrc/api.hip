@@ -995,9 +995,9 @@ sph_status sph_smoothing_length(sph_ctx ctx, sph_particles *p, const sph_box *bo
                                ctx->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
         if (e != hipSuccess) return hip_fail(ctx, e, "smoothing-length sweeps");
-        sweep = (int32_t)words[3];
-        if (words[2]) break;      // done: the counts of sweep `sweep` are final
-        if (!words[4]) return fail(ctx, SPH_E_HIP, "smoothing-length sweeps did not finish");
+        sweep = (int32_t)words[IT_SWEEP];
+        if (words[IT_DONE]) break;      // done: the counts of sweep `sweep` are final
+        if (!words[IT_REACH]) return fail(ctx, SPH_E_HIP, "smoothing-length sweeps did not finish");
     }
     *iterations = sweep;
     // cells for the final h (this may reorder the particles, and the cells'

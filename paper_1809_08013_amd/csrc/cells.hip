@@ -437,9 +437,9 @@ permute_store_kernel(int64_t n, const int64_t *n_dev, int64_t stride, PermFields
 // caller's arrays in cell order, writes the search records (position and
 // (2h)^2), the density records if asked for and the cell table (a particle whose
 // predecessor lies in another cell ends that one and starts its own; cells without
-// particles stay empty). With varying h also each cell's largest (2h)^2, as the ordered bit pattern of a
-// positive double: a segmented maximum over the wave's lanes (a cell's
-// particles are consecutive), then one atomic per cell and wave.
+// particles stay empty). With varying h also each cell's largest (2h)^2, as the
+// ordered bit pattern of a positive double: a segmented maximum over the wave's lanes
+// (a cell's particles are consecutive), then one atomic per cell and wave.
 __global__ void __launch_bounds__(256)
 build_tail_kernel(int64_t n, const int32_t *__restrict__ perm, const uint32_t *__restrict__ keys,
                   BuildArrays A, Grid g, SearchRec *__restrict__ srec,

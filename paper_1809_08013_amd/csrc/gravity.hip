@@ -82,7 +82,8 @@ pack_grav_kernel(int64_t n, const double *__restrict__ x, const double *__restri
 // take three of the reorder scratch's rows each). Up to kDirectAlone particles the
 // launch that adds the shares up takes longer than they save: 64 particles 7.7 us
 // with one share, 9.9 with eight, 100: 10.8 and 9.9, 256: 23 and 10.
-constexpr int kDirectShares = kPermFields / 3;
+constexpr int kDirectShares = 8;
+static_assert(3 * kDirectShares <= kPermFields, "the shares' partial sums");
 constexpr int64_t kDirectAlone = 80;
 
 // What bounds it: FP64 issue, 18 instructions a pair. 40,009 particles (157

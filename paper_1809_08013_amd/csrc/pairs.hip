@@ -195,11 +195,6 @@ __device__ __forceinline__ void wave_lds_fence()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__device__ __forceinline__ double4 lds_load4(const char *p)
-{
-    return *reinterpret_cast<const double4 *>(p);
-}
-
 // ---------------------------------------------------------------------------
 // Summation density: rho_i = (m_i + sum_j m_j w(r_ij / h_i)) / (pi h_i^3).
 // Records: DensRec {x, y, z, m}, 32 B; two lanes fetch one record.
@@ -965,10 +960,10 @@ __device__ __forceinline__ void momentum_tile(
                     tz = dz;
                     tv = vdotr;
                 } else {
-                sx = fma_r(-mG, dx, sx);
-                sy = fma_r(-mG, dy, sy);
-                sz = fma_r(-mG, dz, sz);
-                su = fma_r(mG, vdotr, su);
+                    sx = fma_r(-mG, dx, sx);
+                    sy = fma_r(-mG, dy, sy);
+                    sz = fma_r(-mG, dz, sz);
+                    su = fma_r(mG, vdotr, su);
                 }
             }
             mum = fmax(mum, fabs(mu));
@@ -1082,7 +1077,6 @@ pack_pair_kernel(int64_t n, const int64_t *n_dev, const double *__restrict__ x,
     // PairRec32.
     constexpr int kStride = 17;
     constexpr int kRecBytes = R32 ? (int)sizeof(PairRec32) : (int)sizeof(PairRec);
-    constexpr int kParts = kRecBytes / 16;  // chunks per record in memory
     __shared__ double lds[4][64 * kStride];
     if (n_dev) n = *n_dev;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1144,7 +1138,6 @@ pack_pair_kernel(int64_t n, const int64_t *n_dev, const double *__restrict__ x,
                     make_double2(src[0], src[1]);
             }
         }
-        (void)kParts;
         wave_lds_fence();
     }
 }

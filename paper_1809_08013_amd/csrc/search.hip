@@ -84,7 +84,6 @@ template <>
 struct SearchShape<16> : SearchShape<4> {
     static constexpr int kEntries = 1024;
 };
-enum WrapMode { WRAP_NONE = 0, WRAP_CELL = 1, WRAP_PAIR = 2 };
 
 __device__ __forceinline__ uint32_t spread3(uint32_t v)
 {
@@ -142,25 +141,15 @@ __device__ __forceinline__ double uniform_f64(double v)
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-// Relation test: r2 < (2h_i)^2 or r2 < (2h_j)^2, i.e. r2 < (2 max(h_i,h_j))^2.
-// UniformH: every particle has the same h, one compare against the lane's
-// own (2h)^2. sh: the per-cell image shift (WRAP_CELL).
-template <int Mode, bool UniformH>
-__device__ __forceinline__ bool related(const SearchRec &me, const SearchRec &o, const Grid &g,
-                                        const double (&sh)[3])
+// Relation test: r2 < (2h_i)^2 or r2 < (2h_j)^2, i.e. r2 < (2 max(h_i,h_j))^2, with
+// the minimum image on periodic axes.
+__device__ __forceinline__ bool related(const SearchRec &me, const SearchRec &o, const Grid &g)
 {
     double dx = me.x - o.x, dy = me.y - o.y, dz = me.z - o.z;
-    if (Mode == WRAP_CELL) {
-        dx += sh[0];
-        dy += sh[1];
-        dz += sh[2];
-    } else if (Mode == WRAP_PAIR) {
-        if (g.periodic[0]) dx = min_image_sel(dx, g.len[0], g.half[0]);
-        if (g.periodic[1]) dy = min_image_sel(dy, g.len[1], g.half[1]);
-        if (g.periodic[2]) dz = min_image_sel(dz, g.len[2], g.half[2]);
-    }
+    if (g.periodic[0]) dx = min_image_sel(dx, g.len[0], g.half[0]);
+    if (g.periodic[1]) dy = min_image_sel(dy, g.len[1], g.half[1]);
+    if (g.periodic[2]) dz = min_image_sel(dz, g.len[2], g.half[2]);
     const double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
-    if (UniformH) return r2 < me.s2;
     return (r2 < me.s2) | (r2 < o.s2);
 }
 
@@ -410,15 +399,6 @@ __device__ __forceinline__ float block_bits(float x, float y, float z, float n, 
 __device__ __forceinline__ int cand_of_lane(int lane)
 {
     return ((lane & 12) << 2) | ((lane & 48) >> 2) | (lane & 3);
-}
-
-// The FP64 relation of particle `me` with one record, minimum image on
-// periodic axes.
-__device__ __forceinline__ bool related_exact(const SearchRec &me, const SearchRec &o,
-                                              const Grid &g)
-{
-    const double no_shift[3] = {0.0, 0.0, 0.0};
-    return related<WRAP_PAIR, false>(me, o, g, no_shift);
 }
 
 // Barrier of the tile's waves.
@@ -789,7 +769,7 @@ __device__ __forceinline__ bool search_tile(
 #pragma unroll 1
                 for (int c = 0; c < kWave; ++c) {
                     const int j = __builtin_amdgcn_readfirstlane(candidate_at(min(ub + c, len - 1)));
-                    acc = (acc << 1) | (related_exact(mine, srec[j], g) ? 1u : 0u);
+                    acc = (acc << 1) | (related(mine, srec[j], g) ? 1u : 0u);
                     if (c == 31) bits[0] = acc;
                 }
                 bits[1] = acc;
@@ -829,7 +809,7 @@ __device__ __forceinline__ bool search_tile(
                             const uint32_t bt = 0x80000000u >> t;
                             a &= ~bt;
                             const SearchRec oj = srec[candidate_at(ub + 32 * r + t)];
-                            bits[r] = related_exact(mine, oj, g) ? bits[r] | bt : bits[r] & ~bt;
+                            bits[r] = related(mine, oj, g) ? bits[r] | bt : bits[r] & ~bt;
                         }
                     }
                 }
@@ -952,7 +932,6 @@ __device__ __forceinline__ void lane_lists(
                         (int)compact3(mkey >> 2)};
     const Grid &gl = Multi ? b.runs[my_slot].grid : g0;
     const int64_t cbl = Multi ? (int64_t)b.runs[my_slot].cell_base : 0;
-    const double no_shift[3] = {0.0, 0.0, 0.0};
     uint32_t ks[32];
 #pragma unroll
     for (int s = 0; s < 32; ++s) {
@@ -1001,7 +980,7 @@ __device__ __forceinline__ void lane_lists(
         for (int32_t j = a; j < e; ++j) {
             const SearchRec o = nx;
             if (j + 1 < e) nx = srec[j + 1];
-            if (related<WRAP_PAIR, false>(me, o, gl, no_shift) && j != ii) {
+            if (related(me, o, gl) && j != ii) {
                 if (cnt < max_nb) idx[(int64_t)cnt * ld + i] = j;
                 ++cnt;
             }
@@ -1017,8 +996,8 @@ __device__ __forceinline__ void lane_lists(
 // pipe is busy 17% of the time. Before, each candidate was tested in FP64 by
 // every lane (8 instructions a pair row) and the bits went through HBM: the 1M
 // patch took 715 us, now 480; the 1M Evrard sphere 2,700 us, now 1,990; 104k
-// particles 229 us, now 103; 8,000 particles 188 us, now 41 (one wave did a
-// tile however few there were).
+// particles 229 us, now 103; 8,000 particles 188 us, now 36 (one wave did a
+// tile however few there were, now sixteen).
 template <bool Multi, int W>
 __global__ void __launch_bounds__(W * kWave, 4)
 find_neighbors_kernel(int64_t n, int64_t ld, const SearchRec *__restrict__ srec,
@@ -1087,15 +1066,9 @@ __device__ __forceinline__ AxisCells axis_cells(const Grid &g, int a, int own, d
     return AxisCells{lo, hi - lo + 1, false};
 }
 
-// Words of the on-device iteration (ctx->it_words): [1] the first sweep at which
-// a particle outgrew the grid's reach, [2] done (the counts are final), [3]
-// sweeps counted, [4] a particle outside the grid's reach (2 h > 2 cells): the
-// host rebuilds the cells and continues.
-enum { IT_STOP = 1, IT_DONE = 2, IT_SWEEP = 3, IT_REACH = 4, IT_WORDS = 5 };
-
 __global__ void h_begin_kernel(uint32_t *words, int32_t first)
 {
-    words[0] = words[IT_DONE] = words[IT_REACH] = 0u;
+    words[IT_DONE] = words[IT_REACH] = 0u;
     words[IT_STOP] = 0x7FFFFFFFu;
     words[IT_SWEEP] = (uint32_t)first;
 }
@@ -1142,8 +1115,9 @@ __device__ __forceinline__ double cbrt_newton(double a)
 // periodic 3.52 -> 1.40; 200, 2.54 -> 2.22 and 4.35 -> 3.62.) The cells were built for a largest h
 // that the sweeps may outgrow: a particle with 2 h_i up to two cells walks the
 // cells its sphere meets, beyond that it raises IT_REACH and stops. Each cell
-// reached without a periodic image is walked only in its window for the sphere. Periodic: some axis of the box is periodic (then each pair takes
-// the minimum image; else the separation is used as it is).
+// reached without a periodic image is walked only in its window for the sphere.
+// Periodic: some axis of the box is periodic (then each pair takes the minimum image;
+// else the separation is used as it is).
 //
 // redo = 0: h goes to `tmp`. redo = 1: to `h`; from tmp, unless a particle
 // outgrew the reach at some sweep: then every particle stops before that sweep,
@@ -1398,8 +1372,7 @@ hipError_t launch_h_iteration(sph_ctx ctx, const sph_particles &p, int32_t *coun
                               int32_t lo_count, int32_t hi_count, double n_target,
                               int32_t first_sweep, int32_t max_iter, uint32_t *words)
 {
-    // words: IT_WORDS counters; sweeps counted from first_sweep. The new h wait
-    // in the reorder scratch, which no kernel uses between two cell builds.
+    // The new h wait in the reorder scratch, which no kernel uses between two cell builds.
     const Grid &g = ctx->grid;
     const unsigned blocks = (unsigned)((p.n + 256 / kHLanes - 1) / (256 / kHLanes));
     h_begin_kernel<<<1, 1, 0, ctx->stream>>>(words, first_sweep);

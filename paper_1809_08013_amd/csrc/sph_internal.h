@@ -358,8 +358,10 @@ struct sph_ctx_s {
     int64_t n_built = -1;
 
     // permutation scratch
+    // (between two builds also: the direct sum's shares, 3 rows each, and the
+    // smoothing-length sweeps' new h)
     double *perm_tmp = nullptr;      // kPermFields * n_max
-    int32_t *perm_tmp_id = nullptr;  // n_max; also the smoothing-length sweeps' list
+    int32_t *perm_tmp_id = nullptr;  // n_max
 
     // reductions
     double *red_part = nullptr;      // kRedFields * kRedMaxBlocks
@@ -490,9 +492,11 @@ Grid make_grid(const sph_box &b, double h_max, int64_t cell_cap, int max_axis);
 hipError_t launch_max_h(sph_ctx ctx, const sph_particles &p, unsigned long long *out);
 // Sweeps first_sweep..max_iter of the count-based h iteration on the cells
 // last built, on the device: counts, the band test and the h update, with no
-// host work between sweeps. words (kItWords): [2] done, [3] last sweep, [4] a
-// particle outgrew the cells (the host rebuilds and calls again from sweep [3]).
-constexpr int kItWords = 5;
+// host work between sweeps. words (kItWords): the first sweep at which a particle
+// outgrew the cells, done (the counts are final), the last sweep, and whether a
+// particle outgrew the cells (the host rebuilds and calls again from the last sweep).
+enum { IT_STOP = 0, IT_DONE = 1, IT_SWEEP = 2, IT_REACH = 3 };
+constexpr int kItWords = 4;
 // Reorders an int32 per-particle array as the last cell build reordered the
 // particles (its sort permutation).
 hipError_t launch_permute_like_build(sph_ctx ctx, int32_t *a, int64_t n);
