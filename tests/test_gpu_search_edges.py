@@ -83,3 +83,55 @@ def test_thin_cells(n, k, spread):
     with fewer takes one wave per tile."""
     print(f"thin n={n} k={k} spread={spread}", flush=True)
     _check(_cloud(n, k, spread, (0, 0, 1)), int(3 * k * (1 + spread) ** 3) + 24)
+
+
+@pytest.mark.parametrize("n", [5_000, 20_000, 140_000])
+@pytest.mark.parametrize("spread,periodic", [(0.0, (0, 0, 0)), (0.3, (0, 0, 0)), (0.3, (1, 0, 1))])
+def test_positions_that_are_not_numbers(n, spread, periodic):
+    """NaN, infinite and huge coordinates, first in their tile and in the middle of one,
+    with sixteen, four and one wave per tile: such particles have no neighbours but
+    those of the same huge coordinate, the others have the lists they have without
+    them."""
+    print(f"not numbers n={n} spread={spread} {periodic}", flush=True)
+    ic = _cloud(n, 60, spread, periodic)
+    bad = np.random.default_rng(2).choice(n, 24, replace=False)
+    values = [np.nan, np.inf, -np.inf, 1e300]
+    for q, i in enumerate(bad):
+        (ic.x, ic.y, ic.z)[q % 3][i] = values[q % 4]
+        if q % 5 == 0:
+            ic.x[i] = ic.y[i] = ic.z[i] = np.nan
+    good = np.setdiff1d(np.arange(n), bad)
+    off, ids = O.neighbors(ic.x[good], ic.y[good], ic.z[good], ic.h[good], ic.lo, ic.hi, ic.periodic)
+    want = [np.empty(0, dtype=np.int64)] * n
+    for k, i in enumerate(good):
+        want[i] = good[ids[off[k]:off[k + 1]]]
+    with np.errstate(invalid="ignore", over="ignore"):
+        for i in bad:
+            r2 = sum((p[i] - p[bad]) ** 2 for p in (ic.x, ic.y, ic.z))
+            near = r2 < (2.0 * np.maximum(ic.h[i], ic.h[bad])) ** 2
+            want[i] = np.sort(bad[near & (bad != i)])
+    max_nb = int(2.5 * 60 * (1 + spread) ** 3)
+    ctx, st = S.Context(n, max_nb), S.SphState(ic, max_nb)
+    S.sph_build_cells(ctx, st)
+    S.sph_find_neighbors(ctx, st)
+    S.sph_ctx_check(ctx)
+    goff, gids = S.sph_export_neighbors(ctx, st)
+    assert np.array_equal(np.diff(goff), [w.size for w in want])
+    assert np.array_equal(gids, np.concatenate(want))
+
+
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+@pytest.mark.parametrize("n", [5_000, 140_000])
+def test_lengths_that_are_not_numbers(n, value):
+    """An h that is no number is above the promised bound: the calls end and the check
+    says so; a context that has seen it works on."""
+    ic = _cloud(n, 40, 0.3)
+    h_max = float(ic.h.max())
+    ic.h[::97] = value
+    ctx, st = S.Context(n, 256), S.SphState(ic, 256)
+    S.sph_build_cells(ctx, st, h_max)
+    S.sph_find_neighbors(ctx, st)
+    with pytest.raises(S.SphError) as e:
+        S.sph_ctx_check(ctx)
+    assert e.value.status == S.SPH_E_DOMAIN
+    _check(_cloud(n, 40, 0.3), 256)
