@@ -19,6 +19,9 @@ All arrays are float64 (int32 for ids) in original-id order.
 from __future__ import annotations
 
 import math
+import os
+import threading
+from concurrent.futures import ThreadPoolExecutor
 from dataclasses import dataclass, field
 
 import numpy as np
@@ -100,6 +103,11 @@ class SphIC:
                      params=self.params, meta=dict(self.meta))
 
 
+# Held around matrix products, here and in the callers' threads: the BLAS at hand gives
+# wrong values when several threads call it at once (pressures off by up to 3).
+_BLAS = threading.Lock()
+
+
 def square_patch_pressure(x: np.ndarray, y: np.ndarray, L: float = 1.0,
                           omega: float = 5.0, rho: float = 1.0,
                           kmax: int = 99) -> np.ndarray:
@@ -120,20 +128,13 @@ def square_patch_pressure(x: np.ndarray, y: np.ndarray, L: float = 1.0,
                                     ((mm * np.pi / L) ** 2 + (nn * np.pi / L) ** 2))
     out = np.empty(x.shape[0])
 
-    # The matrix products are taken one at a time: the BLAS at hand gives wrong values
-    # when several threads call it at once (differences of up to 3 here).
-    import os
-    import threading
-    from concurrent.futures import ThreadPoolExecutor
-    blas = threading.Lock()
-
     def rows(a: int, b: int) -> None:
         xs = (x[a:b] + 0.5 * L) / L
         ys = (y[a:b] + 0.5 * L) / L
         sx = np.sin(np.pi * np.outer(xs, ks))  # (rows, K)
         sy = np.sin(np.pi * np.outer(ys, ks))
         # P_i = sum_mn sx[i,m] coef[m,n] sy[i,n]
-        with blas:
+        with _BLAS:
             sc = sx @ coef
         out[a:b] = rho * np.sum(sc * sy, axis=1)
 

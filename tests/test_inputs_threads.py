@@ -1,6 +1,7 @@
 """The patch's pressure series over several row chunks, which threads evaluate, equals
 the same rows taken one chunk at a time."""
 import threading
+from concurrent.futures import ThreadPoolExecutor
 
 import numpy as np
 
@@ -18,9 +19,8 @@ def test_chunks_in_threads_equal_single_chunks():
         assert np.array_equal(I.square_patch_pressure(x, y, kmax=19), want)
 
 
-def test_products_one_at_a_time(monkeypatch):
-    """No two threads are inside a matrix product together (the values above go wrong
-    only now and then when they are)."""
+def _most_threads_in_a_product(monkeypatch, work):
+    """Largest number of threads inside a matrix product together while work runs."""
     inside, most, lock = [0], [0], threading.Lock()
 
     class Coef(np.ndarray):
@@ -43,7 +43,25 @@ def test_products_one_at_a_time(monkeypatch):
         return [m.view(Coef) for m in grid(*a, **kw)]
 
     monkeypatch.setattr(np, "meshgrid", meshgrid)
+    work()
+    return most[0]
+
+
+def test_products_one_at_a_time(monkeypatch):
+    """(The values above go wrong only now and then when they are not.)"""
     rng = np.random.default_rng(1)
     x, y = rng.random((2, 6 * CHUNK)) - 0.5
-    I.square_patch_pressure(x, y, kmax=19)
-    assert most[0] == 1
+    assert _most_threads_in_a_product(
+        monkeypatch, lambda: I.square_patch_pressure(x, y, kmax=19)) == 1
+
+
+def test_products_of_callers_threads(monkeypatch):
+    """Several threads that make an input each, as a client of the serving engine may."""
+    rng = np.random.default_rng(2)
+    x, y = rng.random((2, 300_000)) - 0.5
+
+    def work():
+        with ThreadPoolExecutor(max_workers=6) as ex:
+            list(ex.map(lambda _: I.square_patch_pressure(x, y, kmax=49), range(18)))
+
+    assert _most_threads_in_a_product(monkeypatch, work) == 1
